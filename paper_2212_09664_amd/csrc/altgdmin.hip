@@ -64,6 +64,7 @@ void carve(altgdmin_ctx* c) {
   c->o_pairs = take(sizeof(int2) * (size_t)q * c->width);
   c->o_pairof = take(sizeof(int32_t) * (size_t)q * c->width);
   c->o_unitof = take(sizeof(int32_t) * (size_t)q * c->width);
+  c->o_imap = take(c->lines ? 0 : sizeof(int32_t) * (size_t)q * n);
   c->o_Ui = take(sizeof(float2) * (size_t)n * r);
   const size_t ysz = sizeof(float2) * (size_t)q * nc * p.m_max;
   c->o_yh = take(c->lines ? ysz : 0);
@@ -502,147 +503,145 @@ hipError_t one_iteration(altgdmin_ctx* c, float2* U, float2* U_prev) {
 
 namespace ag_host {
 
-// X = A^H(Y) scaled per column (back-projection when trunc/scale are set)
-hipError_t adjoint_op(altgdmin_ctx* c, const float2* Y, float2* X, int trunc, int scale_mk) {
+// the adjoint columns: k-space rows at src (compact sampled rows of line
+// masks, else full images) to images img0 .. img0 + images - 1 of dst
+ColAdjArgs col_adj_args(altgdmin_ctx* c, const float2* src, float2* dst) {
   const altgdmin_params& p = c->p;
-  hipError_t e;
-  float2* T = c->at<float2>(c->o_T) + (size_t)c->n * p.q;  // after the X0 slot
+  ColAdjArgs d{};
+  d.src = src;
   if (c->lines) {
-    RowArgs ra{};
-    ra.src = Y;
-    ra.dst = T;
-    ra.tw = c->at<float2>(c->o_twx);
-    ra.nrows = (long)p.q * p.nc * c->lmax;
-    ra.m_k = c->m_k;
-    ra.nc = p.nc;
-    ra.lmax = c->lmax;
-    ra.scale = (float)(1.0 / sqrt((double)p.nx));
-    ra.trunc = trunc;
-    ra.trunc_count = trunc ? &c->st()->n_trunc : nullptr;
-    ra.st = c->st();
-    e = launch_rows(p.nx, ra, true, c->stream);
-    if (e != hipSuccess) return e;
-    ColAdjArgs d{};
-    d.src = T;
     d.src_c_stride = (long)c->lmax * p.nx;
     d.src_img_stride = (long)p.nc * c->lmax * p.nx;
     d.rows = c->mask;
     d.rows_img_stride = c->width;
-    d.m_k_rows = c->m_k;
-    d.coils = c->coils;
-    d.n = c->n;
-    d.nx = p.nx;
-    d.nc = p.nc;
-    d.tw = c->at<float2>(c->o_twy);
-    d.dst = X;
-    d.dst_img_stride = c->n;
-    d.m_k_scale = scale_mk ? c->m_k : nullptr;
-    d.scale = (float)(1.0 / sqrt((double)p.ny));
-    d.st = c->st();
-    return launch_cols(p.ny, nullptr, &d, p.nx, p.q, p.nc, c->stream);
-  }
-  for (int k0 = 0; k0 < p.q; k0 += c->kc) {
-    const int kc = std::min(c->kc, p.q - k0);
-    const long nimg = (long)kc * p.nc * c->n;
-    hipLaunchKernelGGL(k_zero, dim3(1024), dim3(256), 0, c->stream, T, nimg);
-    hipLaunchKernelGGL(k_scatter, dim3((p.m_max + 255) / 256, kc, p.nc), dim3(256), 0, c->stream, Y, c->mask,
-                       c->m_k, p.m_max, p.nc, k0, T, (long)c->n, (long)p.nc * c->n, c->st(), trunc,
-                       trunc ? &c->st()->n_trunc : nullptr);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    RowArgs ra{};
-    ra.src = ra.dst = T;
-    ra.tw = c->at<float2>(c->o_twx);
-    ra.nrows = (long)kc * p.nc * p.ny;
-    ra.scale = (float)(1.0 / sqrt((double)p.nx));
-    ra.st = c->st();
-    e = launch_rows(p.nx, ra, true, c->stream);
-    if (e != hipSuccess) return e;
-    ColAdjArgs d{};
-    d.src = T;
+    d.m_k = c->m_k;
+  } else {
     d.src_c_stride = c->n;
     d.src_img_stride = (long)p.nc * c->n;
-    d.coils = c->coils;
-    d.n = c->n;
-    d.nx = p.nx;
-    d.nc = p.nc;
-    d.tw = c->at<float2>(c->o_twy);
-    d.dst = X + (size_t)k0 * c->n;
-    d.dst_img_stride = c->n;
-    d.m_k_scale = scale_mk ? c->m_k + k0 : nullptr;
-    d.scale = (float)(1.0 / sqrt((double)p.ny));
-    d.st = c->st();
-    e = launch_cols(p.ny, nullptr, &d, p.nx, kc, p.nc, c->stream);
-    if (e != hipSuccess) return e;
   }
-  return hipSuccess;
+  d.coils = c->coils;
+  d.n = c->n;
+  d.nx = p.nx;
+  d.nc = p.nc;
+  d.tw = c->at<float2>(c->o_twy);
+  d.dst = dst;
+  d.dst_img_stride = c->n;
+  d.scale = (float)(1.0 / sqrt((double)p.ny));
+  d.st = c->st();
+  return d;
 }
 
-
-
-hipError_t forward_op(altgdmin_ctx* c, const float2* X, float2* Y) {
+// the forward columns of images src to k-space rows at dst, laid out as above
+ColFwdArgs col_fwd_args(altgdmin_ctx* c, const float2* src, float2* dst) {
   const altgdmin_params& p = c->p;
-  hipStream_t s = c->stream;
+  ColFwdArgs f{};
+  f.src = src;
+  f.coils = c->coils;
+  f.n = c->n;
+  f.nx = p.nx;
+  f.nc = p.nc;
+  f.tw = c->at<float2>(c->o_twy);
+  f.dst = dst;
   if (c->lines) {
-    ColFwdArgs f{};
-    f.src = X;
-    f.src_img_stride = c->n;
-    f.coils = c->coils;
-    f.n = c->n;
-    f.nx = p.nx;
-    f.tw = c->at<float2>(c->o_twy);
-    f.dst = Y;
     f.dst_c_stride = p.m_max;
     f.dst_img_stride = (long)p.nc * p.m_max;
     f.rows = c->mask;
     f.rows_img_stride = c->width;
     f.m_k = c->m_k;
-    f.zero_pad_rows = c->lmax;
-    f.scale = (float)(1.0 / sqrt((double)p.ny));
-    f.st = c->st();
-    AGCHK(launch_cols(p.ny, &f, nullptr, p.nx, p.q, p.nc, s));
-    RowArgs ra{};
-    ra.src = ra.dst = Y;
-    ra.tw = c->at<float2>(c->o_twx);
-    ra.nrows = (long)p.q * p.nc * c->lmax;
-    ra.m_k = c->m_k;
-    ra.nc = p.nc;
-    ra.lmax = c->lmax;
-    ra.scale = (float)(1.0 / sqrt((double)p.nx));
-    ra.st = c->st();
-    AGCHK(launch_rows(p.nx, ra, false, s));
-    return hipSuccess;
-  }
-  float2* T = c->at<float2>(c->o_T) + (size_t)c->n * p.q;
-  for (int k0 = 0; k0 < p.q; k0 += c->kc) {
-    const int kc = std::min(c->kc, p.q - k0);
-    ColFwdArgs f{};
-    f.src = X + (size_t)k0 * c->n;
-    f.src_img_stride = c->n;
-    f.coils = c->coils;
-    f.n = c->n;
-    f.nx = p.nx;
-    f.tw = c->at<float2>(c->o_twy);
-    f.dst = T;
+    f.pad_rows = c->lmax;
+  } else {
     f.dst_c_stride = c->n;
     f.dst_img_stride = (long)p.nc * c->n;
-    f.scale = (float)(1.0 / sqrt((double)p.ny));
-    f.st = c->st();
-    AGCHK(launch_cols(p.ny, &f, nullptr, p.nx, kc, p.nc, s));
-    RowArgs ra{};
-    ra.src = ra.dst = T;
-    ra.tw = c->at<float2>(c->o_twx);
-    ra.nrows = (long)kc * p.nc * p.ny;
-    ra.scale = (float)(1.0 / sqrt((double)p.nx));
-    ra.st = c->st();
-    AGCHK(launch_rows(p.nx, ra, false, s));
-    hipLaunchKernelGGL(k_gather, dim3((p.m_max + 255) / 256, kc, p.nc), dim3(256), 0, s, T, (long)c->n,
-                       (long)p.nc * c->n, c->mask, c->m_k, p.m_max, p.nc, k0, Y, c->st());
-    AGCHK(hipGetLastError());
+  }
+  f.scale = (float)(1.0 / sqrt((double)p.ny));
+  f.st = c->st();
+  return f;
+}
+
+// the x transform of every measurement line (line masks)
+RowArgs row_args(altgdmin_ctx* c, const float2* src, float2* dst) {
+  const altgdmin_params& p = c->p;
+  RowArgs ra{};
+  ra.src = src;
+  ra.dst = dst;
+  ra.tw = c->at<float2>(c->o_twx);
+  ra.nrows = (long)p.q * p.nc * c->lmax;
+  ra.m_k = c->m_k;
+  ra.nc = p.nc;
+  ra.lmax = c->lmax;
+  ra.scale = (float)(1.0 / sqrt((double)p.nx));
+  ra.st = c->st();
+  return ra;
+}
+
+// the row pass between k-space images T and measurements (general masks)
+IndexRowArgs index_row_args(altgdmin_ctx* c, float2* T) {
+  const altgdmin_params& p = c->p;
+  IndexRowArgs a{};
+  a.T = T;
+  a.imap = c->at<int32_t>(c->o_imap);
+  a.n = c->n;
+  a.nc = p.nc;
+  a.ny = p.ny;
+  a.m_max = p.m_max;
+  a.m_k = c->m_k;
+  a.tw = c->at<float2>(c->o_twx);
+  a.scale = (float)(1.0 / sqrt((double)p.nx));
+  a.st = c->st();
+  return a;
+}
+
+// X = A^H(Y) scaled per column (back-projection when trunc/scale are set)
+hipError_t adjoint_op(altgdmin_ctx* c, const float2* Y, float2* X, int trunc, int scale_mk) {
+  const altgdmin_params& p = c->p;
+  float2* T = c->at<float2>(c->o_T) + (size_t)c->n * p.q;  // after the X0 slot
+  ColAdjArgs d = col_adj_args(c, T, X);
+  d.m_k_scale = scale_mk ? c->m_k : nullptr;
+  if (c->lines) {
+    RowArgs ra = row_args(c, Y, T);
+    ra.trunc = trunc;
+    ra.trunc_count = trunc ? &c->st()->n_trunc : nullptr;
+    AGCHK(launch_rows(p.nx, ra, true, c->stream));
+    return launch_cols_adj(p.ny, d, false, p.q, c->stream);
+  }
+  IndexRowArgs ir = index_row_args(c, T);
+  ir.yin = Y;
+  ir.trunc = trunc;
+  ir.trunc_count = trunc ? &c->st()->n_trunc : nullptr;
+  for (int k0 = 0; k0 < p.q; k0 += c->kc) {
+    const int kc = std::min(c->kc, p.q - k0);
+    ir.img0 = d.img0 = k0;
+    AGCHK(launch_index_rows(p.nx, ir, IDX_ADJ, false, kc, c->stream));
+    AGCHK(launch_cols_adj(p.ny, d, false, kc, c->stream));
   }
   return hipSuccess;
 }
 
+// Y = A(X + add 1^T), or sub - that where sub is given (X, add, sub may be null)
+hipError_t forward_op(altgdmin_ctx* c, const float2* X, float2* Y, const float2* add, const float2* sub) {
+  const altgdmin_params& p = c->p;
+  if (c->lines) {
+    ColFwdArgs f = col_fwd_args(c, X, Y);
+    f.add = add;
+    AGCHK(launch_cols_fwd(p.ny, f, false, p.q, c->stream));
+    RowArgs ra = row_args(c, Y, Y);
+    ra.sub = sub;
+    return launch_rows(p.nx, ra, false, c->stream);
+  }
+  float2* T = c->at<float2>(c->o_T) + (size_t)c->n * p.q;
+  ColFwdArgs f = col_fwd_args(c, X, T);
+  f.add = add;
+  IndexRowArgs ir = index_row_args(c, T);
+  ir.y = Y;
+  ir.yin = sub;
+  for (int k0 = 0; k0 < p.q; k0 += c->kc) {
+    const int kc = std::min(c->kc, p.q - k0);
+    f.img0 = ir.img0 = k0;
+    AGCHK(launch_cols_fwd(p.ny, f, false, kc, c->stream));
+    AGCHK(launch_index_rows(p.nx, ir, IDX_FWD, false, kc, c->stream));
+  }
+  return hipSuccess;
+}
 
 hipError_t spectral_eig(altgdmin_ctx* c, int r_eig, double* lam_out) {
   const altgdmin_params& p = c->p;
@@ -790,10 +789,12 @@ altgdmin_status altgdmin_set_problem(altgdmin_ctx* c, const void* d_coils, const
     HIPCHK(launch_gram_work(c->at<int2>(c->o_unitspan), c->at<int4>(c->o_gwork), c->at<int4>(c->o_lineord),
                             c->n_loc, c->st(), s));
 
+  if (!c->lines)
+    hipLaunchKernelGGL(k_fill_i32, dim3(1024), dim3(256), 0, s, c->at<int32_t>(c->o_imap), -1, (long)p.q * c->n);
   hipLaunchKernelGGL(k_inv_fill, dim3((c->width + 255) / 256, p.q), dim3(256), 0, s, c->mask, c->m_k,
-                     c->width, c->per, c->at<uint32_t>(c->o_bitmap), c->nw, c->at<int32_t>(c->o_locptr),
+                     c->width, c->per, c->n_loc, c->at<uint32_t>(c->o_bitmap), c->nw, c->at<int32_t>(c->o_locptr),
                      c->at<int32_t>(c->o_loc2unit), c->at<int2>(c->o_pairs), c->at<int32_t>(c->o_pairof),
-                     c->at<int32_t>(c->o_unitof), c->st());
+                     c->at<int32_t>(c->o_unitof), c->lines ? nullptr : c->at<int32_t>(c->o_imap), c->st());
   HIPCHK(hipGetLastError());
   if (c->y) {
     hipLaunchKernelGGL(k_ysq, dim3(p.q, p.nc), dim3(AG_NT), 0, s, c->y, c->m_k, p.nc, p.m_max,
@@ -804,16 +805,8 @@ altgdmin_status altgdmin_set_problem(altgdmin_ctx* c, const void* d_coils, const
                        c->st());
     HIPCHK(hipGetLastError());
     if (c->lines) {
-      RowArgs ra{};
-      ra.src = c->y;
-      ra.dst = c->at<float2>(c->o_T);  // frame-major hybrid data, temporary
-      ra.tw = c->at<float2>(c->o_twx);
-      ra.nrows = (long)p.q * p.nc * c->lmax;
-      ra.m_k = c->m_k;
-      ra.nc = p.nc;
-      ra.lmax = c->lmax;
-      ra.scale = (float)(1.0 / sqrt((double)p.nx));
-      ra.st = c->st();
+      // frame-major hybrid data, temporary
+      const RowArgs ra = ag_host::row_args(c, c->y, c->at<float2>(c->o_T));
       HIPCHK(launch_rows(p.nx, ra, true, s));
       // per-line layout: the largest pair count is q per line
       hipLaunchKernelGGL(k_build_yu, dim3(p.q * c->width, p.nc), dim3(256), 0, s, c->at<float2>(c->o_T),
@@ -1021,7 +1014,7 @@ altgdmin_status altgdmin_gradient(altgdmin_ctx* c, const void* d_U, void* d_B, v
 altgdmin_status altgdmin_apply_A(altgdmin_ctx* c, const void* d_X, void* d_Y) {
   if (!c || !d_X || !d_Y) return ALTGDMIN_EINVAL;
   if (!c->bound) return ALTGDMIN_ESTATE;
-  return map_hip(ag_host::forward_op(c, static_cast<const float2*>(d_X), static_cast<float2*>(d_Y)));
+  return map_hip(ag_host::forward_op(c, static_cast<const float2*>(d_X), static_cast<float2*>(d_Y), nullptr, nullptr));
 }
 
 altgdmin_status altgdmin_apply_AH(altgdmin_ctx* c, const void* d_Y, void* d_X) {

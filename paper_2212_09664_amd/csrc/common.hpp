@@ -264,28 +264,50 @@ template <> struct FftPlan<128> { static constexpr int P = 2, R0 = 16, RL = 8;  
 template <> struct FftPlan<256> { static constexpr int P = 2, R0 = 16, RL = 16; };
 template <> struct FftPlan<512> { static constexpr int P = 3, R0 = 8,  RL = 8;  };
 
-template <int N, int TX, int NT>
+// REV swaps the radices of the first and the last pass (the input layout of
+// the reversed plan is the output layout of the plain one and the other way
+// round, so that a transform can feed an inverse one without leaving its
+// registers).  ROWS transforms TX contiguous rows instead of TX interleaved
+// columns: consecutive threads take consecutive elements of a row, so that
+// memory rows are read and written in whole segments, and the LDS tile holds
+// row after row, one element of padding after every 16 (the first pass's
+// strided writes then fall in different banks).
+template <int N, int TX, int NT, bool REV = false, bool ROWS = false>
 struct FftGeom {
   using PL = FftPlan<N>;
-  static constexpr int R0 = PL::R0, RL = PL::RL;
+  static constexpr int R0 = REV ? PL::RL : PL::R0, RL = REV ? PL::R0 : PL::RL;
   static constexpr int G0 = TX * (N / R0), IT0 = (G0 + NT - 1) / NT;
   static constexpr int GL = TX * (N / RL), ITL = (GL + NT - 1) / NT;
+  static constexpr int PITCH = N + N / 16;                      // ROWS: LDS row pitch
+  static constexpr int LDS = PL::P == 1 ? 1 : (ROWS ? PITCH * TX : N * TX);  // float2 entries of the tile
   __device__ static bool in_ok(int g) { return (G0 % NT == 0) || g < G0; }
   __device__ static bool out_ok(int g) { return (GL % NT == 0) || g < GL; }
-  __device__ static int in_row(int g, int r) { return g / TX + r * (N / R0); }
+  // column (ROWS: row of the batch) and sub-index of group g of a pass of radix R
+  template <int R> __device__ static int colr(int g) { return ROWS ? g / (N / R) : g % TX; }
+  template <int R> __device__ static int jr(int g) { return ROWS ? g % (N / R) : g / TX; }
+  __device__ static int in_col(int g) { return colr<R0>(g); }
+  __device__ static int out_col(int g) { return colr<RL>(g); }
+  __device__ static int in_row(int g, int r) { return jr<R0>(g) + r * (N / R0); }
   __device__ static int out_row(int g, int r) {
-    return PL::P == 1 ? (g / TX) * R0 + r : g / TX + r * (N / RL);
+    return PL::P == 1 ? jr<RL>(g) * R0 + r : jr<RL>(g) + r * (N / RL);
   }
+  __device__ static int at(int e, int col) { return ROWS ? col * PITCH + e + e / 16 : e * TX + col; }
 };
 
-template <int N, int TX, int NT, bool INV, int IT0_, int R0_, int ITL_, int RL_>
+// CONJ: tw is the forward table and the transform wants its conjugate
+template <int N, int TX, int NT, bool INV, bool CONJ = false, bool REV = false, bool ROWS = false, int IT0_, int R0_,
+          int ITL_, int RL_>
 __device__ __forceinline__ void fft_regs(float2 (&v0)[IT0_][R0_], float2 (&vo)[ITL_][RL_], float2* s,
                                          const float2* __restrict__ tw) {
-  using GM = FftGeom<N, TX, NT>;
+  using GM = FftGeom<N, TX, NT, REV, ROWS>;
   static_assert(IT0_ == GM::IT0 && R0_ == GM::R0 && ITL_ == GM::ITL && RL_ == GM::RL,
                 "register tiles do not match the plan");
   constexpr int R0 = GM::R0, RL = GM::RL, P = FftPlan<N>::P;
   const int tid = threadIdx.x % NT;
+  auto twd = [&](int t) {
+    const float2 w = tw[t];
+    return CONJ ? make_float2(w.x, -w.y) : w;
+  };
 #pragma unroll
   for (int it = 0; it < GM::IT0; ++it)
     if (GM::in_ok(tid + it * NT)) dft_reg<R0, INV>(v0[it]);
@@ -301,21 +323,49 @@ __device__ __forceinline__ void fft_regs(float2 (&v0)[IT0_][R0_], float2 (&vo)[I
     for (int it = 0; it < GM::IT0; ++it) {
       const int g = tid + it * NT;
       if (GM::in_ok(g)) {
-        const int col = g % TX, j = g / TX;
+        const int col = GM::in_col(g), j = GM::template jr<R0>(g);
 #pragma unroll
-        for (int r = 0; r < R0; ++r) s[(j * R0 + r) * TX + col] = v0[it][out_pos<R0>(r)];
+        for (int r = 0; r < R0; ++r) s[GM::at(j * R0 + r, col)] = v0[it][out_pos<R0>(r)];
       }
     }
     __syncthreads();
-    if constexpr (P == 3) stockham_pass<N, 8, TX, NT, INV, false>(s, tw, R0);
+    if constexpr (P == 3) {  // the middle pass, radix 8 at Ns = R0, in place
+      constexpr int G = TX * (N / 8), IT = (G + NT - 1) / NT;
+      float2 v[IT][8];
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int g = tid + it * NT;
+        if ((G % NT == 0) || g < G) {
+          const int col = GM::template colr<8>(g), j = GM::template jr<8>(g);
+#pragma unroll
+          for (int r = 0; r < 8; ++r) v[it][r] = s[GM::at(j + r * (N / 8), col)];
+          const int step = (j % R0) * (N / (R0 * 8));
+#pragma unroll
+          for (int r = 1; r < 8; ++r) v[it][r] = cmul(v[it][r], twd(step * r));
+          dft_reg<8, INV>(v[it]);
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int g = tid + it * NT;
+        if ((G % NT == 0) || g < G) {
+          const int col = GM::template colr<8>(g), j = GM::template jr<8>(g);
+          const int d = (j / R0) * R0 * 8 + (j % R0);
+#pragma unroll
+          for (int r = 0; r < 8; ++r) s[GM::at(d + r * R0, col)] = v[it][out_pos<8>(r)];
+        }
+      }
+      __syncthreads();
+    }
     // last pass: Ns = N/RL, reads rows j + r*Ns, outputs rows j + r*Ns
 #pragma unroll
     for (int it = 0; it < GM::ITL; ++it) {
       const int g = tid + it * NT;
       if (GM::out_ok(g)) {
-        const int col = g % TX, j = g / TX;
+        const int col = GM::out_col(g), j = GM::template jr<RL>(g);
 #pragma unroll
-        for (int r = 0; r < RL; ++r) vo[it][r] = s[(j + r * (N / RL)) * TX + col];
+        for (int r = 0; r < RL; ++r) vo[it][r] = s[GM::at(j + r * (N / RL), col)];
       }
     }
     __syncthreads();
@@ -323,9 +373,9 @@ __device__ __forceinline__ void fft_regs(float2 (&v0)[IT0_][R0_], float2 (&vo)[I
     for (int it = 0; it < GM::ITL; ++it) {
       const int g = tid + it * NT;
       if (GM::out_ok(g)) {
-        const int j = g / TX;
+        const int j = GM::template jr<RL>(g);
 #pragma unroll
-        for (int r = 1; r < RL; ++r) vo[it][r] = cmul(vo[it][r], tw[j * r]);
+        for (int r = 1; r < RL; ++r) vo[it][r] = cmul(vo[it][r], twd(j * r));
         dft_reg<RL, INV>(vo[it]);
         float2 t[RL];
 #pragma unroll

@@ -55,7 +55,7 @@ struct altgdmin_ctx {
   int bound = 0, initialized = 0;
   // workspace carve
   size_t o_st, o_twx, o_twy, o_bitmap, o_locptr, o_loc2unit, o_unitloc, o_pairs, o_pairof, o_yh, o_ysq,
-      o_cost, o_W, o_K, o_P, o_hp, o_B, o_G, o_qpart, o_qtot, o_rfac, o_Vs, o_V, o_T, o_Ui, o_unitof, o_unitspan, o_bcp, o_Uc,
+      o_cost, o_W, o_K, o_P, o_hp, o_B, o_G, o_qpart, o_qtot, o_rfac, o_Vs, o_V, o_T, o_Ui, o_unitof, o_imap, o_unitspan, o_bcp, o_Uc,
       o_fcmp, o_planes, o_gwork, o_lineord, o_coilb, o_yg, o_ysqp, o_stsrc, o_end;
   size_t T_bytes;
   // timing
@@ -79,8 +79,14 @@ namespace ag_host {
 // X = A^H(Y) (n x q, column-major), scaled per column by 1/sqrt(m_k mbar)
 // when scale_mk, with the truncation of Algorithm 2 when trunc
 hipError_t adjoint_op(altgdmin_ctx* c, const float2* Y, float2* X, int trunc, int scale_mk);
-// Y = A(X) in the padded measurement layout
-hipError_t forward_op(altgdmin_ctx* c, const float2* X, float2* Y);
+// Y = A(X + add 1^T) in the padded measurement layout, or sub - that on the
+// valid samples (X, add and sub may each be null)
+hipError_t forward_op(altgdmin_ctx* c, const float2* X, float2* Y, const float2* add, const float2* sub);
+// the argument blocks of the operators' passes over every frame (kernels.hpp)
+ColAdjArgs col_adj_args(altgdmin_ctx* c, const float2* src, float2* dst);
+ColFwdArgs col_fwd_args(altgdmin_ctx* c, const float2* src, float2* dst);
+RowArgs row_args(altgdmin_ctx* c, const float2* src, float2* dst);
+IndexRowArgs index_row_args(altgdmin_ctx* c, float2* T);
 // the truncated back-projection X_0 (into the workspace) and the top r_eig
 // eigenpairs of X_0^H X_0: eigenvalues to lam_out (device, descending) when
 // it is non-null (then no eigenvectors), else V_r Sigma_r^-1 for the context's r

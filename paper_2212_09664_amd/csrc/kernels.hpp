@@ -6,6 +6,43 @@
 
 namespace ag {
 
+// The column and row passes of the measurement operators: CT image columns
+// (or CT contiguous rows) per workgroup of NT threads, such that every thread
+// has a whole radix group in both passes of the transform and the LDS tile
+// stays at 32 KB or less (512: three passes).
+template <int N> struct OpTile;
+template <> struct OpTile<8>   { static constexpr int CT = 64, NT = 64;  };
+template <> struct OpTile<16>  { static constexpr int CT = 64, NT = 64;  };
+template <> struct OpTile<32>  { static constexpr int CT = 32, NT = 128; };
+template <> struct OpTile<64>  { static constexpr int CT = 16, NT = 128; };
+template <> struct OpTile<128> { static constexpr int CT = 16, NT = 128; };
+template <> struct OpTile<256> { static constexpr int CT = 16, NT = 256; };
+template <> struct OpTile<512> { static constexpr int CT = 8,  NT = 256; };
+int op_tile(int N);  // OpTile<N>::CT
+
+// conjugate gradients, one system per image (the mean image: one; MEC-1: one
+// per frame): the scalars after an iteration's stop test
+struct FrameCg {
+  double gamma, gamma0;  // ||s||^2 now and at the start
+  int32_t iters, done;
+  int32_t brk, pad;      // set by the step: ||A p|| = 0
+};
+
+// one CG iteration's scalars: iteration it reads slot (it - 1) & 1 and writes slot it & 1
+struct CgArgs {
+  const FrameCg* in;
+  FrameCg* out;
+  const double* nrm;  // [image][nnrm]: shares of ||s||^2
+  int nnrm, it;
+  double tol;
+};
+
+// ISTA (MEC-2)
+struct IstaState {
+  double omega, last_change;
+  int32_t iters, done, stop_next, pad;
+};
+
 struct RowArgs {
   const float2* src;
   float2* dst;
@@ -15,9 +52,9 @@ struct RowArgs {
   int nc, lmax;        // measurement-line layout when m_k != null
   float scale;
   int trunc;           // zero samples with |v|^2 > gamma before the transform
-  int check_halt;
   const DevState* st;
   int32_t* trunc_count;  // non-null with trunc: receives the number of samples zeroed
+  const float2* sub;   // non-null: store sub - result on the valid rows
 };
 
 __device__ __forceinline__ bool row_valid(const RowArgs& a, long rho, int N) {
@@ -28,32 +65,39 @@ __device__ __forceinline__ bool row_valid(const RowArgs& a, long rho, int N) {
   return l < a.m_k[k] / N;
 }
 
+// image columns -> k-space rows
 struct ColFwdArgs {
-  const float2* src;
-  long src_img_stride;
+  const float2* src;       // images, n apart (null: zero)
+  const float2* add;       // non-null: one image added to every src image
   const float2* coils;
   long n;
-  int nx;
+  int nx, nc;
+  int cgs;                 // coils per workgroup
   const float2* tw;
   float2* dst;
   long dst_c_stride, dst_img_stride;
-  const int32_t* rows;     // ky of each output row
+  const int32_t* rows;     // ky of each output row of an image (null: all rows)
   long rows_img_stride;
-  const int32_t* m_k;      // non-null: n_rows = m_k[img]/nx, rows per image
-  const int32_t* n_rows_ptr;  // non-null: n_rows = *n_rows_ptr
-  int zero_pad_rows;       // > 0: write zeros for rows n_rows..zero_pad_rows-1
+  const int32_t* m_k;      // with rows: n_rows = m_k[img]/nx
+  int pad_rows;            // with rows: zeros written for rows n_rows..pad_rows-1
   float scale;
-  int check_halt;
+  int img0;                // first image (src, rows, CG systems); dst starts at it
+  // CG: src is s, p = s + beta p_old is transformed and stored
+  const float2* p_old;
+  float2* p_new;
+  double* dot;             // with rows: [image][parts] shares of ||A p||^2
+  CgArgs cg;
+  const IstaState* ista;   // non-null: nothing to do once its done is set
   const DevState* st;
 };
 
+// k-space rows -> image columns, with the coil combine
 struct ColAdjArgs {
   const float2* src;
   long src_c_stride, src_img_stride;
-  const int32_t* rows;
+  const int32_t* rows;     // as in ColFwdArgs
   long rows_img_stride;
-  const int32_t* m_k_rows;    // non-null: n_rows = m_k_rows[img]/nx, rows per image
-  const int32_t* n_rows_ptr;  // non-null: n_rows = *n_rows_ptr
+  const int32_t* m_k;
   const float2* coils;
   long n;
   int nx, nc;
@@ -64,23 +108,49 @@ struct ColAdjArgs {
   long dst_part_stride;
   const int32_t* m_k_scale;   // non-null: scale by 1/sqrt(m_k[img] * mbar)
   float scale;
-  int accumulate;
-  int check_halt;
+  int img0;
+  // CGLS: x = 0 (first) or x += alpha p; with rows also r -= alpha q before the transform
+  int first;
+  float2 *x, *r;              // r: src, updated in place
+  const float2 *p, *q;
+  FrameCg* cg;                // this iteration's slot
+  const double* dot;
+  int ndot;
+  double* nrm;                // one coil group: [image][tiles] shares of ||s||^2, s = the result
+  const IstaState* ista;
+  const DevState* st;
+};
+
+// general masks: a row pass between the k-space rows T[image][c][ky][x] and
+// the measurements y[k][c][m_max]; imap[k][location] is the sample's position
+// in its frame, -1 where the frame does not sample
+struct IndexRowArgs {
+  float2* T;
+  const int32_t* imap;
+  long n;
+  int nc, ny, m_max, img0;
+  const int32_t* m_k;
+  const float2* tw;
+  float scale;
+  float2* y;               // forward: out
+  const float2* yin;       // adjoint: in; forward: stored as yin - result when non-null
+  int trunc;
+  int32_t* trunc_count;
+  // CGLS: forward adds its shares of ||q||^2; adjoint takes r - alpha q (stored)
+  double* dot;
+  FrameCg* cg;
+  float2* r;
+  const float2* q;
+  int ndot;
+  const IstaState* ista;
   const DevState* st;
 };
 
 hipError_t launch_rows(int N, const RowArgs& a, bool inv, hipStream_t st);
-hipError_t launch_cols(int N, const ColFwdArgs* f, const ColAdjArgs* d, int nx, int n_img, int nc,
-                       hipStream_t st);
-int col_tile(int N, int nx);
-int col_tile_adj(int N, int nx);
+hipError_t launch_cols_fwd(int N, const ColFwdArgs& a, bool cg, int images, hipStream_t st);
+hipError_t launch_cols_adj(int N, const ColAdjArgs& a, bool cgls, int images, hipStream_t st);
+enum { IDX_FWD = 0, IDX_ADJ = 1, IDX_RES = 2 };  // T -> y; y -> T; T -> F^H(y - F T) in T
+hipError_t launch_index_rows(int N, const IndexRowArgs& a, int mode, bool cgls, int images, hipStream_t st);
 
 __global__ void k_twiddle(float2* tw, int N);
-__global__ void k_gather(const float2* img, long img_stride_c, long img_stride_k, const int32_t* mask,
-                         const int32_t* m_k, int m_max, int nc, int k0, float2* y, const DevState* st);
-__global__ void k_scatter(const float2* y, const int32_t* mask, const int32_t* m_k, int m_max, int nc,
-                          int k0, float2* img, long img_stride_c, long img_stride_k, const DevState* st,
-                          int trunc, int32_t* trunc_count);
-__global__ void k_zero(float2* p, long n);
-
 }  // namespace ag

@@ -103,9 +103,9 @@ __global__ __launch_bounds__(1024) void k_inv_scan(const uint32_t* bitmap, int n
   }
 }
 
-__global__ void k_inv_fill(const int32_t* mask, const int32_t* m_k, int width, int per,
+__global__ void k_inv_fill(const int32_t* mask, const int32_t* m_k, int width, int per, int n_loc,
                            const uint32_t* bitmap, int nw, const int32_t* loc_ptr, const int32_t* loc2unit,
-                           int2* pairs, int32_t* pair_of, int32_t* unit_of, const DevState* st) {
+                           int2* pairs, int32_t* pair_of, int32_t* unit_of, int32_t* imap, const DevState* st) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x, k = blockIdx.y;
   if (st->err) return;
   if (e >= m_k[k] / per) return;
@@ -118,6 +118,11 @@ __global__ void k_inv_fill(const int32_t* mask, const int32_t* m_k, int width, i
   pairs[pos] = make_int2(k, e);
   pair_of[(long)k * width + e] = pos;
   unit_of[(long)k * width + e] = loc2unit[loc];
+  if (imap) imap[(long)k * n_loc + loc] = e;  // general masks: frame k's sample at the location
+}
+
+__global__ void k_fill_i32(int32_t* p, int32_t v, long n) {
+  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) p[i] = v;
 }
 
 // ||y_{k,c}||^2 in FP64, one workgroup per (frame k, coil c): part[k * nc + c]

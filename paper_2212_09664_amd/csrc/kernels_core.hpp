@@ -336,9 +336,10 @@ __global__ void k_inv_bitmap(const int32_t* mask, const int32_t* m_k, int width,
                              uint32_t* bitmap, int nw, DevState* st);
 __global__ void k_inv_scan(const uint32_t* bitmap, int nw, int n_loc, int32_t* loc_ptr, int32_t* loc2unit,
                            int32_t* unit_loc, int2* unit_span, DevState* st);
-__global__ void k_inv_fill(const int32_t* mask, const int32_t* m_k, int width, int per, const uint32_t* bitmap,
-                           int nw, const int32_t* loc_ptr, const int32_t* loc2unit, int2* pairs, int32_t* pair_of,
-                           int32_t* unit_of, const DevState* st);
+__global__ void k_inv_fill(const int32_t* mask, const int32_t* m_k, int width, int per, int n_loc,
+                           const uint32_t* bitmap, int nw, const int32_t* loc_ptr, const int32_t* loc2unit, int2* pairs,
+                           int32_t* pair_of, int32_t* unit_of, int32_t* imap, const DevState* st);
+__global__ void k_fill_i32(int32_t* p, int32_t v, long n);
 __global__ void k_ysq(const float2* y, const int32_t* m_k, int nc, int m_max, double* part);
 __global__ void k_ysq_sum(const double* part, int q, int nc, double* ysq_k);
 __global__ void k_init_stats(const double* ysq_k, const int32_t* m_k, int q, double trunc_c, DevState* st);

@@ -1,61 +1,127 @@
 // Device state and kernels of the steps around the altGDmin loop (the mean
-// image, residuals, modelling-error corrections); see kernels_mri.hip.
+// image, the modelling-error corrections, the output); see kernels_normal.hip
+// and kernels_mri.hip.
 #pragma once
 
 #include "kernels_core.hpp"
 
 namespace ag {
 
-// conjugate gradients on one system (the mean image)
-struct CgState {
-  double gamma, gamma0, alpha, beta;
-  int32_t iters, done;
+// the normal operator over image columns (line masks) or k-space rows
+// (general masks, the mean image)
+struct NormalArgs {
+  const float2* s;        // the image of each system (the mean: the residual s; ISTA: E)
+  const float2* p_old;    // the mean: the last direction
+  float2* p_new;          // the mean: this iteration's direction
+  const float2* coils;
+  long n;
+  int nx, ny, nc;
+  const float2 *tw, *tw_x;
+  const int32_t* loc_ptr; // the mean: counts of frames per row or location
+  const int32_t* rows;    // ISTA: a frame's sampled rows and hybrid data [frame][c][line][x]
+  long rows_img_stride;
+  const int32_t* m_k;
+  const float2* y;
+  int m_max;
+  float2* w;              // line masks: out, one part per coil group
+  long part_stride;
+  int cgs;                // coils per group
+  float2* T;              // general masks: k-space rows [c][ky][x]
+  float scale;            // ISTA: 1 / sqrt(ny)
+  double* dot;            // the mean: shares of <p, A^H A p>
+  CgArgs cg;
+  const IstaState* ista;  // non-null: nothing to do once its done is set
+  const DevState* st;
 };
 
-// conjugate gradients on one system per frame (MEC-1)
-struct FrameCg {
-  double gamma, gamma0, alpha, beta;
-  int32_t iters, done;
+struct CgStepArgs {
+  const float2 *w, *p;
+  float2 *x, *s;
+  int nsum;               // parts of w
+  long part_stride, n;
+  FrameCg* cg;            // this iteration's slot
+  const double* dot;
+  int ndot;
+  double* nrm;
+  const DevState* st;
 };
 
-// ISTA (MEC-2)
-struct IstaState {
-  double omega, last_change;
-  int32_t iters, done, stop_next, pad;
-};
+// sum of part[0..nb) by one wave (every lane active), in a fixed order
+__device__ __forceinline__ double wave_sum_parts(const double* part, int nb, int lane) {
+  double s = 0.0;
+  for (int i = lane; i < nb; i += 64) s += part[i];
+  return wave_sum(s);
+}
 
-constexpr int MRI_NB = 256;   // workgroups (and partial sums) of a single-system reduction
-constexpr int MRI_NBF = 64;   // workgroups per frame of a per-frame reduction
+// The start of CG iteration a.it for system `img`: the stop test of the
+// iteration before, beta, and the new scalars (written by the one workgroup
+// with `writer`).  Every wave computes the same values.  False: stopped.
+__device__ __forceinline__ bool cg_open(const CgArgs& a, int img, bool writer, float& beta) {
+  const int lane = threadIdx.x & 63;
+  const double g = wave_sum_parts(a.nrm + (long)img * a.nnrm, a.nnrm, lane);
+  FrameCg o;
+  beta = 0.f;
+  if (a.it == 0) {
+    o.gamma = o.gamma0 = g;
+    o.iters = 0;
+    o.done = !(g > 0.0);
+  } else {
+    const FrameCg i = a.in[img];
+    o = i;
+    o.done = i.done | i.brk;
+    if (!o.done) {
+      o.iters = i.iters + 1;
+      o.done = sqrt(g) <= a.tol * sqrt(i.gamma0);
+      beta = (float)(g / i.gamma);
+      o.gamma = g;
+    }
+  }
+  o.brk = 0;
+  if (writer && threadIdx.x == 0) a.out[img] = o;
+  return !o.done;
+}
 
-__global__ void k_count_scale(float2* T, long n, int nc, int loc_div, const int32_t* loc_ptr, const DevState* st);
-__global__ void k_colsum(const float2* X, long n, int q, float2* out, const DevState* st);
-__global__ void k_dot_parts(const float2* a, const float2* b, long n, double* part, const DevState* st);
-__global__ void k_cg_start(const double* part, int nb, CgState* cs, const DevState* st);
-__global__ void k_cg_alpha(const double* part, int nb, CgState* cs, const DevState* st);
-__global__ void k_cg_update_xs(float2* x, float2* s, const float2* p, const float2* w, long n, const CgState* cs,
-                               double* part, const DevState* st);
-__global__ void k_cg_beta(const double* part, int nb, double tol, CgState* cs, const DevState* st);
-__global__ void k_cg_update_p(float2* p, const float2* s, long n, const CgState* cs, const DevState* st);
-__global__ void k_frame_norm_parts(const float2* v, long len, double* part, const DevState* st);
-__global__ void k_frames_cg(const double* part, int nb, int q, int mode, double tol, FrameCg* fc, const DevState* st);
-__global__ void k_frames_axpy(float2* x, const float2* p, long len, const FrameCg* fc, int sign, const DevState* st);
-__global__ void k_frames_pupdate(float2* p, const float2* s, long len, const FrameCg* fc, const DevState* st);
-__global__ void k_form_z(const float2* X, const float2* zbar, long n, int q, float2* Z, const DevState* st);
-__global__ void k_sub_from(const float2* y, float2* out, const int32_t* m_k, int nc, int m_max, int q,
+// consecutive workgroups go to the eight XCDs in turn: tile b of a row of
+// nt tiles is dealt so that an XCD's tiles are neighbours, which share the
+// cache lines that a tile narrower than a line splits
+__device__ __forceinline__ int xcd_tile(int b, int nt) { return nt % 8 == 0 ? (b % 8) * (nt / 8) + b / 8 : b; }
+
+enum { NORMAL_MEAN = 0, NORMAL_ISTA = 1 };
+hipError_t launch_normal_lines(const NormalArgs& a, int mode, int images, int groups, hipStream_t s);
+hipError_t launch_normal_rows(const NormalArgs& a, hipStream_t s);  // the mean
+__global__ void k_cg_begin(const float2* src, int nsum, long part_stride, float2* s, float2* x, long n, double* nrm,
                            const DevState* st);
-__global__ void k_add(float2* a, const float2* b, long n, const DevState* st);
+__global__ void k_cg_step(CgStepArgs a);
+__global__ void k_cgls_sum(const float2* src, int nsum, long part_stride, float2* s, long n, double* nrm,
+                           const FrameCg* cg, const DevState* st);
+__global__ void k_cg_end(CgArgs a, const DevState* st);
+__global__ void k_line_sum(const float2* yu, const int32_t* loc_ptr, int nc, int nx, float2* T, const DevState* st);
+__global__ void k_loc_sum(const float2* y, const int2* pairs, const int32_t* loc_ptr, long n, int nc, int m_max,
+                          float2* T, const DevState* st);
 __global__ void k_expand(const float2* U, const float2* B, const float2* zbar, const float2* E, long n, int q, int r,
                          float2* Z, const DevState* st);
-__global__ void k_zero2(float2* a, long n);
-__global__ void k_copy2(const float2* a, float2* b, long n);
-__global__ void k_absmax_parts(const float2* v, long len, double* part, const IstaState* is, const DevState* st);
-__global__ void k_change_parts(const float2* a, const float2* b, long len, double* part, const IstaState* is,
-                               const DevState* st);
-__global__ void k_ista_step(const double* part, int nb, int t, double frac, double tol, IstaState* is,
-                            const DevState* st);
-__global__ void k_ista_commit(IstaState* is, const DevState* st);
-__global__ void k_ista_reset(IstaState* is);
-hipError_t launch_tdft(const float2* in, float2* out, long n, int q, bool inv, bool thresh, const IstaState* is,
-                       const DevState* st, hipStream_t s);
+
+// ISTA's temporal step (kernels_mri.hip); partial sums: one pair per 64 pixels
+struct IstaArgs {
+  float2* E;              // n x q
+  const float2* w;        // parts of A^H(yres - A(E))
+  int nsum;
+  long part_stride;
+  float2* M;              // n x q: M_{t-1} in, M_t out
+  long n;
+  int q, t;
+  float scale;            // 1 / sqrt(q)
+  double frac, tol;
+  const IstaState* in;    // the scalars of update t - 1 / t
+  IstaState* out;
+  const double* pin;      // partial sums of update t - 1 / t
+  double* pout;
+  const DevState* st;
+};
+enum { ISTA_FIRST = 0, ISTA_THRESH = 1, ISTA_STEP = 2 };
+hipError_t launch_ista_dft(const IstaArgs& a, int phase, hipStream_t s);
+__global__ void k_ista_begin(float2* E, long total, IstaState* is);
+__global__ void k_ista_end(const IstaState* in, IstaState* out, const double* pin, int np, int t, double tol,
+                           const DevState* st);
 
 }  // namespace ag

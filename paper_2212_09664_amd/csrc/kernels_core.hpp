@@ -116,17 +116,27 @@ struct PdftArgs {
 // warm-start CNN
 struct ConvArgs {
   const float* X;        // [b][cin][H][W]
-  const float* Wp;       // packed weights [kappa][32], kappa = tap*cin + ci, then the bias row
+  const void* Wq;        // packed BF16 weights (k_cnn_pack)
+  const float* bias;     // [cout], or null
   float* Y;              // [b][cout][H][W]
   const float* mask;     // optional [b][cout][H][W]: Y = 0 where mask <= 0
-  int cin, cout, H, W, bias, relu;
+  int cin, cout, H, W, relu;
+};
+
+struct CnnLayers {       // one entry per layer
+  const float* W[4];     // parameters: W[cout][cin][3][3], then b[cout]
+  void *Wf[4], *Wb[4];   // packed weights: forward, input gradient (null: none)
+  float* part[4];        // weight-gradient partials
+  float* g[4];           // gradient of the parameters
+  int cin[4], cout[4], kp[4];
+  int nparts;
 };
 
 struct WgradArgs {
   const float* X;        // layer input [b][cin][H][W]
   const float* dY;       // gradient at the layer output [b][cout][H][W]
   float* part;           // [b][band][kp][32] partial weight gradients
-  int cin, cout, H, W, kp, rows_per_band;
+  int cin, cout, H, W, kp;
 };
 
 struct LossArgs {
@@ -135,9 +145,10 @@ struct LossArgs {
   double2* part;         // [b][chunk][tri(2r)] Gram partials of [M Ut]
   double2* P;            // [b][2][r][r]: C^H G^-1, G^-1 C C^H G^-1
   double* loss_b;        // [b]
+  double* loss;          // their mean
   float* dY4;            // [b][2r][n]
   long n, chunk;
-  int r, nchunks;
+  int r, nchunks, batch;
   float scale;           // 1 / batch
 };
 
@@ -371,11 +382,13 @@ hipError_t launch_fold2(const FoldArgs& a, bool lines, int grid_x, int grid_y, h
 hipError_t launch_gram_work(const int2* unit_span, int4* items, int4* line_order, int n_loc, DevState* st,
                             hipStream_t s);
 __global__ void k_build_yg(const float2* yu, const int4* items, int nc, int nx, float2* yg, const DevState* st);
-hipError_t launch_cnn_pack(const float* Wl, int cin, int cout, int kp, int kpb, float* Wf, float* Wb, hipStream_t s);
+constexpr int CNN_BAND = 8;  // image rows per weight-gradient partial
+size_t cnn_pack_bytes(int cin);  // packed weights of a convolution over cin channels
+hipError_t launch_cnn_pack(const CnnLayers& a, hipStream_t s);
 hipError_t launch_conv(const ConvArgs& a, int batch, hipStream_t s);
-hipError_t launch_wgrad(const WgradArgs& a, int bands, int batch, int nparam_layer, float* g, float scale,
-                        hipStream_t s);
-hipError_t launch_loss(const LossArgs& a, int batch, double* d_loss, hipStream_t s);
+hipError_t launch_wgrad(const WgradArgs& a, int batch, hipStream_t s);
+hipError_t launch_wgrad_reduce(const CnnLayers& a, hipStream_t s);
+hipError_t launch_loss(const LossArgs& a, hipStream_t s);
 hipError_t launch_cnn_to_M(const float* Y4, int r, long n, int batch, float2* M, hipStream_t s);
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, long n, float lr, int step, hipStream_t s);
 hipError_t launch_cnn_planes(const float2* X, long n, int q, double* partial, float* out, hipStream_t s);

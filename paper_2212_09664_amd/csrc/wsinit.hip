@@ -14,12 +14,12 @@ struct wsinit_ctx {
   long n;
   hipStream_t stream;
   struct Layer {
-    int cin, cout, kp, kpb;
+    int cin, cout, kp;
     long poff, nparam;
-    size_t o_wf, o_wb;
+    size_t o_wf, o_wb, o_part;
   } L[4];
-  int bands, rows_per_band, chunk, nchunks;
-  size_t o_h[4], o_y4, o_dz[2], o_dy4, o_part, o_lpart, o_P, o_lossb, bytes;
+  int bands, chunk, nchunks;
+  size_t o_h[4], o_y4, o_dz[2], o_dy4, o_lpart, o_P, o_lossb, bytes;
   long nparams;
   template <typename T>
   T* at(void* ws, size_t off) const {
@@ -37,24 +37,38 @@ namespace {
 
 bool aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 255) == 0; }
 
-altgdmin_status forward_layers(wsinit_ctx* h, const float* params, const float* in, int batch, void* ws) {
+// the layers' parameters, packed weights, gradient partials and gradients
+CnnLayers layers(const wsinit_ctx* h, const float* params, float* grads, int batch, void* ws) {
+  CnnLayers c{};
   for (int l = 0; l < 4; ++l) {
     const auto& Ly = h->L[l];
-    WCHK(launch_cnn_pack(params + Ly.poff, Ly.cin, Ly.cout, Ly.kp, Ly.kpb, h->at<float>(ws, Ly.o_wf),
-                         l > 0 ? h->at<float>(ws, Ly.o_wb) : nullptr, h->stream));
+    c.W[l] = params ? params + Ly.poff : nullptr;
+    c.Wf[l] = h->at<char>(ws, Ly.o_wf);
+    c.Wb[l] = l > 0 ? h->at<char>(ws, Ly.o_wb) : nullptr;
+    c.part[l] = h->at<float>(ws, Ly.o_part);
+    c.g[l] = grads ? grads + Ly.poff : nullptr;
+    c.cin[l] = Ly.cin;
+    c.cout[l] = Ly.cout;
+    c.kp[l] = Ly.kp;
   }
+  c.nparts = h->bands * batch;
+  return c;
+}
+
+altgdmin_status forward_layers(wsinit_ctx* h, const float* params, const float* in, int batch, void* ws) {
+  WCHK(launch_cnn_pack(layers(h, params, nullptr, batch, ws), h->stream));
   for (int l = 0; l < 4; ++l) {
     const auto& Ly = h->L[l];
     ConvArgs a{};
     a.X = l == 0 ? in : h->at<float>(ws, h->o_h[l]);
-    a.Wp = h->at<float>(ws, Ly.o_wf);
+    a.Wq = h->at<char>(ws, Ly.o_wf);
+    a.bias = params + Ly.poff + (long)Ly.cout * Ly.cin * 9;
     a.Y = l == 3 ? h->at<float>(ws, h->o_y4) : h->at<float>(ws, h->o_h[l + 1]);
     a.mask = nullptr;
     a.cin = Ly.cin;
     a.cout = Ly.cout;
     a.H = h->ny;
     a.W = h->nx;
-    a.bias = 1;
     a.relu = l < 3;
     WCHK(launch_conv(a, batch, h->stream));
   }
@@ -89,20 +103,19 @@ altgdmin_status wsinit_create(int32_t nx, int32_t ny, int32_t q, int32_t r, int3
     off += (b + 255) / 256 * 256;
     return o;
   };
+  h->bands = ny / CNN_BAND;
   long poff = 0;
-  int max_kp = 0;
   for (int l = 0; l < 4; ++l) {
     auto& Ly = h->L[l];
     Ly.cin = l == 0 ? 2 * q : width;
     Ly.cout = l == 3 ? 2 * r : width;
     Ly.kp = (9 * Ly.cin + 1 + 15) / 16 * 16;
-    Ly.kpb = 9 * Ly.cout;
     Ly.poff = poff;
     Ly.nparam = (long)Ly.cout * Ly.cin * 9 + Ly.cout;
     poff += Ly.nparam;
-    Ly.o_wf = take(sizeof(float) * Ly.kp * 32);
-    Ly.o_wb = take(sizeof(float) * Ly.kpb * 32);
-    if (Ly.kp > max_kp) max_kp = Ly.kp;
+    Ly.o_wf = take(cnn_pack_bytes(Ly.cin));
+    Ly.o_wb = take(cnn_pack_bytes(Ly.cout));
+    Ly.o_part = take(sizeof(float) * (size_t)batch * h->bands * Ly.kp * 32);
   }
   h->nparams = poff;
   const size_t act = sizeof(float) * (size_t)batch * width * h->n;
@@ -112,9 +125,6 @@ altgdmin_status wsinit_create(int32_t nx, int32_t ny, int32_t q, int32_t r, int3
   h->o_dz[0] = take(act);
   h->o_dz[1] = take(act);
   h->o_dy4 = take(sizeof(float) * (size_t)batch * 2 * r * h->n);
-  h->rows_per_band = 8;
-  h->bands = ny / 8;
-  h->o_part = take(sizeof(float) * (size_t)batch * h->bands * max_kp * 32);
   h->chunk = 1024;
   h->nchunks = (int)((h->n + h->chunk - 1) / h->chunk);
   const int m = 2 * r;
@@ -165,8 +175,10 @@ altgdmin_status wsinit_loss_backward(wsinit_ctx* h, const float* params, const f
   la.chunk = h->chunk;
   la.r = h->r;
   la.nchunks = h->nchunks;
+  la.batch = batch;
+  la.loss = d_loss;
   la.scale = 1.0f / batch;
-  WCHK(launch_loss(la, batch, d_loss, h->stream));
+  WCHK(launch_loss(la, h->stream));
   // backward: dZ_3 = dY4; for each layer the weight gradient, then the
   // gradient at its input times the ReLU mask of that input
   const float* dz = h->at<float>(ws, h->o_dy4);
@@ -177,18 +189,17 @@ altgdmin_status wsinit_loss_backward(wsinit_ctx* h, const float* params, const f
     WgradArgs wa{};
     wa.X = X;
     wa.dY = dz;
-    wa.part = h->at<float>(ws, h->o_part);
+    wa.part = h->at<float>(ws, Ly.o_part);
     wa.cin = Ly.cin;
     wa.cout = Ly.cout;
     wa.H = h->ny;
     wa.W = h->nx;
     wa.kp = Ly.kp;
-    wa.rows_per_band = h->rows_per_band;
-    WCHK(launch_wgrad(wa, h->bands, batch, (int)Ly.nparam, grads + Ly.poff, 1.0f, h->stream));
+    WCHK(launch_wgrad(wa, batch, h->stream));
     if (l > 0) {
       ConvArgs a{};
       a.X = dz;
-      a.Wp = h->at<float>(ws, Ly.o_wb);
+      a.Wq = h->at<char>(ws, Ly.o_wb);
       float* dnext = h->at<float>(ws, h->o_dz[ping]);
       a.Y = dnext;
       a.mask = X;  // h_l = relu(z_{l-1})
@@ -196,13 +207,13 @@ altgdmin_status wsinit_loss_backward(wsinit_ctx* h, const float* params, const f
       a.cout = Ly.cin;
       a.H = h->ny;
       a.W = h->nx;
-      a.bias = 0;
       a.relu = 0;
       WCHK(launch_conv(a, batch, h->stream));
       dz = dnext;
       ping ^= 1;
     }
   }
+  WCHK(launch_wgrad_reduce(layers(h, params, grads, batch, ws), h->stream));
   return ALTGDMIN_OK;
 }
 

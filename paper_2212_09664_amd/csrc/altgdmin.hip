@@ -90,8 +90,7 @@ void carve(altgdmin_ctx* c) {
   // plus one slot for their sum
   c->o_qpart = take(sizeof(double2) * qo * (std::max(std::max(c->qr_nblk, init_nblk(c)), p.nx) + 1));
   c->o_qtot = take(sizeof(double2) * m_iter * (m_iter + 1) / 2);  // their sum (the fused step)
-  c->o_rfac = take(sizeof(float2) * r * r);
-  c->o_stsrc = take(sizeof(double2) * 193);  // deferred statistics of the fused step
+  c->o_stsrc = take(sizeof(double2) * STATS_SRC);  // deferred statistics of the step
   c->o_Vs = take(sizeof(float2) * (size_t)q * r);
   c->o_V = take(sizeof(double2) * 2 * (size_t)q * (q | 1));  // matrix and reflectors, odd row pitch
   // temp: X0 plus the truncated hybrid data (LINES) or a chunk of coil images (INDEX)
@@ -283,12 +282,24 @@ hipError_t gram_solve(altgdmin_ctx* c, int check_halt) {
   return e;
 }
 
-hipError_t cholqr(altgdmin_ctx* c, float2* U) {
+// the QR Gram's partials summed (FP64) and the kernel that factors and
+// updates, for either mode that updates
+hipError_t step_apply(altgdmin_ctx* c, QrSmallArgs qa, const ApplyArgs& aa) {
+  const int m = qa.mode == STEP_MODE_QR ? qa.r : 2 * qa.r;
+  hipError_t e = launch_partials_total(qa.part, qa.part_f32, qa.nblk, m * (m + 1) / 2, c->at<double2>(c->o_qtot),
+                                       c->stream);
+  if (e != hipSuccess) return e;
+  qa.part = c->at<double2>(c->o_qtot);
+  return launch_step_apply(qa, aa, c->stream);
+}
+
+// U = CholeskyQR of src (both n x r, column-major; may be the same), and its
+// pixel-major working copy
+hipError_t cholqr(altgdmin_ctx* c, const float2* src, float2* U) {
   const altgdmin_params& p = c->p;
-  hipError_t e0 = to_pixmajor(c, U);
-  if (e0 != hipSuccess) return e0;
   GramColsArgs g{};
-  g.A = c->at<float2>(c->o_Ui);
+  g.A = src;
+  g.a_colmajor = 1;
   g.m1 = p.r;
   g.m2 = 0;
   g.n = c->n;
@@ -302,22 +313,16 @@ hipError_t cholqr(altgdmin_ctx* c, float2* U) {
   qa.part = c->at<double2>(c->o_qpart);
   qa.nblk = c->qr_nblk;
   qa.r = p.r;
-  qa.mode = 1;
+  qa.mode = STEP_MODE_QR;
   qa.n = c->n;
   qa.q = p.q;
-  qa.rfac = c->at<float2>(c->o_rfac);
   qa.st = c->st();
-  e = launch_qr_small(qa, c->stream);
-  if (e != hipSuccess) return e;
   ApplyArgs aa{};
+  aa.src = src;
   aa.U = U;
   aa.Ui = c->at<float2>(c->o_Ui);
-  aa.rfac = c->at<float2>(c->o_rfac);
   aa.n = c->n;
-  aa.r = p.r;
-  aa.mode = 1;
-  aa.st = c->st();
-  return launch_apply(aa, c->stream);
+  return step_apply(c, qa, aa);
 }
 
 // b_k for every frame and the gradient at U (into the workspace's B and G)
@@ -381,8 +386,6 @@ hipError_t gradient_pieces(altgdmin_ctx* c, int check_halt) {
   return e;
 }
 
-// Gram of [U grad] (summing the partial gradients) and the small QR-step
-// work; mode 0 a step, mode 2 only the step size at the first iteration
 // the QR Gram of [U grad] (summing the adjoint's partial gradients)
 hipError_t qr_step_gram(altgdmin_ctx* c, int check_halt) {
   if (c->adj_qr) return hipSuccess;  // the adjoint transform wrote the block partials
@@ -423,74 +426,51 @@ QrSmallArgs qr_small_args(altgdmin_ctx* c, int mode, int check_halt) {
   qa.guard = 1e-6;  // FP32 gradient: below this it is rounding noise
   qa.B = c->at<float2>(c->o_B);
   qa.cost_k = c->at<double>(c->o_cost);
-  qa.rfac = c->at<float2>(c->o_rfac);
   qa.st = c->st();
   qa.check_halt = check_halt;
   return qa;
 }
 
-hipError_t qr_step_small(altgdmin_ctx* c, int mode, int check_halt) {
-  hipError_t e = qr_step_gram(c, check_halt);
+// only the step size (Algorithm 2's rule at the basis whose gradient was formed last)
+hipError_t qr_step_eta(altgdmin_ctx* c) {
+  hipError_t e = qr_step_gram(c, 0);
   if (e != hipSuccess) return e;
-  const QrSmallArgs qa = qr_small_args(c, mode, check_halt);
+  QrSmallArgs qa = qr_small_args(c, STEP_MODE_ETA, 0);
+  qa.commit_direct = 1;
   tmark(c, TK_QRSMALL);
-  e = launch_qr_small(qa, c->stream);
+  ApplyArgs aa{};
+  aa.n = c->n;
+  e = step_apply(c, qa, aa);
   tmark(c, TK_QRSMALL);
   return e;
 }
 
-// the step and the update fused (rank <= 8): QR Gram, then one kernel that
-// factors and updates, then (exit rule on) the commit of its outcome
+// the step and the update: QR Gram, then one kernel that factors and
+// updates, then (exit rule on) the commit of its outcome
 hipError_t qr_step_apply(altgdmin_ctx* c, float2* U, float2* U_prev) {
   const altgdmin_params& p = c->p;
   hipError_t e = qr_step_gram(c, 1);
   if (e != hipSuccess) return e;
-  QrSmallArgs qa = qr_small_args(c, 0, 1);
-  tmark(c, TK_APPLY);
-  const int nout = p.r * (2 * p.r + 1);
-  e = launch_partials_total(qa.part, qa.part_f32, qa.nblk, nout, c->at<double2>(c->o_qtot), c->stream);
-  if (e != hipSuccess) return e;
-  qa.part = c->at<double2>(c->o_qtot);  // the partials summed (FP64)
-  qa.part_f32 = 0;
-  qa.nblk = 1;
+  QrSmallArgs qa = qr_small_args(c, STEP_MODE_STEP, 1);
   qa.commit_direct = !(p.eps_exit > 0.0);
   qa.stats_src = c->at<double2>(c->o_stsrc);
   ApplyArgs aa{};
+  aa.src = U;
   aa.U = U;
   aa.Ui = c->at<float2>(c->o_Ui);
   aa.G = c->at<float2>(c->o_G);
-  aa.rfac = c->at<float2>(c->o_rfac);
   aa.U_prev = U_prev;
   aa.n = c->n;
-  aa.r = p.r;
-  aa.mode = 0;
-  aa.st = c->st();
-  e = launch_step_apply(qa, aa, c->stream);
+  tmark(c, TK_APPLY);
+  e = step_apply(c, qa, aa);
   tmark(c, TK_APPLY);
   return e;
 }
 
 hipError_t one_iteration(altgdmin_ctx* c, float2* U, float2* U_prev) {
-  const altgdmin_params& p = c->p;
   hipError_t e = gradient_pieces(c, 1);
   if (e != hipSuccess) return e;
-  if (p.r <= 8) return qr_step_apply(c, U, U_prev);
-  e = qr_step_small(c, 0, 1);
-  if (e != hipSuccess) return e;
-  ApplyArgs aa{};
-  aa.U = U;
-  aa.Ui = c->at<float2>(c->o_Ui);
-  aa.G = c->at<float2>(c->o_G);
-  aa.rfac = c->at<float2>(c->o_rfac);
-  aa.U_prev = U_prev;
-  aa.n = c->n;
-  aa.r = p.r;
-  aa.mode = 0;
-  aa.st = c->st();
-  tmark(c, TK_APPLY);
-  e = launch_apply(aa, c->stream);
-  tmark(c, TK_APPLY);
-  return e;
+  return qr_step_apply(c, U, U_prev);
 }
 
 }  // namespace
@@ -662,22 +642,16 @@ hipError_t spectral_eig(altgdmin_ctx* c, int r_eig, double* lam_out) {
   // workgroups (k_init_gram up to 48 frames, k_init_gram_cx up to 128), whose
   // partials a second kernel sums
   InitEigArgs ie{};
-  if (p.q <= 128) {
-    const int nb = init_nblk(c);
-    g.rows_per_block = ((c->n + nb - 1) / nb + 31) / 32 * 32;
-    const int nbu = (int)((c->n + g.rows_per_block - 1) / g.rows_per_block);
-    if (p.q <= 48) AGCHK(launch_init_gram(g, nbu, s));
-    else AGCHK(launch_init_gram_cx(g, nbu, s));
-    const int nout = p.q * (p.q + 1) / 2;
-    double2* sum = c->at<double2>(c->o_qpart) + (size_t)nbu * nout;
-    AGCHK(launch_sum_partials(c->at<double2>(c->o_qpart), nbu, nout, sum, s));
-    ie.part = sum;
-    ie.nblk = 1;
-  } else {
-    AGCHK(launch_gram_cols(g, c->qr_nblk, true, s));
-    ie.part = c->at<double2>(c->o_qpart);
-    ie.nblk = c->qr_nblk;
-  }
+  const int nb = init_nblk(c);
+  g.rows_per_block = ((c->n + nb - 1) / nb + 31) / 32 * 32;
+  const int nbu = (int)((c->n + g.rows_per_block - 1) / g.rows_per_block);
+  if (p.q <= 48) AGCHK(launch_init_gram(g, nbu, s));
+  else AGCHK(launch_init_gram_cx(g, nbu, s));
+  const int nout = p.q * (p.q + 1) / 2;
+  double2* sum = c->at<double2>(c->o_qpart) + (size_t)nbu * nout;
+  AGCHK(launch_sum_partials(c->at<double2>(c->o_qpart), nbu, nout, sum, s));
+  ie.part = sum;
+  ie.nblk = 1;
   ie.q = p.q;
   ie.r = r_eig;
   ie.lam_out = lam_out;
@@ -835,7 +809,7 @@ altgdmin_status altgdmin_init(altgdmin_ctx* c, void* d_U) {
   HIPCHK(launch_x_times_v(X0, c->at<float2>(c->o_Vs), c->n, p.q, p.r, U, c->st(), s));
   // X0 V Sigma^-1 is orthonormal up to FP32 rounding (errors grow with
   // sigma_1 / sigma_r): one CholeskyQR pass restores it
-  HIPCHK(cholqr(c, U));
+  HIPCHK(cholqr(c, U, U));
   c->initialized = 1;
   return ALTGDMIN_OK;
 }
@@ -846,12 +820,9 @@ altgdmin_status altgdmin_init_from(altgdmin_ctx* c, const void* d_U0, void* d_U)
   const altgdmin_params& p = c->p;
   hipStream_t s = c->stream;
   hipLaunchKernelGGL(k_state_reset, dim3(1), dim3(1), 0, s, c->st(), 0);
-  if (d_U0 != d_U)
-    hipLaunchKernelGGL(k_copy, dim3(1024), dim3(256), 0, s, static_cast<const float2*>(d_U0),
-                       static_cast<float2*>(d_U), (long)c->n * p.r);
   HIPCHK(hipGetLastError());
-  HIPCHK(cholqr(c, static_cast<float2*>(d_U)));
-  HIPCHK(cholqr(c, static_cast<float2*>(d_U)));
+  HIPCHK(cholqr(c, static_cast<const float2*>(d_U0), static_cast<float2*>(d_U)));
+  HIPCHK(cholqr(c, static_cast<float2*>(d_U), static_cast<float2*>(d_U)));
   c->initialized = 1;
   return ALTGDMIN_OK;
 }
@@ -876,7 +847,7 @@ static altgdmin_status warm_combine(altgdmin_ctx* c, const void* d_M, void* d_U,
   // evaluated there would overshoot
   HIPCHK(to_pixmajor(c, static_cast<const float2*>(d_U)));
   HIPCHK(gradient_pieces(c, 0));
-  HIPCHK(qr_step_small(c, 2, 0));
+  HIPCHK(qr_step_eta(c));
   // the gradient pass's solve left the spectral basis's per-frame costs:
   // their sum is the spectral side of the comparison below
   double* f = c->at<double>(c->o_fcmp);
@@ -885,11 +856,9 @@ static altgdmin_status warm_combine(altgdmin_ctx* c, const void* d_M, void* d_U,
   int32_t* snap = reinterpret_cast<int32_t*>(f + 2);
   hipLaunchKernelGGL(k_err_snapshot, dim3(1), dim3(1), 0, s, c->st(), snap);
   float2* Uc = c->at<float2>(c->o_Uc);
-  hipLaunchKernelGGL(k_copy, dim3(1024), dim3(256), 0, s, static_cast<const float2*>(d_M), Uc, (long)c->n * p.r);
   HIPCHK(hipGetLastError());
-  HIPCHK(cholqr(c, Uc));
-  HIPCHK(cholqr(c, Uc));
-  HIPCHK(to_pixmajor(c, Uc));
+  HIPCHK(cholqr(c, static_cast<const float2*>(d_M), Uc));
+  HIPCHK(cholqr(c, Uc, Uc));  // (leaves the pixel-major copy that the transform reads)
   HIPCHK(fwd_transform(c, 0));
   HIPCHK(gram_solve(c, 0));
   hipLaunchKernelGGL(k_cost_total, dim3(1), dim3(1), 0, s, c->at<double>(c->o_cost), p.q, f + 1, c->st());

@@ -199,582 +199,62 @@ __global__ void k_state_set_eta(DevState* st, double eta) {
   if (threadIdx.x == 0) st->eta = eta;
 }
 
-// ===========================================================================
-// per-frame Gram and right-hand side, 1D Cartesian (hybrid ky, x form)
-// For each sampled line (unit u, phase-encode ky):
-//   P_u  = sum_{c,x} W_c(u,x,:)^H W_c(u,x,:)                  (r x r)
-//   hp_p = sum_{c,x} conj(W_c(u,x,:)) y'_{k,c}(l,x)            per sample (k,l) of ky
-// so that G_k = sum_{l} P_{u(k,l)} and h_k = sum_l hp_{(k,l)}.
-// Rows of W_c(u,:,:) and the samples' y' rows are staged in LDS; every
-// thread owns a few outputs and forms their dot products over x.
-// ===========================================================================
-
-template <typename ACC>
-struct Acc2;
-template <>
-struct Acc2<float> {
-  using T = float2;
-  __device__ static T zero() { return make_float2(0.f, 0.f); }
-  __device__ static T fma_cj(T acc, float2 a, float2 b) {  // acc + conj(a) b
-    acc.x += a.x * b.x + a.y * b.y;
-    acc.y += a.x * b.y - a.y * b.x;
-    return acc;
-  }
-  __device__ static double2 to_d(T v) { return f2d(v); }
-};
-template <>
-struct Acc2<double> {
-  using T = double2;
-  __device__ static T zero() { return make_double2(0.0, 0.0); }
-  __device__ static T fma_cj(T acc, float2 a, float2 b) {
-    const double ax = a.x, ay = a.y, bx = b.x, by = b.y;
-    acc.x += ax * bx + ay * by;
-    acc.y += ax * by - ay * bx;
-    return acc;
-  }
-  __device__ static double2 to_d(T v) { return v; }
-};
-
-// ===========================================================================
-// Gram of column blocks: C = [A B]^H [A B] over n rows (column-major n x m1
-// and n x m2), upper triangle, partial sums per workgroup in FP64.
-// ===========================================================================
-template <typename ACC>
-__global__ __launch_bounds__(GCOLS_NT) void k_gram_cols(GramColsArgs a) {
-  using A2 = Acc2<ACC>;
-  __shared__ float2 Xs[64 * 64];
-  const int tid = threadIdx.x, blk = blockIdx.x;
-  if (halted(a.st, a.check_halt)) return;
-  const int m = a.m1 + a.m2;  // <= 128
-  const int nout = m * (m + 1) / 2;
-  const int RC = m <= 64 ? 64 : 32;  // rows staged per chunk
-  typename A2::T acc[GCOLS_OPT];
-#pragma unroll
-  for (int t = 0; t < GCOLS_OPT; ++t) acc[t] = A2::zero();
-  const long pa = (long)blk * a.rows_per_block;
-  const long pb = min((long)a.n, pa + a.rows_per_block);
-  for (long p0 = pa; p0 < pb; p0 += RC) {
-    const int np = (int)min((long)RC, pb - p0);
-    for (int g = tid; g < RC * m; g += GCOLS_NT) {
-      const int j = g / RC, pp = g % RC;
-      float2 v = make_float2(0.f, 0.f);
-      if (pp < np) v = (j < a.m1) ? a.A[(long)j * a.n + p0 + pp] : a.B[(long)(j - a.m1) * a.n + p0 + pp];
-      Xs[pp * m + j] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int t = 0; t < GCOLS_OPT; ++t) {
-      const int o = tid + t * GCOLS_NT;
-      if (o < nout) {
-        int i, j;
-        tri_index(o, m, i, j);
-        for (int pp = 0; pp < np; ++pp) acc[t] = A2::fma_cj(acc[t], Xs[pp * m + i], Xs[pp * m + j]);
-      }
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int t = 0; t < GCOLS_OPT; ++t) {
-    const int o = tid + t * GCOLS_NT;
-    if (o < nout) a.part[(long)blk * nout + o] = A2::to_d(acc[t]);
-  }
-}
-
-// ===========================================================================
-// small dense FP64 routines for one workgroup (matrices in LDS, leading
-// dimension ld).
-// ===========================================================================
-__device__ double block_sum(double v, double* red) {
-  const int tid = threadIdx.x;
-  red[tid] = v;
-  __syncthreads();
-  for (int off = blockDim.x / 2; off > 0; off >>= 1) {
-    if (tid < off) red[tid] += red[tid + off];
-    __syncthreads();
-  }
-  double s = red[0];
-  __syncthreads();
-  return s;
-}
-
-// one complex Jacobi rotation G (c, s, e) that zeroes A[p][q] of the
-// Hermitian 2x2 block [[app, apq], [conj(apq), aqq]]; identity if q >= n or
-// the entry is already negligible
-// reciprocal and reciprocal square root in FP64 from the hardware estimates
-// (v_rcp_f64, v_rsq_f64) refined by two Newton steps each, to about one ulp:
-// shorter dependent chains than the IEEE-exact division and square root
+// reciprocal in FP64 from the hardware estimate (v_rcp_f64) refined by two
+// Newton steps, to about one ulp: a shorter dependent chain than the
+// IEEE-exact division
 __device__ __forceinline__ double rcp_nr(double x) {
   double y = __builtin_amdgcn_rcp(x);
   y = fma(y, fma(-x, y, 1.0), y);
   y = fma(y, fma(-x, y, 1.0), y);
   return y;
 }
-__device__ __forceinline__ double rsq_nr(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  const double h = 0.5 * x;
-  y = y * fma(-h * y, y, 1.5);
-  y = y * fma(-h * y, y, 1.5);
-  return y;
-}
-
-__device__ __forceinline__ JRot jacobi_rot(const double2* A, int ld, int n, int p, int q) {
-  JRot g{1.0, 0.0, make_double2(1.0, 0.0)};
-  if (q >= n) return g;
-  const double2 apq = A[p * ld + q];
-  const double m2 = apq.x * apq.x + apq.y * apq.y;
-  const double app = A[p * ld + p].x, aqq = A[q * ld + q].x;
-  const double scale = fabs(app) + fabs(aqq);
-  if (m2 > 1e-280 && m2 > 1e-36 * scale * scale) {
-    const double rm = rsq_nr(m2);  // 1 / |a_pq|
-    g.e = make_double2(apq.x * rm, -apq.y * rm);  // exp(-i phi)
-    const double tau = (aqq - app) * 0.5 * rm;
-    const double at = fabs(tau);
-    // t = sign(tau) / (|tau| + sqrt(1 + tau^2)); for huge |tau|, t ~ 1 / (2 tau)
-    const double h = (at < 1e150) ? (1.0 + tau * tau) * rsq_nr(1.0 + tau * tau) : at;
-    const double t = (tau >= 0 ? 1.0 : -1.0) * rcp_nr(at + h);
-    g.c = rsq_nr(1.0 + t * t);
-    g.s = t * g.c;
-  }
-  return g;
-}
-
-// pair i of round s of the round-robin ordering over Q (even) indices
-__device__ __forceinline__ void jacobi_pair(int s, int i, int Q, int& p, int& q) {
-  if (i == 0) {
-    p = Q - 1;
-    q = s;
-  } else {
-    p = (s + i) % (Q - 1);
-    q = (s - i + Q - 1) % (Q - 1);
-  }
-  if (p > q) {
-    const int t = p;
-    p = q;
-    q = t;
-  }
-}
-
-// Cyclic complex Jacobi eigensolver for the Hermitian n x n matrix A
-// (row-major, leading dimension ld), parallel round-robin ordering: the
-// Q/2 rotations of a round are disjoint and are applied together.  The
-// matrix splits into 2x2 blocks (pair i rows, pair j columns); each block
-// is updated independently, A_ij <- G_i^H A_ij G_j, with the rotations
-// computed first (one thread per pair) from the matrix as it was at the
-// start of the round; then a read phase and a write phase.  V (if given, ld n) accumulates
-// V <- V G in place (block (i, j) of V is touched by one thread only).  A and V may be in LDS or in global memory private to the
-// workgroup.  On return diag(A) holds the eigenvalues and the columns of V
-// the eigenvectors.  Up to ITEMS*blockDim blocks: ITEMS = 1 covers n <= 64
-// with 1024 threads, ITEMS = 4 covers n <= 128.
-//
-// With r_top > 0 only the invariant subspace of the r_top largest
-// eigenvalues is wanted.  Partition the indices into the current top r_top
-// diagonal entries and the rest, A = [A11 A12; A21 A22].  Gershgorin discs
-// within each diagonal block bound the spectra of A11 from below and of A22
-// from above; once these bounds are separated by sep > 0 and
-// ||A12||_F <= 1e-10 sep, the span of the top coordinate vectors is within
-// an angle of about 1e-10 of the wanted subspace (Davis-Kahan sin-theta),
-// and the sweeps stop.
-template <int JAC_ITEMS>
-__device__ __forceinline__ void jacobi_eig(double2* A, int n, int ld, double2* V, JacobiScratch* js,
-                                           int max_sweeps, int r_top = 0) {
-  const int tid = threadIdx.x, NT = blockDim.x;
-  if (V)
-    for (int e = tid; e < n * n; e += NT) V[e] = make_double2((e / n) == (e % n) ? 1.0 : 0.0, 0.0);
-  __syncthreads();
-  const int Q = n + (n & 1), H = Q / 2;
-  for (int sweep = 0; sweep < max_sweeps; ++sweep) {
-    if (r_top > 0) {  // which diagonal entries are currently the top r_top
-      for (int i = tid; i < n; i += NT) {
-        const double di = A[i * ld + i].x;
-        int rank = 0;
-        for (int j = 0; j < n; ++j) {
-          const double dj = A[j * ld + j].x;
-          rank += (dj > di) || (dj == di && j < i);
-        }
-        js->top[i] = rank < r_top;
-      }
-      __syncthreads();
-      // Gershgorin bound of row i within its own block
-      for (int i = tid; i < n; i += NT) {
-        const int ti = js->top[i];
-        double rad = 0.0;
-        for (int j = 0; j < n; ++j) {
-          if (j == i || js->top[j] != ti) continue;
-          const double2 v = A[i * ld + j];
-          rad += fabs(v.x) + fabs(v.y);  // >= |v|: still a Gershgorin bound
-        }
-        js->bnd[i] = ti ? A[i * ld + i].x - rad : A[i * ld + i].x + rad;
-      }
-      __syncthreads();
+// The largest eigenvalue of the Hermitian positive semidefinite r x r matrix M
+// (LDS, rows of 16, destroyed; S is scratch of the same shape) by the whole
+// workgroup (256 threads or more): M is scaled to unit trace and squared until
+// it is rank one to rounding, or 30 times, by when eigenvalues closer to the
+// largest than 1e-8 of it are all that is left beside it; the result is the
+// weighted mean tr(M^p A) / tr(M^p) of A = M's eigenvalues.  Each squaring is one
+// short product in LDS, where a cyclic Jacobi takes r rotation rounds a sweep.
+__device__ __forceinline__ double spectral_norm2(double2* M, double2* S, double2* A, int r) {
+  const int tid = threadIdx.x, i = (tid >> 4) & 15, j = tid & 15;
+  const bool in = tid < 256 && i < r && j < r;
+  auto trace = [&](const double2* X) {
+    double t = 0.0;
+#pragma unroll 8
+    for (int k = 0; k < r; ++k) t += X[k * 16 + k].x;
+    return t;
+  };
+  if (in) A[i * 16 + j] = M[i * 16 + j];
+  double t = trace(M);
+  if (!(t > 0.0) || !isfinite(t)) return 0.0;  // the same in every thread
+  for (int it = 0; it < 30; ++it) {
+    double2 v = make_double2(0.0, 0.0);
+    if (in) {
+#pragma unroll 8
+      for (int k = 0; k < r; ++k) v = dadd(v, dmul(M[i * 16 + k], M[k * 16 + j]));
     }
-    double off = 0.0, tot = 0.0, cross = 0.0;
-    for (int e = tid; e < n * n; e += NT) {
-      const int i = e / n, j = e % n;
-      const double2 v = A[i * ld + j];
-      const double m2 = v.x * v.x + v.y * v.y;
-      tot += m2;
-      if (i != j) off += m2;
-      if (r_top > 0 && js->top[i] && !js->top[j]) cross += m2;
-    }
-    off = block_sum(off, js->red);
-    tot = block_sum(tot, js->red);
-    if (!(off > 1e-26 * tot)) break;
-    if (r_top > 0 && r_top < n) {
-      cross = block_sum(cross, js->red);
-      double lo = INFINITY, hi = -INFINITY;  // lower bound of eig(A11), upper bound of eig(A22)
-      for (int i = 0; i < n; ++i) {
-        if (js->top[i]) lo = fmin(lo, js->bnd[i]);
-        else hi = fmax(hi, js->bnd[i]);
-      }
-      const double sep = lo - hi;
-      if (sep > 0.0 && cross <= 1e-20 * sep * sep) break;
-    }
-    for (int s = 0; s < Q - 1; ++s) {
-      // this round's rotations, one thread per pair, from the matrix as it is
-      for (int i = tid; i < H; i += NT) {
-        int p, q;
-        jacobi_pair(s, i, Q, p, q);
-        js->rot[i] = jacobi_rot(A, ld, n, p, q);
-        js->pq[i] = make_int2(p, q);
-      }
-      __syncthreads();
-      double2 na[JAC_ITEMS][4];
-#pragma unroll
-      for (int k = 0; k < JAC_ITEMS; ++k) {
-        const int t = tid + k * NT;
-        if (t < H * H) {
-          const int i = t / H, j = t - (t / H) * H;
-          const int pi = js->pq[i].x, qi = js->pq[i].y, pj = js->pq[j].x, qj = js->pq[j].y;
-          const JRot gi = js->rot[i];
-          const JRot gj = js->rot[j];
-          const bool ri = qi < n, rj = qj < n;  // the second row / column exists
-          const double2 z = make_double2(0.0, 0.0);
-          // the block [[a, b], [c, d]] = A[(pi, qi), (pj, qj)]
-          double2 a = A[pi * ld + pj], b = rj ? A[pi * ld + qj] : z;
-          double2 c = ri ? A[qi * ld + pj] : z, d = (ri && rj) ? A[qi * ld + qj] : z;
-          // columns: (x, y) <- (c x - s y e, s x + c y e)
-          {
-            const double2 y0 = dmul(b, gj.e), y1 = dmul(d, gj.e);
-            const double2 a2 = make_double2(gj.c * a.x - gj.s * y0.x, gj.c * a.y - gj.s * y0.y);
-            const double2 b2 = make_double2(gj.s * a.x + gj.c * y0.x, gj.s * a.y + gj.c * y0.y);
-            const double2 c2 = make_double2(gj.c * c.x - gj.s * y1.x, gj.c * c.y - gj.s * y1.y);
-            const double2 d2 = make_double2(gj.s * c.x + gj.c * y1.x, gj.s * c.y + gj.c * y1.y);
-            a = a2; b = b2; c = c2; d = d2;
-          }
-          // rows: with conj(e_i)
-          {
-            const double2 ec = dconj(gi.e);
-            const double2 y0 = dmul(c, ec), y1 = dmul(d, ec);
-            na[k][0] = make_double2(gi.c * a.x - gi.s * y0.x, gi.c * a.y - gi.s * y0.y);
-            na[k][1] = make_double2(gi.c * b.x - gi.s * y1.x, gi.c * b.y - gi.s * y1.y);
-            na[k][2] = make_double2(gi.s * a.x + gi.c * y0.x, gi.s * a.y + gi.c * y0.y);
-            na[k][3] = make_double2(gi.s * b.x + gi.c * y1.x, gi.s * b.y + gi.c * y1.y);
-          }
-          if (V) {  // V rows (pi, qi), columns (pj, qj), right rotation only: no other
-                    // thread touches these entries this round, so update in place
-            const double2 va = V[pi * n + pj], vb = rj ? V[pi * n + qj] : z;
-            const double2 vc = ri ? V[qi * n + pj] : z, vd = (ri && rj) ? V[qi * n + qj] : z;
-            const double2 y0 = dmul(vb, gj.e), y1 = dmul(vd, gj.e);
-            V[pi * n + pj] = make_double2(gj.c * va.x - gj.s * y0.x, gj.c * va.y - gj.s * y0.y);
-            if (rj) V[pi * n + qj] = make_double2(gj.s * va.x + gj.c * y0.x, gj.s * va.y + gj.c * y0.y);
-            if (ri) V[qi * n + pj] = make_double2(gj.c * vc.x - gj.s * y1.x, gj.c * vc.y - gj.s * y1.y);
-            if (ri && rj) V[qi * n + qj] = make_double2(gj.s * vc.x + gj.c * y1.x, gj.s * vc.y + gj.c * y1.y);
-          }
-        }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < JAC_ITEMS; ++k) {
-        const int t = tid + k * NT;
-        if (t < H * H) {
-          const int i = t / H, j = t - (t / H) * H;
-          const int pi = js->pq[i].x, qi = js->pq[i].y, pj = js->pq[j].x, qj = js->pq[j].y;
-          const bool ri = qi < n, rj = qj < n;
-          A[pi * ld + pj] = na[k][0];
-          if (rj) A[pi * ld + qj] = na[k][1];
-          if (ri) A[qi * ld + pj] = na[k][2];
-          if (ri && rj) A[qi * ld + qj] = na[k][3];
-        }
-      }
-      __syncthreads();
-    }
-  }
-}
-
-// Cholesky of the Hermitian r x r matrix M (LDS, ld 16) in FP64, lower L in
-// place, right-looking, by the whole workgroup (every thread must call it).
-// Returns false (in every thread) if M is not positive definite.
-__device__ bool chol_lower(double2* M, int r) {
-  const int tid = threadIdx.x, nt = blockDim.x;
-  double dmax = 0.0;
-  for (int i = 0; i < r; ++i) dmax = fmax(dmax, M[i * 16 + i].x);
-  for (int j = 0; j < r; ++j) {
-    const double d = M[j * 16 + j].x;  // every thread reads the same pivot
-    if (!(d > 1e-14 * dmax) || !isfinite(d)) return false;
-    const double ljj = sqrt(d), inv = 1.0 / ljj;
+    if (in) S[i * 16 + j] = make_double2(v.x / t / t, v.y / t / t);
     __syncthreads();
-    if (tid == 0) M[j * 16 + j] = make_double2(ljj, 0.0);
-    for (int i = j + 1 + tid; i < r; i += nt) M[i * 16 + j] = make_double2(M[i * 16 + j].x * inv, M[i * 16 + j].y * inv);
-    __syncthreads();
-    // trailing update of the lower triangle: M[i][k] -= L[i][j] conj(L[k][j]), j < k <= i
-    for (int e = tid; e < 256; e += nt) {
-      const int i = e >> 4, k = e & 15;
-      if (k > j && k <= i && i < r) M[i * 16 + k] = dsub(M[i * 16 + k], dmul(M[i * 16 + j], dconj(M[k * 16 + j])));
-    }
-    __syncthreads();
+    double2* const w = M;
+    M = S;
+    S = w;
+    t = trace(M);  // sum of squared eigenvalue weights: 1 when one weight holds all
+    if (!(t < 1.0 - 1e-14)) break;
   }
-  return true;
+  // every wave the same sum: lane l's entries in order, then over the lanes
+  double num = 0.0;
+  for (int e = tid & 63; e < r * 16; e += 64)
+    if ((e & 15) < r) num += M[e].x * A[e].x + M[e].y * A[e].y;
+  return wave_sum(num) / t;
 }
 
 // entry e = (i, j) of R = L^H with the reciprocal on the diagonal, from the
-// lower Cholesky factor L (LDS, ld 16): the form the update kernel solves with
+// lower Cholesky factor L (LDS, row pitch CHOL_LD): the form the update solves with
 __device__ __forceinline__ float2 rfac_entry(const double2* L, int r, int e) {
   const int i = e / r, j = e - (e / r) * r;
-  if (i < j) return make_float2((float)L[j * 16 + i].x, -(float)L[j * 16 + i].y);
-  if (i == j) return make_float2((float)(1.0 / L[i * 16 + i].x), 0.f);
+  if (i < j) return make_float2((float)L[j * CHOL_LD + i].x, -(float)L[j * CHOL_LD + i].y);
+  if (i == j) return make_float2((float)(1.0 / L[i * CHOL_LD + i].x), 0.f);
   return make_float2(0.f, 0.f);
-}
-
-// ===========================================================================
-// the QR step's small work (one workgroup): reduce the Gram partials of
-// [U grad]; at the first iteration set eta = eta_c / sigma_max(grad) (with
-// the stationarity guard and the optional cap); Gram of Uhat = U - eta grad
-// from the blocks; R = chol(.)^H, R^{-1}; SD(U, U+) from r x r data.
-// mode 1: plain CholeskyQR of U (no gradient).
-// ===========================================================================
-template <int RT>
-__global__ __launch_bounds__(1024) void k_qr_small(QrSmallArgs a) {
-  __shared__ double2 UU[256], UG[256], GG[256], Gh[256], Tm[256];
-  __shared__ JacobiScratch js;
-  __shared__ int s_ok;
-  const int tid = threadIdx.x, r = a.r;
-  DevState* st = a.st;
-  if (st->err || (a.mode == 0 && a.check_halt && st->halt)) {
-    if (tid == 0 && a.mode == 0) st->step_ok = 0;
-    return;
-  }
-  const int m = a.mode == 1 ? r : 2 * r;  // mode 0 step, 1 CholeskyQR of U, 2 step size only
-  const int nout = m * (m + 1) / 2;
-  // sum the block partials: thread = (output, slice of blocks)
-  __shared__ double2 red2[1024];
-  const int NTH = blockDim.x;
-  const int NS = max(1, NTH / nout);
-  const int OW = NTH / NS;
-  for (int o0 = 0; o0 < nout; o0 += OW) {
-    const int o = o0 + tid % OW, sl = tid / OW;
-    double2 s = make_double2(0.0, 0.0);
-    if (o < nout && sl < NS) {
-      if (a.part_f32) {
-        const float2* pf = reinterpret_cast<const float2*>(a.part);
-#pragma unroll 8
-        for (int b = sl; b < a.nblk; b += NS) s = dadd(s, f2d(pf[(long)b * nout + o]));
-      } else {
-#pragma unroll 8
-        for (int b = sl; b < a.nblk; b += NS) s = dadd(s, a.part[(long)b * nout + o]);
-      }
-    }
-    red2[tid] = s;
-    __syncthreads();
-    if (tid < OW && o < nout) {
-      for (int q2 = 1; q2 < NS; ++q2) s = dadd(s, red2[tid + q2 * OW]);
-      int i, j;
-    tri_index(o, m, i, j);
-    // entry (i, j), i <= j, of [U G]^H [U G]
-    if (j < r) {
-      UU[i * 16 + j] = s;
-      UU[j * 16 + i] = dconj(s);
-    } else if (i < r) {
-      UG[i * 16 + (j - r)] = s;  // (U^H G)[i][j-r]
-    } else {
-      GG[(i - r) * 16 + (j - r)] = s;
-      GG[(j - r) * 16 + (i - r)] = dconj(s);
-    }
-    }
-    __syncthreads();
-  }
-  __syncthreads();
-  if (a.mode == 1) {
-    for (int e = tid; e < 256; e += blockDim.x) Gh[e] = UU[e];
-    __syncthreads();
-    bool ok = chol_lower(Gh, r);
-    __syncthreads();
-    if (!ok) {  // numerically rank-deficient basis: retry with a small ridge
-      for (int e = tid; e < 256; e += blockDim.x) Gh[e] = UU[e];
-      __syncthreads();
-      double tr = 0.0;
-      for (int i = 0; i < r; ++i) tr += UU[i * 16 + i].x;
-      __syncthreads();
-      if (tid < r) Gh[tid * 16 + tid].x += 1e-6 * tr / r;
-      __syncthreads();
-      ok = (tr > 0.0) && isfinite(tr) && chol_lower(Gh, r);
-      __syncthreads();
-    }
-    if (!ok) {
-      if (tid == 0) set_error(st, 4, -1);
-      return;
-    }
-    for (int e = tid; e < r * r; e += blockDim.x) a.rfac[e] = rfac_entry(Gh, r, e);
-    return;
-  }
-  // first iteration: step size from the spectral norm of grad
-  if (st->eta <= 0.0) {
-    for (int e = tid; e < 256; e += AG_NT) Tm[e] = GG[e];
-    __syncthreads();
-    jacobi_eig<1>(Tm, r, 16, nullptr, &js, 40);
-    __syncthreads();
-    if (tid == 0) {
-      double lam = 0.0;
-      for (int i = 0; i < r; ++i) lam = fmax(lam, Tm[i * 16 + i].x);
-      const double smax = sqrt(lam);
-      st->grad_norm = smax;
-      if (!(smax > a.guard * st->ysq)) {
-        st->converged = 1;
-        st->halt = 1;
-        st->step_ok = 0;
-        s_ok = 0;
-      } else {
-        st->eta = a.eta_c / smax;
-        s_ok = 1;
-      }
-    }
-    __syncthreads();
-    if (!s_ok) return;
-    if (a.eta_cap_c > 0.0) {  // cap: eta <= c n / (mbar ||B_0||_2^2)
-      for (int e = tid; e < r * r; e += AG_NT) {
-        const int i = e / r, j = e % r;
-        double2 s = make_double2(0.0, 0.0);
-        for (int k = 0; k < a.q; ++k) s = dadd(s, dmul(f2d(a.B[(long)k * r + i]), dconj(f2d(a.B[(long)k * r + j]))));
-        Tm[i * 16 + j] = s;
-      }
-      __syncthreads();
-      jacobi_eig<1>(Tm, r, 16, nullptr, &js, 40);
-      __syncthreads();
-      if (tid == 0) {
-        double lam = 0.0;
-        for (int i = 0; i < r; ++i) lam = fmax(lam, Tm[i * 16 + i].x);
-        const double cap = a.eta_cap_c * (double)a.n / (st->mbar * lam);
-        if (cap < st->eta) st->eta = cap;
-      }
-      __syncthreads();
-    }
-  }
-  if (a.mode == 2) return;  // only the step size was wanted
-  // the step size as thread 0 left it, shared through LDS
-  __shared__ double s_eta;
-  if (tid == 0) s_eta = st->eta;
-  __syncthreads();
-  // one wave from here on: Cholesky of Uhat^H Uhat, Uhat = U - eta G, from the
-  // blocks (rows in lanes), R^{-1}, SD(U, U+) and the cost
-  if (tid >= 64) return;
-  const int i = tid;
-  const double eta = s_eta;
-  auto gh = [&](int a_, int b_) -> double2 {  // (Uhat^H Uhat)[a_][b_]
-    const double2 ug = UG[a_ * 16 + b_], gu = dconj(UG[b_ * 16 + a_]);
-    const double2 v = UU[a_ * 16 + b_], g = GG[a_ * 16 + b_];
-    return make_double2(v.x - eta * (ug.x + gu.x) + eta * eta * g.x, v.y - eta * (ug.y + gu.y) + eta * eta * g.y);
-  };
-  double2 g[RT];  // padded to RT with the identity
-#pragma unroll
-  for (int m = 0; m < RT; ++m) g[m] = (i < r && m < r) ? gh(i, m) : make_double2(i == m ? 1.0 : 0.0, 0.0);
-  const double dmax = wave_max((i < r) ? gh(i, i).x : 0.0);
-  if (!wave_chol<double, double2, RT>(g, r, 1e-14 * dmax)) {
-    if (i == 0) {
-      set_error(st, 4, -1);
-      st->step_ok = 0;
-    }
-    return;
-  }
-#pragma unroll
-  for (int m = 0; m < RT; ++m)
-    if (i < RT && m <= i) Gh[i * 16 + m] = g[m];
-  wave_sync();
-  // U^H U+ = (U^H U - eta U^H G) R^{-1}: lane i solves x R = row i by forward
-  // substitution (R = L^H); SD^2 = r - ||U^H U+||_F^2
-  double fro = 0.0;
-  if (i < r) {  // x in LDS (Tm, free after the first iteration's step size): short code, few registers
-    double2* x = Tm + i * 16;
-    for (int j = 0; j < r; ++j) {
-      double2 acc = make_double2(UU[i * 16 + j].x - eta * UG[i * 16 + j].x, UU[i * 16 + j].y - eta * UG[i * 16 + j].y);
-      for (int k = 0; k < j; ++k) acc = dsub(acc, dmul(x[k], dconj(Gh[j * 16 + k])));  // R[k][j] = conj(L[j][k])
-      const double rd = 1.0 / Gh[j * 16 + j].x;
-      const double2 xj = make_double2(acc.x * rd, acc.y * rd);
-      x[j] = xj;
-      fro += xj.x * xj.x + xj.y * xj.y;
-    }
-  }
-  fro = wave_sum(fro);
-  for (int e = i; e < r * r; e += 64) a.rfac[e] = rfac_entry(Gh, r, e);
-  double fv = 0.0;  // f = sum_k cost_k
-  for (int k = i; k < a.q; k += 64) fv += a.cost_k[k];
-  fv = wave_sum(fv);
-  if (i == 0) {
-    const double sd2 = fmax(0.0, (double)r - fro);
-    double tr = 0.0;
-    for (int m = 0; m < r; ++m) tr += GG[m * 16 + m].x;
-    st->sd = sqrt(sd2);
-    st->grad_norm = sqrt(tr);
-    st->f = fv;
-    st->t += 1;
-    st->step_ok = 1;
-    if (a.eps_exit > 0.0 && sqrt(sd2 / r) < a.eps_exit) {
-      st->exit_run += 1;
-      if (st->exit_run >= a.exit_consec) {
-        st->exited = 1;
-        st->halt = 1;
-      }
-    } else {
-      st->exit_run = 0;
-    }
-  }
-}
-
-// U <- (U - eta grad) Rinv per pixel (mode 0, when the step is applied), or
-// U <- U Rinv (mode 1).  Optionally keeps U before the update.
-template <int RT>
-__global__ __launch_bounds__(AG_NT) void k_apply(ApplyArgs a) {
-  __shared__ float2 Ri[RT * RT];
-  const int tid = threadIdx.x;
-  const long p = (long)blockIdx.x * AG_NT + tid;
-  const int r = a.r;
-  // this pixel's basis row and gradient are requested before the state is
-  // read (clamped addresses, valid either way)
-  const long pc = min(p, a.n - 1);
-  float2 u0[RT], g0[RT];
-#pragma unroll
-  for (int i = 0; i < RT; ++i) {
-    u0[i] = (i < r) ? a.U[(long)i * a.n + pc] : make_float2(0.f, 0.f);
-    g0[i] = (i < r && a.mode == 0) ? a.G[pc * r + i] : make_float2(0.f, 0.f);  // gradient is pixel-major
-  }
-  for (int e = tid; e < r * r; e += AG_NT) Ri[(e / r) * RT + (e % r)] = a.rfac[e];
-  if (a.mode == 0 && !a.st->step_ok) return;
-  if (a.st->err) return;
-  __syncthreads();
-  if (p >= a.n) return;
-  const float eta = (a.mode == 0) ? (float)a.st->eta : 0.f;
-  float2 uh[RT];
-#pragma unroll
-  for (int i = 0; i < RT; ++i) {
-    if (i < r) {
-      if (a.U_prev) a.U_prev[(long)i * a.n + p] = u0[i];
-      uh[i] = make_float2(u0[i].x - eta * g0[i].x, u0[i].y - eta * g0[i].y);
-    } else {
-      uh[i] = make_float2(0.f, 0.f);
-    }
-  }
-  // U+ R = Uhat, row by row: forward substitution (the diagonal holds 1 / R_jj)
-  float2 un[RT];
-#pragma unroll
-  for (int j = 0; j < RT; ++j) {
-    un[j] = make_float2(0.f, 0.f);
-    if (j < r) {
-      float2 s = uh[j];
-#pragma unroll
-      for (int i = 0; i < j; ++i) s = csub(s, cmul(un[i], Ri[i * RT + j]));
-      un[j] = cscale(s, Ri[j * RT + j].x);
-      a.U[(long)j * a.n + p] = un[j];
-      if (a.Ui) a.Ui[p * r + j] = un[j];
-    }
-  }
 }
 
 // ===========================================================================
@@ -785,7 +265,7 @@ __global__ __launch_bounds__(AG_NT) void k_apply(ApplyArgs a) {
 // IN_LDS: matrix and eigenvectors in dynamic LDS (q <= 64; the accesses are
 // then LDS instructions), else in the workspace
 // ||U^H U+||_F^2 = ||(U^H U - eta U^H G) R^{-1}||_F^2, lanes l < r taking
-// row l by forward substitution with R = L^H (L in Gh, rows of stride 16;
+// row l by forward substitution with R = L^H (L in Gh, row pitch CHOL_LD;
 // x is a row scratch of stride 16); the caller sums over the wave.  The
 // fused step and the deferred statistics both use it, so that SD is the
 // same number either way.
@@ -796,8 +276,8 @@ __device__ __forceinline__ double sd_row_sum(const double2* UU, const double2* U
     double2* x = Tm + l * 16;
     for (int j = 0; j < r; ++j) {
       double2 acc = make_double2(UU[l * 16 + j].x - eta * UG[l * 16 + j].x, UU[l * 16 + j].y - eta * UG[l * 16 + j].y);
-      for (int k = 0; k < j; ++k) acc = dsub(acc, dmul(x[k], dconj(Gh[j * 16 + k])));
-      const double rd = 1.0 / Gh[j * 16 + j].x;
+      for (int k = 0; k < j; ++k) acc = dsub(acc, dmul(x[k], dconj(Gh[j * CHOL_LD + k])));
+      const double rd = 1.0 / Gh[j * CHOL_LD + j].x;
       const double2 xj = make_double2(acc.x * rd, acc.y * rd);
       x[j] = xj;
       fro += xj.x * xj.x + xj.y * xj.y;
@@ -869,92 +349,107 @@ __device__ __forceinline__ void partials_sum(const double2* part, int f32, int n
 }
 
 // ===========================================================================
-// the QR step fused with the update (r <= 8): every workgroup sums the QR
-// Gram partials, takes the step size (Algorithm 2's rule at t = 1, then the
-// stored one), factors Uhat^H Uhat = L L^H in one wave, and solves
-// U+ R = U - eta grad for its NT pixels, R = L^H.  Every workgroup computes
-// the same factor from the same partials in the same order.  With the exit
-// rule on, workgroup 0 also forms SD(U, U+) and the cost, and the outcome
-// (applied, exit rule, stationary start) and the step size go to step_flags /
-// eta_next and are committed by k_step_commit, because a halt written during
-// the launch would stop workgroups that have not yet updated their pixels.
-// With it off (commit_direct), workgroup 0 commits t and eta itself: t is
-// read by no workgroup, and a workgroup that reads the new eta instead of the
-// unset one gets the value it would have computed (the same rule on the same
-// partials, bitwise); the stationary start halts every workgroup alike.  SD,
-// the cost and ||grad|| are then only reported: their r x r inputs are
-// stored and k_stats_finish forms them on request.
+// the QR step fused with the update: every workgroup takes the summed Gram of
+// [U G] and the step size (Algorithm 2's rule at t = 1, then the stored one),
+// factors Uhat^H Uhat = L L^H in one wave, and solves U+ R = U - eta grad for its
+// 256 pixels, R = L^H.  Every workgroup computes the same factor from the same
+// sum in the same order.  With the exit rule on, workgroup 0 also forms
+// SD(U, U+) and the cost, and the outcome (applied, exit rule, stationary
+// start) and the step size go to step_flags / eta_next and are committed by
+// k_step_commit, because a halt written during the launch would stop
+// workgroups that have not yet updated their pixels.  With it off
+// (commit_direct), workgroup 0 commits t and eta itself: t is read by no
+// workgroup, and a workgroup that reads the new eta instead of the unset one
+// gets the value it would have computed (the same rule on the same sum,
+// bitwise); the stationary start halts every workgroup alike.  SD, the cost
+// and ||grad|| are then only reported: their r x r inputs are stored and
+// k_stats_finish forms them on request.
+//
+// STEP_MODE_QR: U+ = CholeskyQR of src (the sum is the Gram of src alone, a
+// small ridge is added if it is numerically singular).  STEP_MODE_ETA (one
+// workgroup): only the step size is set.
+//
+// The factor's wave takes its entries straight from the sum (a lane's four
+// rows of loads in flight at once); the other waves' pixels wait for it at one
+// barrier.  Bound by the latency of that chain.  Rank 16, 256 x 256: 25 us with
+// the partials' sum, against 61 us for a one-workgroup factor and a separate
+// update; rank 8: 11.3 us, 12.2 us with the Gram staged in LDS by the workgroup.
 // ===========================================================================
-template <int RT, int NT>
-__global__ __launch_bounds__(NT) void k_step_apply(QrSmallArgs a, ApplyArgs ap) {
-  __shared__ double2 UU[256], UG[256], GG[256], Gh[256], Tm[256];
-  __shared__ JacobiScratch js;
-  __shared__ double2 tot[RT * (2 * RT + 1)];  // the summed Gram's upper triangle (m = 2 r <= 2 RT)
+template <int RT>
+__global__ __launch_bounds__(256) void k_step_apply(QrSmallArgs a, ApplyArgs ap) {
+  __shared__ double2 L[16 * CHOL_LD], W0[256], W1[256], W2[256];
   __shared__ float2 Rf[RT * RT];
   __shared__ int s_ok;
   __shared__ double s_eta;
-  const int tid = threadIdx.x, r = a.r, wv = tid >> 6, l = tid & 63;
+  const int tid = threadIdx.x, r = a.r, l = tid & 63, ri = l & 15, rg = l >> 4;
   DevState* st = a.st;
-  const long n = ap.n, p = (long)blockIdx.x * NT + tid, pc = min(p, n - 1);
-  // the state, then this pixel's basis row and gradient, requested first
-  // (clamped, valid addresses); the state's loads are in every thread, so
-  // that no branch waits on them
+  const long n = ap.n, p = (long)blockIdx.x * 256 + tid, pc = min(p, n - 1);
+  const bool step = a.mode != STEP_MODE_QR;
+  const int m = step ? 2 * r : r;
+  // the state, this pixel's basis row and gradient and the factor's entries
+  // are requested first (clamped, valid addresses); the state's loads are in
+  // every thread, so that no branch waits on them
   const int err0 = st->err;
   const int halt0 = __hip_atomic_load(&st->halt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const double eta0 = __hip_atomic_load(&st->eta, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   float2 u0[RT], g0[RT];
+  if (a.mode != STEP_MODE_ETA) {
 #pragma unroll
-  for (int i = 0; i < RT; ++i) u0[i] = (i < r) ? ap.U[(long)i * n + pc] : make_float2(0.f, 0.f);
-  if (r == RT) {  // the pixel-major gradient row as 16-byte loads
-    const float4* gs = reinterpret_cast<const float4*>(ap.G + pc * RT);
+    for (int i = 0; i < RT; ++i) u0[i] = (i < r) ? ap.src[(long)i * n + pc] : make_float2(0.f, 0.f);
+    if (!step) {
 #pragma unroll
-    for (int h = 0; h < RT / 2; ++h) {
-      const float4 w = gs[h];
-      g0[2 * h] = make_float2(w.x, w.y);
-      g0[2 * h + 1] = make_float2(w.z, w.w);
-    }
-  } else {
+      for (int i = 0; i < RT; ++i) g0[i] = make_float2(0.f, 0.f);
+    } else if ((r & 1) == 0) {  // the pixel-major gradient row as 16-byte loads
+      const float4* gs = reinterpret_cast<const float4*>(ap.G + pc * r);
 #pragma unroll
-    for (int i = 0; i < RT; ++i) g0[i] = (i < r) ? ap.G[pc * r + i] : make_float2(0.f, 0.f);
-  }
-  // the Gram of [U G] from the partials
-  const int m = 2 * r, nout = m * (m + 1) / 2;
-  const bool summed = a.nblk == 1 && !a.part_f32;  // the FP64 sum itself
-  if (!summed) partials_sum<NT>(a.part, a.part_f32, a.nblk, nout, tot, 0, 1);
-  for (int o = tid; o < nout; o += NT) {
-    int i, j;
-    tri_index(o, m, i, j);
-    const double2 sum = summed ? a.part[o] : tot[o];
-    if (j < r) {
-      UU[i * 16 + j] = sum;
-      UU[j * 16 + i] = dconj(sum);
-    } else if (i < r) {
-      UG[i * 16 + (j - r)] = sum;
+      for (int h = 0; h < RT / 2; ++h) {
+        const float4 w = 2 * h < r ? gs[h] : make_float4(0.f, 0.f, 0.f, 0.f);
+        g0[2 * h] = make_float2(w.x, w.y);
+        g0[2 * h + 1] = make_float2(w.z, w.w);
+      }
     } else {
-      GG[(i - r) * 16 + (j - r)] = sum;
-      GG[(j - r) * 16 + (i - r)] = dconj(sum);
+#pragma unroll
+      for (int i = 0; i < RT; ++i) g0[i] = (i < r) ? ap.G[pc * r + i] : make_float2(0.f, 0.f);
     }
   }
-  __syncthreads();
+  // entry (x, y) of the Hermitian Gram, from its upper triangle in tri order
+  auto gram = [&](int x, int y) -> double2 {
+    const int lo = min(x, y), hi = max(x, y);
+    const double2 v = a.part[lo * m - lo * (lo - 1) / 2 + (hi - lo)];
+    return make_double2(v.x, x <= y ? v.y : -v.y);
+  };
+  // this lane's entries (ri, 4 t + rg) of U^H U, U^H G, G^H U and G^H G
+  double2 uu[4], ug[4], gu[4], gg[4];
+  if (tid < 64) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int x = min(ri, r - 1), y = min(4 * t + rg, r - 1);
+      uu[t] = gram(x, y);
+      if (step) {
+        ug[t] = gram(x, r + y);
+        gu[t] = gram(r + x, y);
+        gg[t] = gram(r + x, r + y);
+      }
+    }
+  }
   // err is written during this launch only when a factor fails, which then
   // fails in every workgroup alike; halt and eta only by workgroup 0, with
   // the values every workgroup derives itself (see above)
   if (tid == 0) {
-    s_ok = !(err0 || (a.check_halt && halt0));
-    s_eta = eta0;
+    s_ok = !(err0 || (step && a.check_halt && halt0));
+    s_eta = step ? eta0 : 0.0;
   }
   __syncthreads();
   if (!s_ok) return;
-  if (!(s_eta > 0.0)) {  // first iteration: eta = eta_c / ||grad||_2 (with the guard and the cap)
-    for (int e = tid; e < 256; e += NT) Tm[e] = GG[e];
+  if (step && !(s_eta > 0.0)) {  // first iteration: eta = eta_c / ||grad||_2 (with the guard and the cap)
+    const int x = tid >> 4, y = tid & 15;
+    if (x < r && y < r) W0[tid] = gram(r + x, r + y);
     __syncthreads();
-    jacobi_eig<1>(Tm, r, 16, nullptr, &js, 40);
+    const double smax = sqrt(spectral_norm2(W0, W1, W2, r));
+    const bool go = smax > a.guard * st->ysq;
     __syncthreads();
     if (tid == 0) {
-      double lam = 0.0;
-      for (int i = 0; i < r; ++i) lam = fmax(lam, Tm[i * 16 + i].x);
-      const double smax = sqrt(lam);
-      if (!(smax > a.guard * st->ysq)) {
+      if (!go) {
         s_ok = 0;  // stationary start
         if (blockIdx.x == 0) {
           st->grad_norm = smax;
@@ -972,62 +467,81 @@ __global__ __launch_bounds__(NT) void k_step_apply(QrSmallArgs a, ApplyArgs ap) 
     __syncthreads();
     if (!s_ok) return;
     if (a.eta_cap_c > 0.0) {  // cap: eta <= c n / (mbar ||B_0||_2^2)
-      for (int e = tid; e < r * r; e += NT) {
-        const int i = e / r, j = e % r;
+      if (x < r && y < r) {
         double2 sum = make_double2(0.0, 0.0);
         for (int k = 0; k < a.q; ++k)
-          sum = dadd(sum, dmul(f2d(a.B[(long)k * r + i]), dconj(f2d(a.B[(long)k * r + j]))));
-        Tm[i * 16 + j] = sum;
+          sum = dadd(sum, dmul(f2d(a.B[(long)k * r + x]), dconj(f2d(a.B[(long)k * r + y]))));
+        W0[tid] = sum;
       }
       __syncthreads();
-      jacobi_eig<1>(Tm, r, 16, nullptr, &js, 40);
+      const double lam = spectral_norm2(W0, W1, W2, r);
+      const double cap = a.eta_cap_c * (double)a.n / (st->mbar * lam);
       __syncthreads();
-      if (tid == 0) {
-        double lam = 0.0;
-        for (int i = 0; i < r; ++i) lam = fmax(lam, Tm[i * 16 + i].x);
-        const double cap = a.eta_cap_c * (double)a.n / (st->mbar * lam);
-        if (cap < s_eta) s_eta = cap;
-      }
+      if (tid == 0 && cap < s_eta) s_eta = cap;
       __syncthreads();
     }
+    if (a.mode == STEP_MODE_ETA) {
+      if (tid == 0) {
+        st->grad_norm = smax;
+        st->eta = s_eta;
+      }
+      return;
+    }
   }
+  if (a.mode == STEP_MODE_ETA) return;
   const double eta = s_eta;
-  if (wv == 0) {  // one wave: the Cholesky factor (rows in lanes, padded with the identity)
-    auto gh = [&](int a_, int b_) -> double2 {  // (Uhat^H Uhat)[a_][b_]
-      const double2 ug = UG[a_ * 16 + b_], gu = dconj(UG[b_ * 16 + a_]);
-      const double2 v = UU[a_ * 16 + b_], g = GG[a_ * 16 + b_];
-      return make_double2(v.x - eta * (ug.x + gu.x) + eta * eta * g.x, v.y - eta * (ug.y + gu.y) + eta * eta * g.y);
-    };
-    double2 g[RT];
+  if (tid < 64) {  // one wave: the Cholesky factor of Uhat^H Uhat
+    double2 h[4], dummy = make_double2(0.0, 0.0);
+    double tr = 0.0, dmax = 0.0, inv_own;
 #pragma unroll
-    for (int mm = 0; mm < RT; ++mm) g[mm] = (l < r && mm < r) ? gh(l, mm) : make_double2(l == mm ? 1.0 : 0.0, 0.0);
-    const double dmax = wave_max((l < r) ? gh(l, l).x : 0.0);
-    const bool ok = wave_chol<double, double2, RT>(g, r, 1e-14 * dmax);
+    for (int t = 0; t < 4; ++t) {
+      const int y = 4 * t + rg;
+      h[t] = uu[t];
+      if (step)
+        h[t] = make_double2(uu[t].x - eta * (ug[t].x + gu[t].x) + eta * eta * gg[t].x,
+                            uu[t].y - eta * (ug[t].y + gu[t].y) + eta * eta * gg[t].y);
+      if (ri >= r || y >= r) h[t] = make_double2(0.0, 0.0);
+      if (ri == y && y < r) {
+        dmax = h[t].x;
+        tr = step ? gg[t].x : h[t].x;
+      }
+    }
+    dmax = wave_max(dmax);
+    tr = wave_sum(tr);  // of G^H G, or of the Gram of src
+    double2 h0[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) h0[t] = h[t];
+    bool ok = wave_chol<double, double2, false>(h, L, r, 1e-14 * dmax, dummy, inv_own);
+    if (!ok && !step && tr > 0.0 && isfinite(tr)) {  // numerically rank-deficient basis: retry with a small ridge
+      const double ridge = 1e-6 * tr / r;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        h[t] = h0[t];
+        if (ri == 4 * t + rg && ri < r) h[t].x += ridge;
+      }
+      ok = wave_chol<double, double2, false>(h, L, r, 1e-14 * (dmax + ridge), dummy, inv_own);
+    }
     if (!ok) {
       if (l == 0) {
         s_ok = 0;
         set_error(st, 4, -1);
       }
     } else {
-#pragma unroll
-      for (int mm = 0; mm < RT; ++mm)
-        if (l < RT && mm <= l) Gh[l * 16 + mm] = g[mm];
       wave_sync();
-      for (int e = l; e < r * r; e += 64) Rf[(e / r) * RT + (e % r)] = rfac_entry(Gh, r, e);
-      if (blockIdx.x == 0) {
+      for (int e = l; e < r * r; e += 64) Rf[(e / r) * RT + (e % r)] = rfac_entry(L, r, e);
+      if (blockIdx.x == 0 && step) {
         if (a.commit_direct) {
           // exit rule off: SD, f and ||grad|| are only reported; their r x r
           // inputs are stored and k_stats_finish forms them when asked
-          for (int e = l; e < 64; e += 64) {
-            const int i = e >> 3, j = e & 7;
-            a.stats_src[e] = UU[i * 16 + j];
-            a.stats_src[64 + e] = UG[i * 16 + j];
-            a.stats_src[128 + e] = Gh[i * 16 + j];
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const int e = ri * 16 + 4 * t + rg;
+            a.stats_src[e] = uu[t];
+            a.stats_src[256 + e] = ug[t];
+            a.stats_src[512 + e] = (ri < r && 4 * t + rg <= ri) ? L[ri * CHOL_LD + 4 * t + rg] : make_double2(0.0, 0.0);
           }
           if (l == 0) {
-            double tr = 0.0;
-            for (int mm = 0; mm < r; ++mm) tr += GG[mm * 16 + mm].x;
-            a.stats_src[192] = make_double2(eta, tr);
+            a.stats_src[768] = make_double2(eta, tr);
             st->stats_pending = 1;
             __hip_atomic_store(&st->eta, eta, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             st->t += 1;
@@ -1035,14 +549,18 @@ __global__ __launch_bounds__(NT) void k_step_apply(QrSmallArgs a, ApplyArgs ap) 
           }
         } else {
           // SD^2 = r - ||U^H U+||_F^2 decides the exit rule
-          const double fro = wave_sum(sd_row_sum(UU, UG, Gh, Tm, eta, r, l));
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            W0[ri * 16 + 4 * t + rg] = uu[t];
+            W1[ri * 16 + 4 * t + rg] = ug[t];
+          }
+          wave_sync();
+          const double fro = wave_sum(sd_row_sum(W0, W1, L, W2, eta, r, l));
           double fv = 0.0;  // f = sum_k cost_k
           for (int k = l; k < a.q; k += 64) fv += a.cost_k[k];
           fv = wave_sum(fv);
           if (l == 0) {
             const double sd2 = fmax(0.0, (double)r - fro);
-            double tr = 0.0;
-            for (int mm = 0; mm < r; ++mm) tr += GG[mm * 16 + mm].x;
             st->sd = sqrt(sd2);
             st->grad_norm = sqrt(tr);
             st->f = fv;
@@ -1069,13 +587,14 @@ __global__ __launch_bounds__(NT) void k_step_apply(QrSmallArgs a, ApplyArgs ap) 
       for (int i = 0; i < j; ++i) sv = csub(sv, cmul(un[i], Rf[i * RT + j]));
       un[j] = cscale(sv, Rf[j * RT + j].x);
       ap.U[(long)j * n + p] = un[j];
-      if (ap.Ui && r != RT) ap.Ui[p * r + j] = un[j];
+      if (ap.Ui && (r & 1)) ap.Ui[p * r + j] = un[j];
     }
   }
-  if (ap.Ui && r == RT) {  // the pixel-major row as 16-byte stores
-    float4* dst = reinterpret_cast<float4*>(ap.Ui + p * RT);
+  if (ap.Ui && (r & 1) == 0) {  // the pixel-major row as 16-byte stores
+    float4* dst = reinterpret_cast<float4*>(ap.Ui + p * r);
 #pragma unroll
-    for (int h = 0; h < RT / 2; ++h) dst[h] = make_float4(un[2 * h].x, un[2 * h].y, un[2 * h + 1].x, un[2 * h + 1].y);
+    for (int h = 0; h < RT / 2; ++h)
+      if (2 * h < r) dst[h] = make_float4(un[2 * h].x, un[2 * h].y, un[2 * h + 1].x, un[2 * h + 1].y);
   }
 }
 
@@ -1110,16 +629,15 @@ __global__ void k_step_commit(DevState* st, int exit_consec) {
 // per-frame costs (no solve has run since), with the fused step's own code
 __global__ __launch_bounds__(64) void k_stats_finish(DevState* st, const double2* src, const double* cost_k, int q,
                                                      int r) {
-  __shared__ double2 UU[256], UG[256], Gh[256], Tm[256];
+  __shared__ double2 UU[256], UG[256], Gh[16 * CHOL_LD], Tm[256];
   const int l = threadIdx.x;
   if (!st->stats_pending) return;
-  for (int e = l; e < 64; e += 64) {
-    const int i = e >> 3, j = e & 7;
-    UU[i * 16 + j] = src[e];
-    UG[i * 16 + j] = src[64 + e];
-    Gh[i * 16 + j] = src[128 + e];
+  for (int e = l; e < 256; e += 64) {
+    UU[e] = src[e];
+    UG[e] = src[256 + e];
+    Gh[(e >> 4) * CHOL_LD + (e & 15)] = src[512 + e];
   }
-  const double2 et = src[192];
+  const double2 et = src[768];
   wave_sync();
   const double fro = wave_sum(sd_row_sum(UU, UG, Gh, Tm, et.x, r, l));
   double fv = 0.0;
@@ -1155,10 +673,16 @@ hipError_t launch_partials_total(const double2* part, int f32, int nblk, int nou
 }
 
 hipError_t launch_step_apply(const QrSmallArgs& a, const ApplyArgs& ap, hipStream_t s) {
-  if (a.r > 8) return hipErrorInvalidValue;
-  // 256 pixels per workgroup: the update's stores spread over every compute unit
-  hipLaunchKernelGGL((k_step_apply<8, 256>), dim3((unsigned)((ap.n + 255) / 256)), dim3(256), 0, s, a, ap);
-  if (!a.commit_direct) hipLaunchKernelGGL(k_step_commit, dim3(1), dim3(64), 0, s, a.st, a.exit_consec);
+  if (a.r < 1 || a.r > 16) return hipErrorInvalidValue;
+  // 256 pixels per workgroup: the update's stores spread over every compute
+  // unit; register rows of 4, 8, 12 or 16
+  const dim3 g(a.mode == STEP_MODE_ETA ? 1u : (unsigned)((ap.n + 255) / 256));
+  if (a.r <= 4) hipLaunchKernelGGL(k_step_apply<4>, g, dim3(256), 0, s, a, ap);
+  else if (a.r <= 8) hipLaunchKernelGGL(k_step_apply<8>, g, dim3(256), 0, s, a, ap);
+  else if (a.r <= 12) hipLaunchKernelGGL(k_step_apply<12>, g, dim3(256), 0, s, a, ap);
+  else hipLaunchKernelGGL(k_step_apply<16>, g, dim3(256), 0, s, a, ap);
+  if (a.mode == STEP_MODE_STEP && !a.commit_direct)
+    hipLaunchKernelGGL(k_step_commit, dim3(1), dim3(64), 0, s, a.st, a.exit_consec);
   return hipGetLastError();
 }
 
@@ -1831,32 +1355,6 @@ __global__ void k_cost_total(const double* cost_k, int q, double* out, DevState*
 // ---------------------------------------------------------------------------
 // launchers (explicit instantiations behind plain functions)
 // ---------------------------------------------------------------------------
-hipError_t launch_gram_cols(const GramColsArgs& a, int nblk, bool fp64, hipStream_t s) {
-  if (fp64)
-    hipLaunchKernelGGL(k_gram_cols<double>, dim3(nblk), dim3(GCOLS_NT), 0, s, a);
-  else
-    hipLaunchKernelGGL(k_gram_cols<float>, dim3(nblk), dim3(GCOLS_NT), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_apply(const ApplyArgs& a, hipStream_t s) {
-  const dim3 g((unsigned)((a.n + AG_NT - 1) / AG_NT));
-  if (a.r <= 4) hipLaunchKernelGGL(k_apply<4>, g, dim3(AG_NT), 0, s, a);
-  else if (a.r <= 8) hipLaunchKernelGGL(k_apply<8>, g, dim3(AG_NT), 0, s, a);
-  else if (a.r <= 12) hipLaunchKernelGGL(k_apply<12>, g, dim3(AG_NT), 0, s, a);
-  else hipLaunchKernelGGL(k_apply<16>, g, dim3(AG_NT), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_qr_small(const QrSmallArgs& a, hipStream_t s) {
-  // 1,024 threads for the partial sums at the start; the one-wave factor's
-  // rows padded to 8, 12 or 16 with the identity
-  if (a.r <= 8) hipLaunchKernelGGL(k_qr_small<8>, dim3(1), dim3(1024), 0, s, a);
-  else if (a.r <= 12) hipLaunchKernelGGL(k_qr_small<12>, dim3(1), dim3(1024), 0, s, a);
-  else hipLaunchKernelGGL(k_qr_small<16>, dim3(1), dim3(1024), 0, s, a);
-  return hipGetLastError();
-}
-
 hipError_t launch_init_eig(const InitEigArgs& a, hipStream_t s) {
   if (a.q > 128 || a.r > 16 || a.r > a.q) return hipErrorInvalidValue;
   // q <= 64: matrix and reflectors in LDS; else the packed lower triangle

@@ -3,31 +3,14 @@
 
 #include "kernels.hpp"
 
-#define GRAM_OPT 2    // outputs per thread in the per-line Gram kernels
 #define SOLVE_NT 1024  // threads of the per-frame solve
 #define QR_NSM 2       // QR Gram: streams of 4 waves per workgroup
 #define GRAM_NWG 1     // per-line Gram: groups of 4 waves per workgroup
 #define GRAM_INDEX_CHUNK 512  // general masks: samples per Gram workgroup (one coil)
 #define GRAM_DS32 2    // per-line Gram, FP32: steps whose loads are issued together
 #define GRAM_DS64 4    // the same for FP64
-#define GCOLS_OPT 9   // outputs per thread in the column-Gram kernel (m <= 128)
-#define GCOLS_NT 1024
 
 namespace ag {
-
-// one complex Jacobi rotation: c, s and the phase e = exp(-i phi)
-struct JRot {
-  double c, s;
-  double2 e;
-};
-
-struct JacobiScratch {
-  double red[1024];
-  JRot rot[64];     // this round's rotations, one per pair
-  int2 pq[64];      // and their index pairs
-  int top[128];     // per index: among the r_top largest diagonal entries
-  double bnd[128];  // per index: Gershgorin bound within its block
-};
 
 struct GramLinesArgs {
   const float2* W;       // [c][u][x][j], ua rows per coil
@@ -184,30 +167,29 @@ struct GramColsArgs {
 };
 
 struct QrSmallArgs {
-  const double2* part;   // per QR Gram workgroup: its partial (FP32 pairs when part_f32)
+  const double2* part;   // per QR Gram workgroup: its partial (FP32 pairs when part_f32), summed first; then the sum
   int part_f32;
-  int nblk, r, mode, n, q;
+  int nblk, r, mode, n, q;  // mode: STEP_MODE_*
   double eta_c, eta_cap_c, eps_exit;
   int exit_consec;  // the exit rule fires after this many consecutive small steps (>= 1)
   double guard;          // stationary start: ||grad_0||_2 <= guard * sum_k ||y_k||^2
   const float2* B;
   const double* cost_k;
-  float2* rfac;          // R = L^H (Uhat^H Uhat = L L^H), row-major r x r, upper, 1 / R_jj on the diagonal
   DevState* st;
   int check_halt;
-  int commit_direct;     // fused step only: workgroup 0 commits t and eta itself (the exit rule is off)
-  double2* stats_src;    // fused step with commit_direct: the r x r inputs of the deferred statistics (193 entries)
+  int commit_direct;     // workgroup 0 commits t and eta itself (the exit rule is off)
+  double2* stats_src;    // with commit_direct: the r x r inputs of the deferred statistics (STATS_SRC entries)
 };
+enum { STEP_MODE_STEP = 0, STEP_MODE_QR = 1, STEP_MODE_ETA = 2 };  // a step; CholeskyQR of U; the step size alone
+constexpr int STATS_SRC = 3 * 256 + 1;
 
 struct ApplyArgs {
+  const float2* src;     // n x r column-major basis to update (may be U)
   float2* U;             // n x r column-major (C ABI layout)
   float2* Ui;            // n x r pixel-major copy for the next iteration (may be null)
-  const float2* G;       // pixel-major gradient
-  const float2* rfac;    // R as written by the small QR step
+  const float2* G;       // pixel-major gradient (a step)
   float2* U_prev;
   long n;
-  int r, mode;
-  DevState* st;
 };
 
 struct InitEigArgs {
@@ -303,31 +285,49 @@ __device__ __forceinline__ double cx_rsqrt(double d) {
   return y;
 }
 
-// Cholesky G = L L^H of a Hermitian positive definite RT x RT matrix by one
-// wave: lane i < RT holds row i of G in g[0..RT-1] on entry and row i of L
-// (entries 0..i) on return.  A problem of size r < RT is padded with the
-// identity (rows and columns r..RT-1), so the code is straight-line and
-// short.  False if a pivot of the r x r problem is not above tol (all lanes
-// agree).
-template <typename T, typename T2, int RT>
-__device__ __forceinline__ bool wave_chol(T2 (&g)[RT], int r, T tol) {
-  const int i = threadIdx.x & 63;
+// Cholesky G = L L^H of a Hermitian positive definite r x r matrix (r <= 16)
+// by one wave: lane l holds rows i = l % 16, columns k = 4 t + l / 16 of G in
+// a[t] (zero past r) and L is left in LDS (row pitch CHOL_LD, lower triangle,
+// real positive diagonal).  With RHS, y (row i's entry, the same in the four
+// lanes of a row) becomes L^-1 y on the way.  inv_own receives 1 / L_ii.  False
+// if a pivot is not above tol (all lanes agree).  The column loop is rolled
+// apart from the register index: these kernels run once per iteration on a
+// cold instruction cache, and straight-line code for 16 columns spent most
+// of its time being fetched.
+constexpr int CHOL_LD = 17;
+template <typename T, typename T2, bool RHS>
+__device__ __forceinline__ bool wave_chol(T2 (&a)[4], T2* L, int r, T tol, T2& y, T& inv_own) {
+  const int l = threadIdx.x & 63, i = l & 15, g = l >> 4;
   bool ok = true;
+  inv_own = (T)1;
 #pragma unroll
-  for (int j = 0; j < RT; ++j) {
-    const T d = lane_get(g[j].x, j);
-    ok = ok && (j >= r || ((d > tol) && isfinite((double)d)));  // padding pivots are 1
-    const T inv = cx_rsqrt(d > (T)0 ? d : (T)1), ljj = (d > (T)0 ? d : (T)1) * inv;
-    if (i == j) {
-      g[j].x = ljj;
-      g[j].y = (T)0;
-    } else if (i > j) {
-      g[j] = cx_scale(g[j], inv);
-    }
+  for (int t = 0; t < 4; ++t) {
+#pragma unroll 1
+    for (int jj = 0; jj < 4; ++jj) {
+      const int j = 4 * t + jj;
+      if (j >= r) break;
+      const T d = lane_get(a[t].x, 16 * jj + j);
+      ok = ok && (d > tol) && isfinite((double)d);
+      const T dp = d > (T)0 ? d : (T)1, inv = cx_rsqrt(dp);
+      if (i == j) inv_own = inv;
+      if (g == jj) {
+        T2 c = cx_scale(a[t], inv);
+        if (i == j) c = T2{dp * inv, (T)0};
+        if (i < j) c = T2{(T)0, (T)0};
+        L[i * CHOL_LD + j] = c;
+      }
+      wave_sync();
+      const T2 li = L[i * CHOL_LD + j];
 #pragma unroll
-    for (int k = j + 1; k < RT; ++k) {
-      const T2 lkj = lane_get(g[j], k);
-      if (i >= k) g[k] = cx_sub(g[k], cx_mul(g[j], T2{lkj.x, -lkj.y}));
+      for (int u = t; u < 4; ++u) {
+        const T2 lk = L[(4 * u + g) * CHOL_LD + j];
+        a[u] = cx_sub(a[u], cx_mul(li, T2{lk.x, -lk.y}));
+      }
+      if (RHS) {
+        const T2 yj = cx_scale(lane_get(y, j), inv);
+        if (i == j) y = yj;
+        else if (i > j) y = cx_sub(y, cx_mul(li, yj));
+      }
     }
   }
   return ok;
@@ -370,12 +370,10 @@ hipError_t launch_gram_lines(const GramLinesArgs& a, int ny, int ngroups, int ma
                              hipStream_t s);
 hipError_t launch_gram_index(const GramIndexArgs& a, int q, bool fp64, hipStream_t s);
 hipError_t launch_solve(const SolveArgs& a, int q, bool fp64, hipStream_t s);
-hipError_t launch_gram_cols(const GramColsArgs& a, int nblk, bool fp64, hipStream_t s);
 hipError_t launch_qr_gram(const GramColsArgs& a, int nblk, bool fp64, hipStream_t s);
 hipError_t launch_init_gram(const GramColsArgs& a, int nblk, hipStream_t s);  // X0^H X0, q <= 48
 hipError_t launch_init_gram_cx(const GramColsArgs& a, int nblk, hipStream_t s);  // X0^H X0, 48 < q <= 128
 __global__ void k_sum_parts(const float2* src, long stride, int nparts, float2* dst, long n);
-hipError_t launch_apply(const ApplyArgs& a, hipStream_t s);
 hipError_t launch_basis(int which, int N, const BasisArgs& a, int grid_x, int grid_y, hipStream_t s);
 hipError_t launch_adj_qr(int N, const BasisArgs& a, hipStream_t s);
 hipError_t launch_fold2(const FoldArgs& a, bool lines, int grid_x, int grid_y, hipStream_t s);
@@ -400,7 +398,6 @@ __global__ void k_build_yu(const float2* yh, const int2* pairs, const int32_t* m
                            int n_loc, int width, int nc, int nx, int lmax, float2* yu, const DevState* st);
 __global__ void k_to_colmajor(const float2* src, int r, long n, float2* dst);
 __global__ void k_to_pixmajor(const float2* src, int r, long n, float2* dst);
-hipError_t launch_qr_small(const QrSmallArgs& a, hipStream_t s);
 hipError_t launch_init_eig(const InitEigArgs& a, hipStream_t s);
 hipError_t launch_partials_total(const double2* part, int f32, int nblk, int nout, double2* total, hipStream_t s);
 hipError_t launch_step_apply(const QrSmallArgs& a, const ApplyArgs& ap, hipStream_t s);

@@ -12,6 +12,7 @@
 // per instruction); the A operand is shared by the P tile and every h tile.
 // FP32 MFMA for the plain form, FP64 MFMA for the mixed form.
 #include <algorithm>
+#include <type_traits>
 
 #include "kernels_core.hpp"
 #include "mma.hpp"
@@ -462,11 +463,18 @@ struct Cx<double> {
   static constexpr double tiny = 1e-12;
 };
 
-template <typename T, int RT>
+// thread = (entry, slice of the frame's partials) sums its partials, several
+// loads in flight together (from clamped, valid indices; the argument
+// pointers in registers: a per-lane choice of argument field would be a
+// load); then one wave factors and solves.  Bound by the latency of that
+// chain.  64 frames, rank 16, 84 partials per entry: 16 us, against 28 us with
+// a division per load, loads past the eighth one at a time and a
+// straight-line factor.
+template <typename T>
 __global__ __launch_bounds__(SOLVE_NT) void k_solve(SolveArgs a) {
   using C = Cx<T>;
   using T2 = typename C::T2;
-  __shared__ T2 G[16 * 16];
+  __shared__ T2 G[16 * 16], L[16 * CHOL_LD];
   __shared__ T2 h[16];
   __shared__ T2 z[16];
   __shared__ double2 part[SOLVE_NT];
@@ -484,119 +492,96 @@ __global__ __launch_bounds__(SOLVE_NT) void k_solve(SolveArgs a) {
   }
   if (halted(a.st, a.check_halt)) return;
   const int E = r * r + r;  // G entries then h entries
-  if (a.kind == 0) {
-    const double2* const Pp = a.P;
-    const double2* const Hp = a.hp;
-    const long ua = a.ua, npairs = a.npairs;
-    // sum over coil groups and the frame's lines; thread = (entry, slice of lines)
-    const int L = mk / a.nx;
-    __syncthreads();
-    const int NS = max(1, SOLVE_NT / E), SW = SOLVE_NT / NS;
-    for (int e0 = 0; e0 < E; e0 += SW) {
-      const int e = e0 + tid % SW;
-      const int sl = tid / SW;
-      double2 s = make_double2(0.0, 0.0);
-      const int items = a.ngroups * L;
-      if (e < E && sl < NS && items > 0) {
-        // the first MI items' loads issued together from clamped, valid
-        // indices (the argument pointers in registers: a per-lane choice of
-        // argument field would be a load), then summed in item order
-        constexpr int MI = 8;
-        const bool isP = e < r * r;
-        const double2* const src = isP ? Pp : Hp;
-        double2 vv[MI];
-#pragma unroll
-        for (int i = 0; i < MI; ++i) {
-          const int it = min(sl + i * NS, items - 1), gg = it / L, l = it - gg * L;
-          vv[i] = src[isP ? ((long)gg * ua + s_mk[l]) * r * r + e : ((long)gg * npairs + s_po[l]) * r + (e - r * r)];
-        }
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-          if (sl + i * NS < items) s = dadd(s, vv[i]);
-        for (int it = sl + MI * NS; it < items; it += NS) {
-          const int gg = it / L, l = it - gg * L;
-          s = dadd(s, src[isP ? ((long)gg * ua + s_mk[l]) * r * r + e : ((long)gg * npairs + s_po[l]) * r + (e - r * r)]);
-        }
-      }
-      part[tid] = s;
-      __syncthreads();
-      if (tid < SW && e < E) {
-        double2 t = part[tid];
-        for (int q2 = 1; q2 < NS; ++q2) t = dadd(t, part[tid + q2 * SW]);
-        if (e < r * r)
-          G[(e / r) * 16 + (e % r)] = C::from(t);
-        else
-          h[e - r * r] = C::from(t);
-      }
-      __syncthreads();
-    }
-  } else {
-    // sum over the frame's partials; thread = (entry, slice of partials)
-    const int NS = max(1, SOLVE_NT / E), SW = SOLVE_NT / NS;
-    const double2* const Pk = a.P + (long)k * a.nchunks * E;
-    for (int e0 = 0; e0 < E; e0 += SW) {
-      const int e = e0 + tid % SW;
-      const int sl = tid / SW;
-      double2 s = make_double2(0.0, 0.0);
-      if (e < E && sl < NS) {
-        constexpr int MI = 4;  // the first MI partials' loads issued together
-        double2 vv[MI];
-#pragma unroll
-        for (int i = 0; i < MI; ++i) vv[i] = Pk[(long)min(sl + i * NS, a.nchunks - 1) * E + e];
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-          if (sl + i * NS < a.nchunks) s = dadd(s, vv[i]);
-        for (int ch = sl + MI * NS; ch < a.nchunks; ch += NS) s = dadd(s, Pk[(long)ch * E + e]);
-      }
-      part[tid] = s;
-      __syncthreads();
-      if (tid < SW && e < E) {
-        double2 t = part[tid];
-        for (int q2 = 1; q2 < NS; ++q2) t = dadd(t, part[tid + q2 * SW]);
-        if (e < r * r)
-          G[(e / r) * 16 + (e % r)] = C::from(t);
-        else
-          h[e - r * r] = C::from(t);
-      }
-      __syncthreads();
-    }
-  }
+  const int nl = mk / a.nx;  // lines of the frame
+  const int items = a.kind == 0 ? a.ngroups * nl : a.nchunks;
   __syncthreads();
-  // the factorization and the two triangular solves: one wave, rows in lanes,
-  // padded to RT with the identity
-  if (tid >= 64) return;
-  const int i = tid;
-  T2 g[RT];
+  // at most 16 slices: their sums are added one after the other
+  const int NS = max(1, min(16, SOLVE_NT / E)), SW = SOLVE_NT / NS;
+  const double2* const Pp = a.P;
+  const double2* const Hp = a.hp;
+  for (int e0 = 0; e0 < E; e0 += SW) {
+    const int e = e0 + tid % SW;
+    const int sl = tid / SW;
+    double2 s = make_double2(0.0, 0.0);
+    if (e < E && sl < NS) {
+      const bool isP = e < r * r;
+      const double2* const src = a.kind != 0 ? Pp + (long)k * a.nchunks * E : isP ? Pp : Hp;
+      // line masks: the line's entries start at its index times `per`, a coil
+      // group's at its index times `gs` (32-bit: fewer than 2^27 entries in all)
+      const int* const tab = isP ? s_mk : s_po;
+      const int per = isP ? r * r : r, gs = (int)(isP ? a.ua * r * r : a.npairs * r), ee = isP ? e : e - r * r;
+      int gg = 0, l = sl;  // (coil group, line) of the next item
+      auto batch = [&](auto mi) {
+        constexpr int MI = decltype(mi)::value;
+        for (int i0 = sl; i0 < items; i0 += MI * NS) {
+          double2 vv[MI];
 #pragma unroll
-  for (int m = 0; m < RT; ++m)
-    g[m] = (i < r && m < r) ? G[i * 16 + m] : T2{(T)(i == m ? 1 : 0), (T)0};
+          for (int i = 0; i < MI; ++i) {
+            int o = min(i0 + i * NS, items - 1) * E + e;
+            if (a.kind == 0) {
+              while (l >= nl && gg < a.ngroups) {
+                l -= nl;
+                ++gg;
+              }
+              o = gg < a.ngroups ? gg * gs + tab[l] * per + ee : ee;
+              l += NS;
+            }
+            vv[i] = src[o];
+          }
+#pragma unroll
+          for (int i = 0; i < MI; ++i)
+            if (i0 + i * NS < items) s = dadd(s, vv[i]);
+        }
+      };
+      // a load past the slice's last item costs as much address arithmetic
+      // as a used one: four in flight where four are enough (recon of
+      // 64 x 64: 6.4 us against 6.8), else eight (256 x 256, 96 items: 8.8
+      // us against 9.5)
+      if (items <= 4 * NS) batch(std::integral_constant<int, 4>());
+      else batch(std::integral_constant<int, 8>());
+    }
+    part[tid] = s;
+    __syncthreads();
+    if (tid < SW && e < E) {
+      double2 t = part[tid];
+      for (int q2 = 1; q2 < NS; ++q2) t = dadd(t, part[tid + q2 * SW]);
+      if (e < r * r)
+        G[(e / r) * 16 + (e % r)] = C::from(t);
+      else
+        h[e - r * r] = C::from(t);
+    }
+    __syncthreads();
+  }
+  // the factorization and the two triangular solves: one wave
+  if (tid >= 64) return;
+  const int i = tid & 15, g4 = tid >> 4;
+  T2 g[4];
   double dmax = 0.0;
-  for (int m = 0; m < r; ++m) dmax = fmax(dmax, (double)G[m * 16 + m].x);
-  if (!wave_chol<T, T2, RT>(g, r, (T)(C::tiny * dmax))) {
-    if (i == 0) set_error(a.st, 4 /*ENOTPD*/, k);
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int m = 4 * t + g4;
+    g[t] = (i < r && m < r) ? G[i * 16 + m] : T2{(T)0, (T)0};
+    if (i == m && i < r) dmax = (double)g[t].x;
+  }
+  dmax = wave_max(dmax);
+  // L y = h on the way, then L^H b = y; the lanes of row i end with b_i
+  T2 sv = (i < r) ? h[i] : T2{(T)0, (T)0};
+  T inv;
+  if (!wave_chol<T, T2, true>(g, L, r, (T)(C::tiny * dmax), sv, inv)) {
+    if (tid == 0) set_error(a.st, 4 /*ENOTPD*/, k);
     return;
   }
-  // L y = h, then L^H b = y; lane i ends with b_i
-  T2 sv = (i < r) ? h[i] : T2{(T)0, (T)0};
-#pragma unroll
-  for (int j = 0; j < RT; ++j) {
-    const T2 yj = C::scale(lane_get(sv, j), (T)1 / lane_get(g[j].x, j));
-    if (i == j) sv = yj;
-    else if (i > j) sv = C::sub(sv, C::mul(g[j], yj));
-  }
-#pragma unroll
-  for (int j = RT - 1; j >= 0; --j) {
-    const T2 bj = C::scale(lane_get(sv, j), (T)1 / lane_get(g[j].x, j));
+  wave_sync();
+#pragma unroll 2
+  for (int j = r - 1; j >= 0; --j) {
+    const T2 lj = L[j * CHOL_LD + i];  // L[j][i]
+    const T2 bj = lane_get(C::scale(sv, inv), j);
     if (i == j) sv = bj;
-#pragma unroll
-    for (int m = 0; m < j; ++m) {
-      const T2 ljm = lane_get(g[m], j);  // L[j][m]
-      if (i == m) sv = C::sub(sv, C::cjm(ljm, bj));
-    }
+    else if (i < j) sv = C::sub(sv, C::cjm(lj, bj));
   }
   double hb = 0.0;
   bool fin = true;
-  if (i < r) {
+  if (tid < r) {
     const T2 hi = h[i];
     hb = (double)hi.x * (double)sv.x + (double)hi.y * (double)sv.y;
     fin = isfinite((double)sv.x) && isfinite((double)sv.y);
@@ -606,14 +591,13 @@ __global__ __launch_bounds__(SOLVE_NT) void k_solve(SolveArgs a) {
   }
   hb = wave_sum(hb);
   const bool allfin = __all(fin);
-  if (i == 0) {
+  if (tid == 0) {
     a.cost_k[k] = a.ysq_k[k] - hb;
     if (!allfin) set_error(a.st, 5 /*ENONFINITE*/, k);
   }
   if (a.kind == 0) {  // conj(b_k) at each of the frame's pairs
     wave_sync();
-    const int L = mk / a.nx;
-    for (int e = i; e < L * r; e += 64) {
+    for (int e = tid; e < nl * r; e += 64) {
       const int l = e / r, j = e - l * r;
       a.bcp[(long)s_po[l] * r + j] = make_float2((float)z[j].x, -(float)z[j].y);
     }
@@ -671,16 +655,8 @@ hipError_t launch_gram_index(const GramIndexArgs& a, int q, bool fp64, hipStream
 }
 
 hipError_t launch_solve(const SolveArgs& a, int q, bool fp64, hipStream_t s) {
-  // the factor's register tile: rows padded to 8, 12 or 16 with the identity
-  if (fp64) {
-    if (a.r <= 8) hipLaunchKernelGGL((k_solve<double, 8>), dim3(q), dim3(SOLVE_NT), 0, s, a);
-    else if (a.r <= 12) hipLaunchKernelGGL((k_solve<double, 12>), dim3(q), dim3(SOLVE_NT), 0, s, a);
-    else hipLaunchKernelGGL((k_solve<double, 16>), dim3(q), dim3(SOLVE_NT), 0, s, a);
-  } else {
-    if (a.r <= 8) hipLaunchKernelGGL((k_solve<float, 8>), dim3(q), dim3(SOLVE_NT), 0, s, a);
-    else if (a.r <= 12) hipLaunchKernelGGL((k_solve<float, 12>), dim3(q), dim3(SOLVE_NT), 0, s, a);
-    else hipLaunchKernelGGL((k_solve<float, 16>), dim3(q), dim3(SOLVE_NT), 0, s, a);
-  }
+  if (fp64) hipLaunchKernelGGL(k_solve<double>, dim3(q), dim3(SOLVE_NT), 0, s, a);
+  else hipLaunchKernelGGL(k_solve<float>, dim3(q), dim3(SOLVE_NT), 0, s, a);
   return hipGetLastError();
 }
 

@@ -325,6 +325,13 @@ hipError_t cholqr(altgdmin_ctx* c, const float2* src, float2* U) {
   return step_apply(c, qa, aa);
 }
 
+// the statistics that the last iteration left pending (the device knows
+// whether one did; a context that never iterated has none)
+hipError_t finish_stats(altgdmin_ctx* c) {
+  if (!c->iterated) return hipSuccess;
+  return launch_stats_finish(c->st(), c->at<double2>(c->o_stsrc), c->at<double>(c->o_cost), c->p.q, c->p.r, c->stream);
+}
+
 // b_k for every frame and the gradient at U (into the workspace's B and G)
 hipError_t gradient_pieces(altgdmin_ctx* c, int check_halt) {
   const altgdmin_params& p = c->p;
@@ -468,10 +475,19 @@ hipError_t qr_step_apply(altgdmin_ctx* c, float2* U, float2* U_prev) {
 }
 
 hipError_t one_iteration(altgdmin_ctx* c, float2* U, float2* U_prev) {
+  c->iterated = 1;
   hipError_t e = gradient_pieces(c, 1);
   if (e != hipSuccess) return e;
   return qr_step_apply(c, U, U_prev);
 }
+
+// a caller's B buffer, which every solve of a call writes too; forgotten on
+// every way out of the call
+struct BOut {
+  altgdmin_ctx* c;
+  BOut(altgdmin_ctx* ctx, void* B) : c(ctx) { c->b_out = static_cast<float2*>(B); }
+  ~BOut() { c->b_out = nullptr; }
+};
 
 }  // namespace
 
@@ -747,52 +763,59 @@ altgdmin_status altgdmin_set_problem(altgdmin_ctx* c, const void* d_coils, const
   c->bound = 0;
   c->initialized = 0;
   hipStream_t s = c->stream;
-  hipLaunchKernelGGL(k_state_reset, dim3(1), dim3(1), 0, s, c->st(), 1);
-  hipLaunchKernelGGL(k_twiddle, dim3((p.nx + 255) / 256), dim3(256), 0, s, c->at<float2>(c->o_twx), p.nx);
-  hipLaunchKernelGGL(k_twiddle, dim3((p.ny + 255) / 256), dim3(256), 0, s, c->at<float2>(c->o_twy), p.ny);
-  hipLaunchKernelGGL(k_coil_block, dim3(1024), dim3(256), 0, s, c->coils, c->at<float2>(c->o_coilb), p.nx, p.ny,
-                     c->txx, c->n, p.nc);
-  HIPCHK(hipGetLastError());
-  HIPCHK(hipMemsetAsync(c->at<uint32_t>(c->o_bitmap), 0, sizeof(uint32_t) * (size_t)c->n_loc * c->nw, s));
-  hipLaunchKernelGGL(k_inv_bitmap, dim3((c->width + 255) / 256, p.q), dim3(256), 0, s, c->mask, c->m_k,
-                     c->width, c->per, c->n_loc, c->at<uint32_t>(c->o_bitmap), c->nw, c->st());
-  hipLaunchKernelGGL(k_inv_scan, dim3(1), dim3(1024), 0, s, c->at<uint32_t>(c->o_bitmap), c->nw, c->n_loc,
-                     c->at<int32_t>(c->o_locptr), c->at<int32_t>(c->o_loc2unit), c->at<int32_t>(c->o_unitloc),
-                     c->at<int2>(c->o_unitspan), c->st());
-  if (c->lines)
-    HIPCHK(launch_gram_work(c->at<int2>(c->o_unitspan), c->at<int4>(c->o_gwork), c->at<int4>(c->o_lineord),
-                            c->n_loc, c->st(), s));
-
-  if (!c->lines)
-    hipLaunchKernelGGL(k_fill_i32, dim3(1024), dim3(256), 0, s, c->at<int32_t>(c->o_imap), -1, (long)p.q * c->n);
-  hipLaunchKernelGGL(k_inv_fill, dim3((c->width + 255) / 256, p.q), dim3(256), 0, s, c->mask, c->m_k,
-                     c->width, c->per, c->n_loc, c->at<uint32_t>(c->o_bitmap), c->nw, c->at<int32_t>(c->o_locptr),
-                     c->at<int32_t>(c->o_loc2unit), c->at<int2>(c->o_pairs), c->at<int32_t>(c->o_pairof),
-                     c->at<int32_t>(c->o_unitof), c->lines ? nullptr : c->at<int32_t>(c->o_imap), c->st());
-  HIPCHK(hipGetLastError());
-  if (c->y) {
-    hipLaunchKernelGGL(k_ysq, dim3(p.q, p.nc), dim3(AG_NT), 0, s, c->y, c->m_k, p.nc, p.m_max,
-                       c->at<double>(c->o_ysqp));
-    hipLaunchKernelGGL(k_ysq_sum, dim3(1), dim3(128), 0, s, c->at<double>(c->o_ysqp), p.q, p.nc,
-                       c->at<double>(c->o_ysq));
-    hipLaunchKernelGGL(k_init_stats, dim3(1), dim3(1), 0, s, c->at<double>(c->o_ysq), c->m_k, p.q, p.trunc_c,
-                       c->st());
+  BindArgs b{};
+  b.coils = c->coils;
+  b.mask = c->mask;
+  b.m_k = c->m_k;
+  b.y = c->y;
+  b.n = c->n;
+  b.nx = p.nx;
+  b.ny = p.ny;
+  b.nc = p.nc;
+  b.q = p.q;
+  b.m_max = p.m_max;
+  b.width = c->width;
+  b.per = c->per;
+  b.n_loc = c->n_loc;
+  b.nw = c->nw;
+  b.txx = c->txx;
+  b.trunc_c = p.trunc_c;
+  b.twx = c->at<float2>(c->o_twx);
+  b.twy = c->at<float2>(c->o_twy);
+  b.coilb = c->at<float2>(c->o_coilb);
+  b.bitmap = c->at<uint32_t>(c->o_bitmap);
+  b.loc_ptr = c->at<int32_t>(c->o_locptr);
+  b.loc2unit = c->at<int32_t>(c->o_loc2unit);
+  b.unit_loc = c->at<int32_t>(c->o_unitloc);
+  b.unit_span = c->at<int2>(c->o_unitspan);
+  b.pairs = c->at<int2>(c->o_pairs);
+  b.pair_of = c->at<int32_t>(c->o_pairof);
+  b.unit_of = c->at<int32_t>(c->o_unitof);
+  b.imap = c->lines ? nullptr : c->at<int32_t>(c->o_imap);
+  b.items = c->at<int4>(c->o_gwork);
+  b.line_order = c->at<int4>(c->o_lineord);
+  b.ysqp = c->at<double>(c->o_ysqp);
+  b.ysq_k = c->at<double>(c->o_ysq);
+  b.st = c->st();
+  const int nb = (c->width + 255) / 256;
+  const long most = std::max((long)c->n * p.nc, c->lines ? 0L : (long)c->n * p.q);
+  hipLaunchKernelGGL(k_bind_begin, dim3((unsigned)std::max(4L, std::min(1024L, (most + 255) / 256))), dim3(256), 0, s, b);
+  hipLaunchKernelGGL(k_bind_mask, dim3((unsigned)(nb * p.q + (c->y ? p.q * p.nc : 0))), dim3(256), 0, s, b);
+  if (c->lines) {
+    hipLaunchKernelGGL(k_bind_lines, dim3(1), dim3(1024), 0, s, b);
     HIPCHK(hipGetLastError());
-    if (c->lines) {
-      // frame-major hybrid data, temporary
-      const RowArgs ra = ag_host::row_args(c, c->y, c->at<float2>(c->o_T));
-      HIPCHK(launch_rows(p.nx, ra, true, s));
-      // per-line layout: the largest pair count is q per line
-      hipLaunchKernelGGL(k_build_yu, dim3(p.q * c->width, p.nc), dim3(256), 0, s, c->at<float2>(c->o_T),
-                         c->at<int2>(c->o_pairs), c->mask, c->at<int32_t>(c->o_locptr), c->n_loc, c->width,
-                         p.nc, p.nx,
-                         c->lmax, c->at<float2>(c->o_yh), c->st());
-      hipLaunchKernelGGL(k_build_yg, dim3((unsigned)gram_items_bound(c), p.nc), dim3(256), 0, s,
-                         c->at<float2>(c->o_yh), c->at<int4>(c->o_gwork), p.nc, p.nx, c->at<float2>(c->o_yg),
-                         c->st());
-      HIPCHK(hipGetLastError());
+    if (c->y) {
+      // frame-major hybrid data (temporary), then its copies by line
+      HIPCHK(launch_rows(p.nx, ag_host::row_args(c, c->y, c->at<float2>(c->o_T)), true, s));
+      hipLaunchKernelGGL(k_build_lines, dim3((unsigned)gram_items_bound(c), p.nc), dim3(256), 0, s,
+                         c->at<float2>(c->o_T), c->at<int2>(c->o_pairs), c->at<int4>(c->o_gwork), p.nc, p.nx, c->lmax,
+                         c->at<float2>(c->o_yh), c->at<float2>(c->o_yg), c->st());
     }
+  } else {
+    hipLaunchKernelGGL(k_bind_index, dim3(1), dim3(1024), 0, s, b);
+    hipLaunchKernelGGL(k_bind_fill, dim3(nb, p.q), dim3(256), 0, s, b);
   }
+  HIPCHK(hipGetLastError());
   c->bound = 1;
   return ALTGDMIN_OK;
 }
@@ -905,11 +928,7 @@ altgdmin_status altgdmin_iterate(altgdmin_ctx* c, int32_t n_iter, void* d_U, voi
   HIPCHK(to_pixmajor(c, static_cast<const float2*>(d_U)));
   // every solve also writes B to the caller's buffer (no copy launch after
   // the loop; a halt part-way leaves there the last B computed)
-  struct CallScope {  // the caller's buffer is forgotten on every way out
-    altgdmin_ctx* c;
-    ~CallScope() { c->b_out = nullptr; }
-  } scope{c};
-  c->b_out = static_cast<float2*>(d_B);
+  const BOut scope(c, d_B);
   for (int t = 0; t < n_iter; ++t)
     HIPCHK(one_iteration(c, static_cast<float2*>(d_U), static_cast<float2*>(d_U_prev)));
   if (h_iters_done) {
@@ -943,8 +962,7 @@ altgdmin_status altgdmin_cost(altgdmin_ctx* c, const void* d_U, double* d_f) {
   if (!c || !d_U || !d_f) return ALTGDMIN_EINVAL;
   if (!c->bound || !c->y) return ALTGDMIN_ESTATE;
   // the last iteration's statistics read cost_k, which the solve below overwrites
-  HIPCHK(launch_stats_finish(c->st(), c->at<double2>(c->o_stsrc), c->at<double>(c->o_cost), c->p.q, c->p.r,
-                             c->stream));
+  HIPCHK(finish_stats(c));
   HIPCHK(to_pixmajor(c, static_cast<const float2*>(d_U)));
   HIPCHK(fwd_transform(c, 0));
   HIPCHK(gram_solve(c, 0));
@@ -957,26 +975,20 @@ altgdmin_status altgdmin_gradient(altgdmin_ctx* c, const void* d_U, void* d_B, v
   if (!c || !d_U) return ALTGDMIN_EINVAL;
   if (!c->bound || !c->y) return ALTGDMIN_ESTATE;
   const altgdmin_params& p = c->p;
-  HIPCHK(launch_stats_finish(c->st(), c->at<double2>(c->o_stsrc), c->at<double>(c->o_cost), p.q, p.r, c->stream));
+  HIPCHK(finish_stats(c));
   HIPCHK(to_pixmajor(c, static_cast<const float2*>(d_U)));
+  const BOut scope(c, d_B);  // the solve writes B to the caller's buffer too
   if (!d_G) {  // the LS step alone
     HIPCHK(fwd_transform(c, 0));
     HIPCHK(gram_solve(c, 0));
-    if (d_B)
-      hipLaunchKernelGGL(k_copy, dim3(64), dim3(256), 0, c->stream, c->at<float2>(c->o_B), static_cast<float2*>(d_B),
-                         (long)p.q * p.r);
-    return map_hip(hipGetLastError());
+    return ALTGDMIN_OK;
   }
   HIPCHK(gradient_pieces(c, 0));
   if (c->grad_parts > 1)
     hipLaunchKernelGGL(k_sum_parts, dim3(1024), dim3(256), 0, c->stream, c->at<float2>(c->o_G),
                        (long)c->n * p.r, c->grad_parts, c->at<float2>(c->o_G), (long)c->n * p.r);
-  if (d_B)
-    hipLaunchKernelGGL(k_copy, dim3(64), dim3(256), 0, c->stream, c->at<float2>(c->o_B),
-                       static_cast<float2*>(d_B), (long)p.q * p.r);
-  if (d_G)
-    hipLaunchKernelGGL(k_to_colmajor, dim3(1024), dim3(256), 0, c->stream, c->at<float2>(c->o_G), p.r,
-                       (long)c->n, static_cast<float2*>(d_G));
+  hipLaunchKernelGGL(k_to_colmajor, dim3(1024), dim3(256), 0, c->stream, c->at<float2>(c->o_G), p.r,
+                     (long)c->n, static_cast<float2*>(d_G));
   return map_hip(hipGetLastError());
 }
 
@@ -996,8 +1008,7 @@ altgdmin_status altgdmin_get_stats(altgdmin_ctx* c, altgdmin_stats* out) {
   if (!c || !out) return ALTGDMIN_EINVAL;
   if (!c->bound) return ALTGDMIN_ESTATE;
   DevState h;
-  HIPCHK(launch_stats_finish(c->st(), c->at<double2>(c->o_stsrc), c->at<double>(c->o_cost), c->p.q, c->p.r,
-                             c->stream));
+  HIPCHK(finish_stats(c));
   HIPCHK(hipStreamSynchronize(c->stream));
   HIPCHK(hipMemcpy(&h, c->st(), sizeof(DevState), hipMemcpyDeviceToHost));
   out->t = h.t;

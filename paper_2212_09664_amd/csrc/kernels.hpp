@@ -152,5 +152,4 @@ hipError_t launch_cols_adj(int N, const ColAdjArgs& a, bool cgls, int images, hi
 enum { IDX_FWD = 0, IDX_ADJ = 1, IDX_RES = 2 };  // T -> y; y -> T; T -> F^H(y - F T) in T
 hipError_t launch_index_rows(int N, const IndexRowArgs& a, int mode, bool cgls, int images, hipStream_t st);
 
-__global__ void k_twiddle(float2* tw, int N);
 }  // namespace ag

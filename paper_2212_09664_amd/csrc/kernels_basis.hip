@@ -421,23 +421,6 @@ __global__ __launch_bounds__(AG_NT) void k_basis_rows(BasisArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// setup: per-line data yu[nc*nx*p0 + (c*np + p)*nx + x] from the hybrid
-// frame-major y'[k][c][l][x]; grid (pairs, nc).
-// ---------------------------------------------------------------------------
-__global__ void k_build_yu(const float2* yh, const int2* pairs, const int32_t* mask, const int32_t* loc_ptr,
-                           int n_loc, int width, int nc, int nx, int lmax, float2* yu, const DevState* st) {
-  if (st->err) return;
-  const int P = blockIdx.x, c = blockIdx.y;
-  if (P >= loc_ptr[n_loc]) return;  // grid covers the largest possible pair count
-  const int2 kl = pairs[P];
-  const int ky = mask[(long)kl.x * width + kl.y];
-  const int p0 = loc_ptr[ky], np = loc_ptr[ky + 1] - p0, p = P - p0;
-  const float2* src = yh + (((long)kl.x * nc + c) * lmax + kl.y) * nx;
-  float2* dst = yu + (long)nc * nx * p0 + ((long)c * np + p) * nx;
-  for (int x = threadIdx.x; x < nx; x += blockDim.x) dst[x] = src[x];
-}
-
-// ---------------------------------------------------------------------------
 // gradient fold, 1D Cartesian: per sampled line u and coil c,
 //   K_c[u][x][:] = sum_{p in u} (W_c[u][x][:] . b_p - y_p(c, x)) conj(b_p)^T
 // over the line's (frame, line) pairs p: the residual of every sample times
@@ -825,18 +808,6 @@ __global__ void k_to_colmajor(const float2* src, int r, long n, float2* dst) {
 // launchers
 // ---------------------------------------------------------------------------
 int basis_ct(int N) { return N >= 256 ? 16 : (N >= 128 ? 32 : 64); }
-
-// coil maps in the layout the transforms read: [c][x / txx][y][x % txx], so
-// that a workgroup's txx columns are one contiguous block per coil
-__global__ void k_coil_block(const float2* coils, float2* dst, int nx, int ny, int txx, long n, int nc) {
-  const long tot = n * nc;
-  for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < tot; e += (long)gridDim.x * blockDim.x) {
-    const long c = e / n, rem = e - c * n;
-    const long xg = rem / ((long)ny * txx), rem2 = rem - xg * ny * txx;
-    const int y = (int)(rem2 / txx), xl = (int)(rem2 - (long)y * txx);
-    dst[e] = coils[c * n + (long)y * nx + xg * txx + xl];
-  }
-}
 
 int basis_txx(int N, int nx, int r) {
   const int ct = basis_ct(N);

@@ -14,32 +14,208 @@ namespace ag {
 // (INDEX).  For every location the list of (frame k, position e) samples
 // that hit it is stored contiguously, in increasing k (deterministic).
 // ===========================================================================
-__global__ void k_inv_bitmap(const int32_t* mask, const int32_t* m_k, int width, int per, int n_loc,
-                             uint32_t* bitmap, int nw, DevState* st) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x, k = blockIdx.y;
-  const int mk = m_k[k];
-  if (mk < 0 || mk > width * per || (mk % per) != 0) {
-    if (e == 0) set_error(st, 1 /*EINVAL: bad m_k*/, k);
+__device__ __forceinline__ void state_reset(DevState* st, int full) {
+  if (full) {
+    st->err = 0;
+    st->err_frame = -1;
+    st->n_units = 0;
+    st->n_gwork = 0;
+  }
+  st->halt = 0;
+  st->step_ok = 0;
+  st->t = 0;
+  st->exited = 0;
+  st->converged = 0;
+  st->eta = -1.0;
+  st->step_flags = 0;
+  st->eta_next = -1.0;
+  st->f = 0.0;
+  st->sd = 0.0;
+  st->grad_norm = 0.0;
+  st->stats_pending = 0;
+  st->n_trunc = 0;
+  st->exit_run = 0;
+}
+
+// What needs nothing but the arguments, in one launch: the state, the twiddle
+// tables tw[t] = exp(-2 pi i t / N) (from a double-precision sincospi), the coil
+// maps in the layout the basis transforms read ([c][x / txx][y][x % txx], so that a
+// workgroup's txx columns are one contiguous block per coil), the zeroed
+// bitmap and (general masks) the map of locations to samples set to -1.
+__global__ __launch_bounds__(256) void k_bind_begin(BindArgs a) {
+  const long t0 = (long)blockIdx.x * 256 + threadIdx.x, nt = (long)gridDim.x * 256;
+  if (t0 == 0) state_reset(a.st, 1);
+  if (t0 < a.nx + a.ny) {
+    const int N = t0 < a.nx ? a.nx : a.ny, t = t0 < a.nx ? (int)t0 : (int)t0 - a.nx;
+    double s, c;
+    sincospi(2.0 * (double)t / (double)N, &s, &c);
+    (t0 < a.nx ? a.twx : a.twy)[t] = make_float2((float)c, (float)(-s));
+  }
+  for (long e = t0; e < (long)a.n_loc * a.nw; e += nt) a.bitmap[e] = 0;
+  if (a.imap)
+    for (long e = t0; e < (long)a.q * a.n; e += nt) a.imap[e] = -1;
+  for (long e = t0; e < a.n * a.nc; e += nt) {
+    const long c = e / a.n, rem = e - c * a.n;
+    const long xg = rem / ((long)a.ny * a.txx), rem2 = rem - xg * a.ny * a.txx;
+    const int y = (int)(rem2 / a.txx), xl = (int)(rem2 - (long)y * a.txx);
+    a.coilb[e] = a.coils[c * a.n + (long)y * a.nx + xg * a.txx + xl];
+  }
+}
+
+// the masks' bits (a workgroup per 256 entries of a frame: blocks 0 ..
+// nb q - 1), and with measurements ||y_{k,c}||^2 in FP64 (the next q nc blocks)
+__global__ __launch_bounds__(256) void k_bind_mask(BindArgs a) {
+  __shared__ double red[4];
+  const int nb = (a.width + 255) / 256, tid = threadIdx.x;
+  if ((int)blockIdx.x >= nb * a.q) {
+    const int kc = blockIdx.x - nb * a.q, k = kc / a.nc;
+    const int mk = min(max(a.m_k[k], 0), a.m_max);
+    const float2* yk = a.y + (long)kc * a.m_max;
+    double s = 0.0;
+#pragma unroll 8
+    for (int i = tid; i < mk; i += 256) {
+      const float2 v = yk[i];
+      s += (double)v.x * v.x + (double)v.y * v.y;
+    }
+    s = wave_sum(s);
+    if ((tid & 63) == 0) red[tid >> 6] = s;
+    __syncthreads();
+    if (tid == 0) a.ysqp[kc] = (red[0] + red[1]) + (red[2] + red[3]);
     return;
   }
-  if (e >= mk / per) return;
-  const int loc = mask[(long)k * width + e];
-  if (loc < 0 || loc >= n_loc) {
-    set_error(st, 1 /*EINVAL*/, k);
+  const int e = (blockIdx.x % nb) * 256 + tid, k = blockIdx.x / nb;
+  const int mk = a.m_k[k];
+  if (mk < 0 || mk > a.width * a.per || (mk % a.per) != 0) {
+    if (e == 0) set_error(a.st, 1 /*EINVAL: bad m_k*/, k);
+    return;
+  }
+  if (e >= mk / a.per) return;
+  const int loc = a.mask[(long)k * a.width + e];
+  if (loc < 0 || loc >= a.n_loc) {
+    set_error(a.st, 1 /*EINVAL*/, k);
     return;
   }
   const uint32_t bit = 1u << (k & 31);
-  const uint32_t old = atomicOr(&bitmap[(long)loc * nw + (k >> 5)], bit);
-  if (old & bit) set_error(st, 1 /*EINVAL: repeated location in a frame*/, k);
+  const uint32_t old = atomicOr(&a.bitmap[(long)loc * a.nw + (k >> 5)], bit);
+  if (old & bit) set_error(a.st, 1 /*EINVAL: repeated location in a frame*/, k);
 }
 
-// the locations' sample counts and their exclusive prefix sums (pairs per
+// ||y_k||^2 (its coils' parts in order), gamma = trunc_c * sum |y|^2 / (m q) with
+// m = max_k m_k, and mbar = sum_k m_k / q, by one workgroup (q <= 128 <= threads)
+__device__ __forceinline__ void bind_stats(const BindArgs& a) {
+  __shared__ double s_ys[128];
+  __shared__ int s_mk[128];
+  const int tid = threadIdx.x;
+  if (!a.y) return;
+  if (tid < a.q) {
+    double s = 0.0;
+    for (int c = 0; c < a.nc; ++c) s += a.ysqp[(long)tid * a.nc + c];
+    a.ysq_k[tid] = s;
+    s_ys[tid] = s;
+    s_mk[tid] = a.m_k[tid];
+  }
+  __syncthreads();
+  if (tid != 0) return;
+  double ys = 0.0, msum = 0.0;
+  int mmax = 0;
+  for (int k = 0; k < a.q; ++k) {
+    ys += s_ys[k];
+    msum += s_mk[k];
+    mmax = max(mmax, s_mk[k]);
+  }
+  a.st->ysq = ys;
+  a.st->mbar = msum / a.q;
+  a.st->gamma = a.trunc_c > 0 ? a.trunc_c * ys / ((double)mmax * a.q) : INFINITY;
+}
+
+// inclusive scan of v over the 1024 threads of the workgroup (s_w: 16 ints)
+__device__ __forceinline__ int block_scan(int v, int* s_w) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  for (int off = 1; off < 64; off <<= 1) {
+    const int u = __shfl_up(v, off);
+    if (lane >= off) v += u;
+  }
+  __syncthreads();
+  if (lane == 63) s_w[wv] = v;
+  __syncthreads();
+  for (int w = 0; w < wv; ++w) v += s_w[w];
+  return v;
+}
+
+// rank of frame k among the frames that sample location loc
+__device__ __forceinline__ int frame_rank(const uint32_t* bm, int k) {
+  int rank = 0;
+  for (int w = 0; w < (k >> 5); ++w) rank += __popc(bm[w]);
+  return rank + __popc(bm[k >> 5] & ((1u << (k & 31)) - 1u));
+}
+
+// Line masks, the rest of the index tables by one workgroup (n_loc = ny <=
+// 512 lines, one per thread): the lines' pair counts and offsets, the sampled
+// lines (units) in order, the Gram kernel's work items (unit u, tile t of 8 of
+// its pairs), the fold's dispatch order (units by pair count, the largest
+// first, ties by index, then the unsampled rows, so that the longest fold
+// workgroups start first instead of ending the launch), every frame's pairs,
+// and the data's statistics.  15 launches of a bind became 5.
+__global__ __launch_bounds__(1024) void k_bind_lines(BindArgs a) {
+  __shared__ int s_w[16], s_ptr[512], s_unit[512], s_np[512], s_p0[512], s_nu;
+  const int tid = threadIdx.x;
+  int c = 0;
+  if (tid < a.n_loc)
+    for (int w = 0; w < a.nw; ++w) c += __popc(a.bitmap[(long)tid * a.nw + w]);
+  const int pc = block_scan(c, s_w) - c, pu = block_scan(c > 0, s_w) - (c > 0);
+  if (tid < a.n_loc) {
+    a.loc_ptr[tid] = pc;
+    a.loc2unit[tid] = c > 0 ? pu : -1;
+    s_ptr[tid] = pc;
+    s_unit[tid] = c > 0 ? pu : -1;
+    if (c > 0) {
+      a.unit_loc[pu] = tid;
+      a.unit_span[pu] = make_int2(pc, c);  // the unit's samples: pairs [pc, pc + c)
+      s_np[pu] = c;
+      s_p0[pu] = pc;
+    }
+    if (tid == a.n_loc - 1) {
+      a.loc_ptr[a.n_loc] = pc + c;
+      s_nu = pu + (c > 0);
+      a.st->n_units = s_nu;
+    }
+  }
+  __syncthreads();
+  const int nu = s_nu, np = tid < nu ? s_np[tid] : 0, nt = (np + 7) / 8;
+  const int o1 = block_scan(nt, s_w);
+  for (int t = 0; t < nt; ++t) a.items[o1 - nt + t] = make_int4(tid, t, s_p0[tid], np);
+  if (tid == 1023) a.st->n_gwork = o1;
+  if (tid < nu) {
+    int rk = 0;
+    for (int v = 0; v < nu; ++v) rk += (s_np[v] > np) || (s_np[v] == np && v < tid);
+    a.line_order[rk] = make_int4(tid, s_p0[tid], np, 0);
+  } else if (tid < a.n_loc) {
+    a.line_order[tid] = make_int4(tid, 0, 0, 0);
+  }
+  if (!a.st->err) {  // (a mask that failed its checks has no valid pairs)
+    for (int i = tid; i < a.q * a.width; i += 1024) {
+      const int k = i / a.width, e = i - k * a.width;
+      if (e >= a.m_k[k] / a.per) continue;
+      const int loc = a.mask[i], pos = s_ptr[loc] + frame_rank(a.bitmap + (long)loc * a.nw, k);
+      a.pairs[pos] = make_int2(k, e);
+      a.pair_of[i] = pos;
+      a.unit_of[i] = s_unit[loc];
+    }
+  }
+  bind_stats(a);
+}
+
+// General masks: the locations' sample counts and their exclusive prefix sums (pairs per
 // location), and the sampled locations (units) numbered in order; one block
 // of 1024 threads over tiles of 1024 locations, scans within waves by
 // shuffles, a running total across tiles
-__global__ __launch_bounds__(1024) void k_inv_scan(const uint32_t* bitmap, int nw, int n_loc,
-                                                   int32_t* loc_ptr, int32_t* loc2unit,
-                                                   int32_t* unit_loc, int2* unit_span, DevState* st) {
+__global__ __launch_bounds__(1024) void k_bind_index(BindArgs a) {
+  const uint32_t* const bitmap = a.bitmap;
+  const int nw = a.nw, n_loc = a.n_loc;
+  int32_t* const loc_ptr = a.loc_ptr;
+  int32_t* const loc2unit = a.loc2unit;
+  int32_t* const unit_loc = a.unit_loc;
+  int2* const unit_span = a.unit_span;
   constexpr int LPT = 1;  // locations per thread and tile (4: slower, the loads less coalesced)
   __shared__ int s_wc[16], s_wu[16];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -99,100 +275,26 @@ __global__ __launch_bounds__(1024) void k_inv_scan(const uint32_t* bitmap, int n
   }
   if (tid == 0) {
     loc_ptr[n_loc] = carry_c;
-    st->n_units = carry_u;
+    a.st->n_units = carry_u;
   }
+  bind_stats(a);
 }
 
-__global__ void k_inv_fill(const int32_t* mask, const int32_t* m_k, int width, int per, int n_loc,
-                           const uint32_t* bitmap, int nw, const int32_t* loc_ptr, const int32_t* loc2unit,
-                           int2* pairs, int32_t* pair_of, int32_t* unit_of, int32_t* imap, const DevState* st) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x, k = blockIdx.y;
-  if (st->err) return;
-  if (e >= m_k[k] / per) return;
-  const int loc = mask[(long)k * width + e];
-  const uint32_t* bm = bitmap + (long)loc * nw;
-  int rank = 0;
-  for (int w = 0; w < (k >> 5); ++w) rank += __popc(bm[w]);
-  rank += __popc(bm[k >> 5] & ((1u << (k & 31)) - 1u));
-  const int pos = loc_ptr[loc] + rank;
-  pairs[pos] = make_int2(k, e);
-  pair_of[(long)k * width + e] = pos;
-  unit_of[(long)k * width + e] = loc2unit[loc];
-  if (imap) imap[(long)k * n_loc + loc] = e;  // general masks: frame k's sample at the location
-}
-
-__global__ void k_fill_i32(int32_t* p, int32_t v, long n) {
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) p[i] = v;
-}
-
-// ||y_{k,c}||^2 in FP64, one workgroup per (frame k, coil c): part[k * nc + c]
-__global__ __launch_bounds__(AG_NT) void k_ysq(const float2* y, const int32_t* m_k, int nc, int m_max,
-                                               double* part) {
-  __shared__ double red[AG_NT];
-  const int k = blockIdx.x, c = blockIdx.y, tid = threadIdx.x;
-  const int mk = m_k[k];
-  const float2* yk = y + ((long)k * nc + c) * m_max;
-  double s = 0.0;
-#pragma unroll 8
-  for (int i = tid; i < mk; i += AG_NT) {
-    const float2 v = yk[i];
-    s += (double)v.x * v.x + (double)v.y * v.y;
-  }
-  red[tid] = s;
-  __syncthreads();
-  for (int off = AG_NT / 2; off > 0; off >>= 1) {
-    if (tid < off) red[tid] += red[tid + off];
-    __syncthreads();
-  }
-  if (tid == 0) part[(long)k * nc + c] = red[0];
-}
-
-// ||y_k||^2 = sum over coils of the parts, in coil order (one thread per frame)
-__global__ void k_ysq_sum(const double* part, int q, int nc, double* ysq_k) {
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < q; k += gridDim.x * blockDim.x) {
-    double s = 0.0;
-    for (int c = 0; c < nc; ++c) s += part[(long)k * nc + c];
-    ysq_k[k] = s;
-  }
-}
-
-// gamma = trunc_c * sum |y|^2 / (m q), m = max_k m_k; mbar = sum_k m_k / q
-__global__ void k_init_stats(const double* ysq_k, const int32_t* m_k, int q, double trunc_c, DevState* st) {
-  if (threadIdx.x != 0) return;
-  double ys = 0.0, msum = 0.0;
-  int mmax = 0;
-  for (int k = 0; k < q; ++k) {
-    ys += ysq_k[k];
-    msum += m_k[k];
-    mmax = max(mmax, m_k[k]);
-  }
-  st->ysq = ys;
-  st->mbar = msum / q;
-  st->gamma = trunc_c > 0 ? trunc_c * ys / ((double)mmax * q) : INFINITY;
+// general masks: every frame's pairs and its map of locations to samples
+__global__ __launch_bounds__(256) void k_bind_fill(BindArgs a) {
+  const int e = blockIdx.x * 256 + threadIdx.x, k = blockIdx.y;
+  if (a.st->err) return;
+  if (e >= a.m_k[k] / a.per) return;
+  const int loc = a.mask[(long)k * a.width + e];
+  const int pos = a.loc_ptr[loc] + frame_rank(a.bitmap + (long)loc * a.nw, k);
+  a.pairs[pos] = make_int2(k, e);
+  a.pair_of[(long)k * a.width + e] = pos;
+  a.unit_of[(long)k * a.width + e] = a.loc2unit[loc];
+  a.imap[(long)k * a.n_loc + loc] = e;
 }
 
 __global__ void k_state_reset(DevState* st, int full) {
-  if (threadIdx.x != 0) return;
-  if (full) {
-    st->err = 0;
-    st->err_frame = -1;
-    st->n_units = 0;
-    st->n_gwork = 0;
-  }
-  st->halt = 0;
-  st->step_ok = 0;
-  st->t = 0;
-  st->exited = 0;
-  st->converged = 0;
-  st->eta = -1.0;
-  st->step_flags = 0;
-  st->eta_next = -1.0;
-  st->f = 0.0;
-  st->sd = 0.0;
-  st->grad_norm = 0.0;
-  st->stats_pending = 0;
-  st->n_trunc = 0;
-  st->exit_run = 0;
+  if (threadIdx.x == 0) state_reset(st, full);
 }
 
 __global__ void k_state_set_eta(DevState* st, double eta) {

@@ -12,6 +12,27 @@
 
 namespace ag {
 
+// binding a problem: the tables that setup builds
+struct BindArgs {
+  const float2* coils;
+  const int32_t* mask;
+  const int32_t* m_k;
+  const float2* y;       // null: only the operators are used
+  long n;
+  int nx, ny, nc, q, m_max, width, per, n_loc, nw, txx;
+  double trunc_c;
+  float2 *twx, *twy, *coilb;
+  uint32_t* bitmap;      // [location][nw]: a bit per frame
+  int32_t *loc_ptr, *loc2unit, *unit_loc;
+  int2* unit_span;
+  int2* pairs;           // (frame, entry) by location
+  int32_t *pair_of, *unit_of;  // [frame][width]
+  int32_t* imap;         // general masks, else null: [frame][location] -> entry, -1
+  int4 *items, *line_order;    // line masks: the Gram's work items and the fold's order
+  double *ysqp, *ysq_k;
+  DevState* st;
+};
+
 struct GramLinesArgs {
   const float2* W;       // [c][u][x][j], ua rows per coil
   const float2* yu;      // per-line data [c][p][x]
@@ -343,17 +364,11 @@ __device__ __forceinline__ void tri_index(int o, int r, int& i, int& j) {
   j = i + rem;
 }
 
-__global__ void k_inv_bitmap(const int32_t* mask, const int32_t* m_k, int width, int per, int n_loc,
-                             uint32_t* bitmap, int nw, DevState* st);
-__global__ void k_inv_scan(const uint32_t* bitmap, int nw, int n_loc, int32_t* loc_ptr, int32_t* loc2unit,
-                           int32_t* unit_loc, int2* unit_span, DevState* st);
-__global__ void k_inv_fill(const int32_t* mask, const int32_t* m_k, int width, int per, int n_loc,
-                           const uint32_t* bitmap, int nw, const int32_t* loc_ptr, const int32_t* loc2unit, int2* pairs,
-                           int32_t* pair_of, int32_t* unit_of, int32_t* imap, const DevState* st);
-__global__ void k_fill_i32(int32_t* p, int32_t v, long n);
-__global__ void k_ysq(const float2* y, const int32_t* m_k, int nc, int m_max, double* part);
-__global__ void k_ysq_sum(const double* part, int q, int nc, double* ysq_k);
-__global__ void k_init_stats(const double* ysq_k, const int32_t* m_k, int q, double trunc_c, DevState* st);
+__global__ void k_bind_begin(BindArgs a);
+__global__ void k_bind_mask(BindArgs a);
+__global__ void k_bind_lines(BindArgs a);  // line masks: the index tables
+__global__ void k_bind_index(BindArgs a);  // general masks: the locations' tables
+__global__ void k_bind_fill(BindArgs a);   // general masks: the frames' pairs
 __global__ void k_state_reset(DevState* st, int full);
 __global__ void k_state_set_eta(DevState* st, double eta);
 hipError_t launch_x_times_v(const float2* X, const float2* Vs, int n, int q, int r, float2* U, const DevState* st,
@@ -377,9 +392,6 @@ __global__ void k_sum_parts(const float2* src, long stride, int nparts, float2* 
 hipError_t launch_basis(int which, int N, const BasisArgs& a, int grid_x, int grid_y, hipStream_t s);
 hipError_t launch_adj_qr(int N, const BasisArgs& a, hipStream_t s);
 hipError_t launch_fold2(const FoldArgs& a, bool lines, int grid_x, int grid_y, hipStream_t s);
-hipError_t launch_gram_work(const int2* unit_span, int4* items, int4* line_order, int n_loc, DevState* st,
-                            hipStream_t s);
-__global__ void k_build_yg(const float2* yu, const int4* items, int nc, int nx, float2* yg, const DevState* st);
 constexpr int CNN_BAND = 8;  // image rows per weight-gradient partial
 size_t cnn_pack_bytes(int cin);  // packed weights of a convolution over cin channels
 hipError_t launch_cnn_pack(const CnnLayers& a, hipStream_t s);
@@ -393,9 +405,8 @@ hipError_t launch_cnn_planes(const float2* X, long n, int q, double* partial, fl
 // mixed form, 1D Cartesian masks: which 0 forward, 1 adjoint + coil combine
 hipError_t launch_pdft(int which, int ny, const PdftArgs& a, int grid_x, int grid_y, hipStream_t s);
 int basis_txx(int N, int nx, int r);
-__global__ void k_coil_block(const float2* coils, float2* dst, int nx, int ny, int txx, long n, int nc);
-__global__ void k_build_yu(const float2* yh, const int2* pairs, const int32_t* mask, const int32_t* loc_ptr,
-                           int n_loc, int width, int nc, int nx, int lmax, float2* yu, const DevState* st);
+__global__ void k_build_lines(const float2* yh, const int2* pairs, const int4* items, int nc, int nx, int lmax,
+                              float2* yu, float2* yg, const DevState* st);
 __global__ void k_to_colmajor(const float2* src, int r, long n, float2* dst);
 __global__ void k_to_pixmajor(const float2* src, int r, long n, float2* dst);
 hipError_t launch_init_eig(const InitEigArgs& a, hipStream_t s);

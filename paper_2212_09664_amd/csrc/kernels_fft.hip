@@ -19,18 +19,6 @@
 namespace ag {
 
 // ---------------------------------------------------------------------------
-// twiddle table: tw[t] = exp(-2 pi i t / N), from a double-precision sincospi
-// ---------------------------------------------------------------------------
-__global__ void k_twiddle(float2* tw, int N) {
-  int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < N) {
-    double s, c;
-    sincospi(2.0 * (double)t / (double)N, &s, &c);
-    tw[t] = make_float2((float)c, (float)(-s));
-  }
-}
-
-// ---------------------------------------------------------------------------
 // rows: FFT along x of TR rows of length N per workgroup.
 // Row rho of the batch lives at src + rho*N.  With m_k != null the rows are
 // the padded measurement lines rho = (k*nc + c)*lmax + l, valid when

@@ -159,62 +159,40 @@ __device__ __forceinline__ void gram_lines_loop(const GramLinesArgs& a, int u, i
   }
 }
 
-// the Gram kernel's data per work item: [item][c][x][8 samples] complex,
-// zero past the line's sample count (consecutive lanes read consecutive
-// floats).  Grid (items bound, nc).
-__global__ void k_build_yg(const float2* yu, const int4* items, int nc, int nx, float2* yg, const DevState* st) {
-  const int w = blockIdx.x, c = blockIdx.y;
+// The loop's two copies of the hybrid data y'[k][c][l][x], per work item (line,
+// tile of 8 of its pairs) and coil: the line's block yu[nc nx p0 + (c np + p) nx +
+// x], read along x by the fold, and the Gram kernel's [item][c][x][8 samples], zero
+// past the line's count (consecutive lanes read consecutive floats), through
+// LDS.  Grid (items bound, nc).  256 x 256, 12 coils, 1,280 lines: 23 us, against
+// 34 us for two passes, the second reading the first's output.
+__global__ __launch_bounds__(256) void k_build_lines(const float2* yh, const int2* pairs, const int4* items, int nc,
+                                                     int nx, int lmax, float2* yu, float2* yg, const DevState* st) {
+  __shared__ float2 s[256 * 9];  // odd pitch: a store's lanes fall in different banks
+  const int w = blockIdx.x, c = blockIdx.y, tid = threadIdx.x;
   if (st->err || w >= st->n_gwork) return;
   const int4 it = items[w];  // (line, tile, first pair, pair count)
-  const float2* src = yu + (long)nc * nx * it.z + (long)c * it.w * nx;  // the line's [c][p][x] block
-  float2* dst = yg + ((long)w * nc + c) * nx * 8;
-  for (int e = threadIdx.x; e < nx * 8; e += blockDim.x) {
-    const int x = e >> 3, p = 8 * it.y + (e & 7);
-    dst[e] = (p < it.w) ? src[(long)p * nx + x] : make_float2(0.f, 0.f);
+  const float2* src[8];
+#pragma unroll
+  for (int p = 0; p < 8; ++p) {
+    const int2 kl = pairs[it.z + min(8 * it.y + p, it.w - 1)];
+    src[p] = yh + (((long)kl.x * nc + c) * lmax + kl.y) * nx;
   }
-}
-
-// the Gram kernel's work items (line u, sample tile t), one block of 1024
-// threads at setup: every sampled line contributes ceil(np_u / 8) items.
-// Also the fold's dispatch order: the sampled lines by pair count, largest
-// first (ties by index), then the unsampled rows in order, so that the
-// longest fold workgroups start first instead of ending the launch.
-__global__ __launch_bounds__(1024) void k_gram_work(const int2* unit_span, int4* items, int4* line_order,
-                                                    int n_loc, DevState* st) {
-  __shared__ int s_off[1024];
-  __shared__ int s_np[1024];
-  const int tid = threadIdx.x, nu = st->n_units;
-  int cnt = 0;
-  const int per = (nu + 1023) / 1024;
-  for (int u = tid * per; u < min(nu, (tid + 1) * per); ++u) cnt += max(1, (unit_span[u].y + 7) / 8);
-  s_off[tid] = cnt;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {  // inclusive scan
-    const int v = (tid >= off) ? s_off[tid - off] : 0;
-    __syncthreads();
-    s_off[tid] += v;
-    __syncthreads();
-  }
-  int o = s_off[tid] - cnt;
-  for (int u = tid * per; u < min(nu, (tid + 1) * per); ++u) {
-    const int2 sp = unit_span[u];
-    const int nt = max(1, (sp.y + 7) / 8);
-    for (int t = 0; t < nt; ++t) items[o++] = make_int4(u, t, sp.x, sp.y);
-  }
-  if (tid == 1023) st->n_gwork = s_off[1023];
-  if (nu <= 1024) {
-    if (tid < nu) s_np[tid] = unit_span[tid].y;
-    __syncthreads();
-    if (tid < nu) {
-      const int m = s_np[tid];
-      int rk = 0;
-      for (int v = 0; v < nu; ++v) rk += (s_np[v] > m) || (s_np[v] == m && v < tid);
-      const int2 sp = unit_span[tid];
-      line_order[rk] = make_int4(tid, sp.x, sp.y, 0);
+  float2* const dst = yu + (long)nc * nx * it.z + ((long)c * it.w + 8 * it.y) * nx;
+  float2* const dg = yg + ((long)w * nc + c) * nx * 8;
+  for (int x0 = 0; x0 < nx; x0 += 256) {
+    const int x = x0 + tid, xn = min(256, nx - x0);
+    float2 v[8];
+#pragma unroll
+    for (int p = 0; p < 8; ++p) v[p] = src[p][min(x, nx - 1)];
+    if (x0 > 0) __syncthreads();
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      const bool in = 8 * it.y + p < it.w;
+      if (in && x < nx) dst[(long)p * nx + x] = v[p];
+      s[tid * 9 + p] = in ? v[p] : make_float2(0.f, 0.f);
     }
-    for (int u = nu + tid; u < n_loc; u += 1024) line_order[u] = make_int4(u, 0, 0, 0);
-  } else {
-    for (int u = tid; u < n_loc; u += 1024) line_order[u] = make_int4(u, u < nu ? unit_span[u].x : 0, u < nu ? unit_span[u].y : 0, 0);
+    __syncthreads();
+    for (int e = tid; e < xn * 8; e += 256) dg[x0 * 8 + e] = s[(e >> 3) * 9 + (e & 7)];
   }
 }
 
@@ -616,12 +594,6 @@ static void launch_lines_tr(const GramLinesArgs& a, int ny, int ngroups, int ht,
   constexpr int NWG = GRAM_NWG;
   if (a.nx >= 64) hipLaunchKernelGGL((k_gram_lines_mma<T, TR, 4, NWG>), g, dim3(256 * NWG), 0, s, a);
   else hipLaunchKernelGGL((k_gram_lines_mma<T, TR, 1, NWG>), g, dim3(256 * NWG), 0, s, a);
-}
-
-hipError_t launch_gram_work(const int2* unit_span, int4* items, int4* line_order, int n_loc, DevState* st,
-                            hipStream_t s) {
-  hipLaunchKernelGGL(k_gram_work, dim3(1), dim3(1024), 0, s, unit_span, items, line_order, n_loc, st);
-  return hipGetLastError();
 }
 
 hipError_t launch_gram_lines(const GramLinesArgs& a, int ny, int ngroups, int max_pairs, bool fp64,

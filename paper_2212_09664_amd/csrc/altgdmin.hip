@@ -92,7 +92,6 @@ void carve(altgdmin_ctx* c) {
   c->o_qtot = take(sizeof(double2) * m_iter * (m_iter + 1) / 2);  // their sum (the fused step)
   c->o_stsrc = take(sizeof(double2) * STATS_SRC);  // deferred statistics of the step
   c->o_Vs = take(sizeof(float2) * (size_t)q * r);
-  c->o_V = take(sizeof(double2) * 2 * (size_t)q * (q | 1));  // matrix and reflectors, odd row pitch
   // temp: X0 plus the truncated hybrid data (LINES) or a chunk of coil images (INDEX)
   size_t tb = sizeof(float2) * (size_t)n * q;
   if (c->lines)
@@ -667,12 +666,9 @@ hipError_t spectral_eig(altgdmin_ctx* c, int r_eig, double* lam_out) {
   double2* sum = c->at<double2>(c->o_qpart) + (size_t)nbu * nout;
   AGCHK(launch_sum_partials(c->at<double2>(c->o_qpart), nbu, nout, sum, s));
   ie.part = sum;
-  ie.nblk = 1;
   ie.q = p.q;
   ie.r = r_eig;
   ie.lam_out = lam_out;
-  ie.V = c->at<double2>(c->o_V);
-  ie.in_lds = p.q <= 64;
   ie.Vs = c->at<float2>(c->o_Vs);
   ie.st = c->st();
   AGCHK(launch_init_eig(ie, s));

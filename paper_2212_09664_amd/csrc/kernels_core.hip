@@ -791,13 +791,60 @@ hipError_t launch_step_apply(const QrSmallArgs& a, const ApplyArgs& ap, hipStrea
 // one-wave reductions
 __device__ __forceinline__ double2 wave_sum2(double2 v) { return make_double2(wave_sum(v.x), wave_sum(v.y)); }
 
-// number of eigenvalues of the real symmetric tridiagonal (d, e) below x
-// (Sturm count of the LDL^T pivots; tiny pivots are replaced by -pivmin)
-__device__ int sturm_count(const double* d, const double* e2, int n, double x, double pivmin) {
+// Number of eigenvalues below each of E points of the real symmetric
+// tridiagonal (d, e), scaled so that |d|, |e| <= 1 and padded to a multiple of
+// eight rows by d = 4, e = 0.  The sign changes of the leading minors' sequence
+// p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2}, whose pair of values is scaled by a
+// power of two every eight rows: four instructions a row and one dependent
+// multiply-add, where the pivots' quotients need a division.  A single minor of
+// zero changes no count (its neighbours' signs differ); two in a row, also by
+// underflow within eight rows, are reported in `zero` and left to sturm_pivots.
+template <int E>
+__device__ __forceinline__ bool sturm_minors(const double* d, const double* e2, int n, const double (&x)[E],
+                                             int (&cnt)[E]) {
+  double p[E], pp[E], eb = 0.0;  // eb: the squared off-diagonal before the row
+  bool zero = false;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    p[e] = 1.0;
+    pp[e] = 0.0;
+    cnt[e] = 0;
+  }
+#pragma unroll 1
+  for (int i0 = 0; i0 < n; i0 += 8) {
+    unsigned sg[E];  // the signs of the minor before the block and of its eight
+#pragma unroll
+    for (int e = 0; e < E; ++e) sg[e] = (unsigned)__double2hiint(p[e]) >> 31;
+#pragma unroll
+    for (int i = i0; i < i0 + 8; ++i) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const double q = fma(d[i] - x[e], p[e], -(eb * pp[e]));
+        sg[e] = __builtin_amdgcn_alignbit(sg[e], (unsigned)__double2hiint(q), 31);
+        pp[e] = p[e];
+        p[e] = q;
+      }
+      eb = e2[i];
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      cnt[e] += __popc((sg[e] ^ (sg[e] >> 1)) & 0xffu);
+      zero = zero || (p[e] == 0.0 && pp[e] == 0.0);
+      const int ex = -__builtin_amdgcn_frexp_exp(fabs(p[e]) > fabs(pp[e]) ? p[e] : pp[e]);
+      p[e] = __builtin_amdgcn_ldexp(p[e], ex);
+      pp[e] = __builtin_amdgcn_ldexp(pp[e], ex);
+    }
+  }
+  return zero;
+}
+
+// the same count from the LDL^T pivots, tiny ones replaced by -pivmin
+__device__ __noinline__ int sturm_pivots(const double* d, const double* e2, int n, double x) {
+  const double pivmin = 1e-300;
   double q = d[0] - x;
   if (fabs(q) < pivmin) q = -pivmin;
   int cnt = q < 0.0;
-#pragma unroll 8
+#pragma unroll 1
   for (int i = 1; i < n; ++i) {
     q = d[i] - x - e2[i - 1] * rcp_nr(q);
     if (fabs(q) < pivmin) q = -pivmin;
@@ -806,421 +853,489 @@ __device__ int sturm_count(const double* d, const double* e2, int n, double x, d
   return cnt;
 }
 
-// back-transformation by one wave (q <= 64): Y = Q D Z with Q = H_0 ... H_{n-3},
-// then V_r Sigma_r^{-1} = Y diag(1 / sqrt(lambda_j)) into Vs (r <= RJ).  Lane
-// (column j = l / G, row group g = l % G, G = 64 / RJ) keeps rows g, g + G, ... of Y in
-// registers for the whole product; a reflector's column sums are taken over
-// a column's G adjacent lanes by DPP moves, with no barrier; rows outside the
-// reflector are selected to zero rather than branched around.
-template <int RJ, int NR>
-__device__ __forceinline__ void backtransform_wave(const double2* Vh, int ld, const double* s_beta, const double2* s_ph,
-                                                   const double* sy, const double* s_lam, int n, int r, int l,
-                                                   float2* Vs) {
-  constexpr int G = 64 / RJ;
-  static_assert(G == 4 || G == 8, "column sums over 4 or 8 adjacent lanes");
-  const int j = l / G, g = l % G, jc = min(j, r - 1);
-  double2 y[NR];
-  int roff[NR];
+// multisection by one wave: E eigenvalues at once, of ascending indices idx[e],
+// 64 lanes with one count each per round (a 65-section of the interval), to an
+// isolating interval of relative width 1e-10, whose middle goes to lam[e * step]
+template <int E>
+__device__ __forceinline__ void multisect(const double* d, const double* e2, int n, double lo0, double hi0, int l,
+                                          const int (&idx)[E], double* lam, int step) {
+  double lo[E], hi[E], x[E];
+  int cnt[E];
 #pragma unroll
-  for (int t = 0; t < NR; ++t) {
-    const int i = g + G * t, ic = min(i, n - 1);
-    roff[t] = ic * ld;
-    const double z = i < n ? sy[ic * r + jc] : 0.0;
-    const double2 ph = s_ph[ic];
-    y[t] = make_double2(ph.x * z, ph.y * z);
+  for (int e = 0; e < E; ++e) {
+    lo[e] = lo0;
+    hi[e] = hi0;
   }
-  for (int k = n - 3; k >= 0; --k) {
-    const double beta = s_beta[k];
-    if (beta == 0.0) continue;  // the same in every lane
-    // the reflector's rows kept in registers when they fit (NR <= 8), else read again for the update
-    constexpr bool KEEP = NR <= 8;
-    double2 v[KEEP ? NR : 1];
-    double sx = 0.0, sy_ = 0.0;
+#pragma unroll 1
+  for (int rnd = 0; rnd < 80; ++rnd) {
 #pragma unroll
-    for (int t = 0; t < NR; ++t) {  // conj(v) y over the reflector's rows
-      // rows outside it read a valid address whose content is not the
-      // reflector's (possibly not a finite number): selected away, not
-      // multiplied by zero
-      const int i = g + G * t;
-      const double2 vl = Vh[roff[t] + k];
-      const double2 vt = (i > k && i < n) ? vl : make_double2(0.0, 0.0);
-      if constexpr (KEEP) v[t] = vt;
-      sx = fma(vt.x, y[t].x, fma(vt.y, y[t].y, sx));
-      sy_ = fma(vt.x, y[t].y, fma(-vt.y, y[t].x, sy_));
-    }
-    sx += dpp_get<DPP_XOR1>(sx);
-    sy_ += dpp_get<DPP_XOR1>(sy_);
-    sx += dpp_get<DPP_XOR2>(sx);
-    sy_ += dpp_get<DPP_XOR2>(sy_);
-    if constexpr (G == 8) {
-      sx += dpp_get<DPP_HALF_MIRROR>(sx);
-      sy_ += dpp_get<DPP_HALF_MIRROR>(sy_);
-    }
-    sx *= beta;
-    sy_ *= beta;
+    for (int e = 0; e < E; ++e) x[e] = lo[e] + (hi[e] - lo[e]) * (double)(l + 1) * (1.0 / 65.0);
+    if (__any(sturm_minors<E>(d, e2, n, x, cnt))) {
 #pragma unroll
-    for (int t = 0; t < NR; ++t) {  // y -= v (beta v^H y), zero outside the reflector
-      double2 vt;
-      if constexpr (KEEP) {
-        vt = v[t];
-      } else {
-        const int i = g + G * t;
-        const double2 vl = Vh[roff[t] + k];
-        vt = (i > k && i < n) ? vl : make_double2(0.0, 0.0);
+      for (int e = 0; e < E; ++e) cnt[e] = sturm_pivots(d, e2, n, x[e]);
+    }
+    bool done = true;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      // the counts rise with the lane: the last point at or below the eigenvalue, the first above it
+      const unsigned long long above = __ballot(cnt[e] > idx[e]);
+      const int f = above ? __builtin_ctzll(above) : 64;
+      const double nlo = lane_get(x[e], f > 0 ? f - 1 : 0), nhi = lane_get(x[e], f < 64 ? f : 63);
+      if (f > 0) lo[e] = nlo;
+      if (f < 64) hi[e] = nhi;
+      done = done && hi[e] - lo[e] <= 1e-10 * fmax(fabs(lo[e]), fabs(hi[e])) + 1e-300;
+    }
+    if (done) break;  // the same in every lane
+  }
+  if (l == 0) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) lam[e * step] = 0.5 * (lo[e] + hi[e]);
+  }
+}
+
+// c ? v : 0, part by part (a selected struct would go through memory)
+__device__ __forceinline__ double2 dkeep(bool c, double2 v) { return make_double2(c ? v.x : 0.0, c ? v.y : 0.0); }
+
+// inclusive product over the lanes 0 .. l
+__device__ __forceinline__ double2 wave_scan_mul(double2 v, int l) {
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const double2 u = make_double2(__shfl_up(v.x, off), __shfl_up(v.y, off));
+    if (l >= off) v = dmul(u, v);
+  }
+  return v;
+}
+
+__host__ __device__ constexpr int eig_vh_off(int n, int k) { return k * (n - 1) - k * (k - 1) / 2; }
+// waves: 16 columns each.  What every wave computes for itself is issued once per
+// wave, so one wave per SIMD where the columns fit (q <= 64), else two.
+template <int NH>
+constexpr int EIG_W = 4 * NH;
+// LDS of the reduction beside the reflectors, in double2: partial products, column, w and two v
+template <int NH>
+constexpr int EIG_WORK = EIG_W<NH> * 64 * NH + 64 * NH + 3 * (64 * NH + 1);
+
+// back-transformation by one wave: Y = Q D Z with Q = H_0 ... H_{n-3}, then V_r
+// Sigma_r^{-1} = Y diag(1 / sqrt(lambda_j)) into Vs, for the columns 4 wv .. 4 wv + 3.
+// Sixteen lanes per column keep its rows g, g + 16, ... in registers for the
+// whole product, a reflector's column sums are DPP moves, and there is no
+// barrier; the next reflector's rows are read during this one's arithmetic.
+template <int NH>
+__device__ __forceinline__ void backtransform(const double2* Vh, const double* s_beta, const double2* s_ph,
+                                              const double* sy, const double* s_lam, double unit, int n, int r, int wv,
+                                              int l, float2* Vs) {
+  constexpr int NT = 4 * NH;
+  const int g = l & 15, j = 4 * wv + (l >> 4), jc = min(j, r - 1);
+  const int zr = n * (n - 1) / 2 - 1;  // a row of zero: the last column has no reflector
+  double2 y[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int i = min(g + 16 * t, n - 1);
+    const double z = sy[i * r + jc];
+    y[t] = dkeep(g + 16 * t < n, make_double2(s_ph[i].x * z, s_ph[i].y * z));
+  }
+  auto reflector = [&](int k, double2 (&dst)[NT]) {  // rows outside it are zero
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int i = g + 16 * t, kc = max(k, 0);
+      dst[t] = Vh[i > kc && i < n ? eig_vh_off(n, kc) + i - kc - 1 : zr];
+    }
+  };
+  if (n > 2) {
+    double2 vc[NT], vx[NT];
+    reflector(n - 3, vc);
+#pragma unroll 1
+    for (int k = n - 3; k >= 0; --k) {
+      const double bk = s_beta[k];
+      reflector(k - 1, vx);
+      double2 s = make_double2(0.0, 0.0);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {  // conj(v) y
+        s.x = fma(vc[t].x, y[t].x, fma(vc[t].y, y[t].y, s.x));
+        s.y = fma(vc[t].x, y[t].y, fma(-vc[t].y, y[t].x, s.y));
       }
-      const double ux = vt.x * sx - vt.y * sy_, uy = vt.x * sy_ + vt.y * sx;
-      y[t] = make_double2(y[t].x - ux, y[t].y - uy);
+      s = make_double2(s.x + dpp_get<DPP_XOR1>(s.x), s.y + dpp_get<DPP_XOR1>(s.y));
+      s = make_double2(s.x + dpp_get<DPP_XOR2>(s.x), s.y + dpp_get<DPP_XOR2>(s.y));
+      s = make_double2(s.x + dpp_get<DPP_ROR4>(s.x), s.y + dpp_get<DPP_ROR4>(s.y));
+      s = make_double2(bk * (s.x + dpp_get<DPP_ROR8>(s.x)), bk * (s.y + dpp_get<DPP_ROR8>(s.y)));
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        y[t].x = fma(-vc[t].x, s.x, fma(vc[t].y, s.y, y[t].x));
+        y[t].y = fma(-vc[t].x, s.y, fma(-vc[t].y, s.x, y[t].y));
+        vc[t] = vx[t];
+      }
     }
   }
-  const double sc = 1.0 / sqrt(s_lam[jc]);
+  const double sc = 1.0 / sqrt(s_lam[jc] * unit);
 #pragma unroll
-  for (int t = 0; t < NR; ++t) {
-    const int i = g + G * t;
+  for (int t = 0; t < NT; ++t) {
+    const int i = g + 16 * t;
     if (i < n && j < r) Vs[i * r + j] = make_float2((float)(y[t].x * sc), (float)(y[t].y * sc));
   }
 }
 
 // ===========================================================================
 // spectral initialisation, the q x q eigenproblem: the r largest eigenpairs
-// of the Hermitian X_0^H X_0 by one wave, then V_r Sigma_r^{-1}:
+// of the Hermitian X_0^H X_0 (q <= 64 NH) by one workgroup, then V_r Sigma_r^{-1}:
 //  1. Householder reduction M = Q T Q^H, T tridiagonal with complex
-//     off-diagonals e_k; reflectors H_k = I - beta_k v_k v_k^H kept in Vh;
+//     off-diagonals e_k; reflectors H_k = I - beta_k v_k v_k^H kept in LDS,
+//     packed (column k from eig_vh_off(n, k), its rows k + 1 .. n - 1);
 //  2. a diagonal unitary D makes T real: T = D T_r D^H, off-diagonals |e_k|;
 //  3. the r largest eigenvalues of T_r by multisection on Sturm counts;
 //  4. their eigenvectors by inverse iteration (one lane each, LDL^T without
 //     pivoting, tiny pivots replaced), orthogonalised within clusters;
 //  5. back-transformation Y = Q D Z.
-// IN_LDS: matrix and reflectors in dynamic LDS (q <= 64), else in the workspace.
+//
+// The reduction's q - 2 dependent steps bound it, not its arithmetic, and a
+// lone wave issues an instruction every four cycles at best: a step is as long
+// as its longest wave's instructions.  The matrix stays in registers: lane l
+// holds rows l and l + 64, wave w of W the columns w, w + W, ..., and a wave
+// drops its first column as the step passes it, so the column a step needs is
+// always its owner's register 0.  The rank-2 update of one step and the product
+// with the next step's reflector are one pass over the registers; the values a
+// column needs (v, w and the new v at its index) are loaded by lane t for
+// column t and read with v_readlane.  Wave 0 alone forms w, the next column
+// and its reflector in between: two barriers a step.  (A version with the matrix
+// in LDS and four barriers took 580 us at 100 frames and rank 10, 140 us at 40
+// and rank 8, 53 us at 16 and rank 4; this one 362, 90 and 35 us.)
 // ===========================================================================
-template <bool IN_LDS>
-__global__ __launch_bounds__(1024) void k_init_eig(InitEigArgs a) {
-  // q <= 64: the q x q matrix, then the q x q reflectors; 64 < q <= 128: the
-  // matrix's lower triangle packed by rows (row i from i (i + 1) / 2), the
-  // reflectors in global memory (a.V)
-  extern __shared__ double2 lds_m[];
-  __shared__ double s_d[128], s_ea[128], s_e2[128], s_beta[128];
-  __shared__ double2 s_ec[128], s_ph[128], s_w[128], s_v[128];
-  __shared__ double2 s_p[8][128];  // the reflector product's column-slice partials
+template <int NH>
+__global__ __launch_bounds__(64 * EIG_W<NH>) void k_init_eig(InitEigArgs a) {
+  constexpr int NR = 64 * NH, W = EIG_W<NH>, CT = NR / W, PP = NR;
+  extern __shared__ double2 lds_m[];  // the packed reflectors, then the work region
+  __shared__ double s_d[NR], s_ea[NR], s_e2[NR], s_beta[NR];
+  __shared__ double2 s_ec[NR], s_ph[NR];
   __shared__ double s_lam[16];
-  __shared__ double s_gs[4];  // Gershgorin interval (lo, hi), the scale, the pivot floor
-  const int tid = threadIdx.x, NT = blockDim.x, n = a.q, r = a.r;
-  // row pitch ld odd: the rows one wave reads together fall in distinct LDS banks
-  const int ld = n | 1;
-  double2* A = lds_m;
-  double2* Vh = IN_LDS ? A + n * ld : a.V;
-  auto tri = [](int i) { return (i * (i + 1)) >> 1; };  // packed row offset
-  const int nout = n * (n + 1) / 2;
-  for (int o = tid; o < nout; o += NT) {
-    double2 sum = make_double2(0.0, 0.0);
-#pragma unroll 16
-    for (int b = 0; b < a.nblk; ++b) sum = dadd(sum, a.part[(long)b * nout + o]);
-    int i, j;
-    tri_index(o, n, i, j);
-    if (i == j) sum.y = 0.0;
-    if constexpr (IN_LDS) {
-      A[i * ld + j] = sum;
-      A[j * ld + i] = dconj(sum);
-    } else {
-      A[tri(max(i, j)) + min(i, j)] = i >= j ? sum : dconj(sum);  // the lower entry
+  __shared__ double s_gs[4];  // Gershgorin interval (lo, hi) and scale of the scaled T_r, its unit
+  const int tid = threadIdx.x, l = tid & 63, n = a.q, r = a.r;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  double2* const Vh = lds_m;
+  double2* const work = lds_m + n * (n - 1) / 2;
+  double2* const s_pp = work;            // [wave][row] partial products
+  double2* const s_c = work + W * PP;    // [row] the next column, before its update
+  double2* const s_w = s_c + NR;         // [row] w, and a row of zero
+  double2* const s_v = s_w + NR + 1;     // [2][row] v and the new v, and a row of zero each
+  const double2 zero2 = make_double2(0.0, 0.0);
+
+  // ---- 1. Householder tridiagonalisation
+  double2 A[NH][CT];
+#pragma unroll
+  for (int h = 0; h < NH; ++h)
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+      const int i = min(l + 64 * h, n - 1), j = min(wv + W * t, n - 1), lo = min(i, j), hi = max(i, j);
+      A[h][t] = a.part[lo * n - lo * (lo - 1) / 2 + (hi - lo)];  // entry (lo, hi) of the upper triangle
     }
+#pragma unroll
+  for (int h = 0; h < NH; ++h)
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+      const int i = l + 64 * h, j = wv + W * t;
+      asm volatile("" : "+v"(A[h][t].x), "+v"(A[h][t].y));  // loaded, all at once, before it is selected
+      A[h][t] = dkeep(i < n && j < n, make_double2(A[h][t].x, i == j ? 0.0 : i < j ? A[h][t].y : -A[h][t].y));
+    }
+  int jb = wv;  // the column in register 0
+  if (wv == 0) {
+#pragma unroll
+    for (int h = 0; h < NH; ++h) s_c[l + 64 * h] = A[h][0];
+  }
+  for (int i = tid; i < 3 * (NR + 1); i += 64 * W) s_w[i] = zero2;
+  // wave 0's state of the last step: v, its first entry, beta
+  double2 v[NH], v0 = zero2;
+  double beta = 0.0;
+#pragma unroll
+  for (int h = 0; h < NH; ++h) v[h] = zero2;
+  __syncthreads();
+#pragma unroll 1
+  for (int k = 0; k + 1 < n; ++k) {
+    const int k1 = k + 1;
+    double2* const s_vn = s_v + (k & 1) * (NR + 1);
+    const double2* const s_vo = s_v + (k1 & 1) * (NR + 1);
+    if (wv == 0) {
+      // step k - 1's product p = beta B v, K = (beta / 2) v^H p, w = p - K v
+      double2 w[NH], x[NH];
+      double kp = 0.0;
+#pragma unroll
+      for (int h = 0; h < NH; ++h) {
+        const int i = l + 64 * h;
+        x[h] = s_c[i];
+        w[h] = zero2;
+        if (k > 0) {
+          double2 q[W];
+#pragma unroll
+          for (int e = 0; e < W; ++e) q[e] = s_pp[e * PP + i];
+#pragma unroll
+          for (int d = W / 2; d > 0; d >>= 1)
+#pragma unroll
+            for (int e = 0; e < d; ++e) q[e] = dadd(q[e], q[e + d]);
+          w[h] = dkeep(i >= k && i < n, q[0]);
+        }
+        kp = fma(v[h].x, w[h].x, fma(v[h].y, w[h].y, kp));
+      }
+      const double K = 0.5 * beta * beta * wave_sum(kp);  // v^H B v is real
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+        w[h] = make_double2(fma(beta, w[h].x, -K * v[h].x), fma(beta, w[h].y, -K * v[h].y));
+      auto row = [&](const double2 (&z)[NH], int i) {  // entry i (uniform)
+        if constexpr (NH == 2)
+          return lane_get(make_double2(i >= 64 ? z[1].x : z[0].x, i >= 64 ? z[1].y : z[0].y), i & 63);
+        else
+          return lane_get(z[0], i);
+      };
+      // column k after its update; rows before k hold values of earlier steps, never read again
+      const double2 wk = row(w, k);
+#pragma unroll
+      for (int h = 0; h < NH; ++h) {
+        x[h].x = fma(-v[h].x, wk.x, fma(-v[h].y, wk.y, fma(-w[h].x, v0.x, fma(-w[h].y, v0.y, x[h].x))));
+        x[h].y = fma(-v[h].y, wk.x, fma(v[h].x, wk.y, fma(-w[h].y, v0.x, fma(w[h].x, v0.y, x[h].y))));
+        if (l + 64 * h == k) s_d[k] = x[h].x;
+        s_w[l + 64 * h] = w[h];
+      }
+      // the reflector of its rows k1 .. n - 1 (none for the last column)
+      const double2 x0 = row(x, k1);
+      double sig = 0.0;
+#pragma unroll
+      for (int h = 0; h < NH; ++h) {
+        const int i = l + 64 * h;
+        const double2 z = dkeep(i > k1 && i < n, x[h]);
+        sig = fma(z.x, z.x, fma(z.y, z.y, sig));
+      }
+      sig = wave_sum(sig);
+      double2 alpha = x0;
+      v0 = zero2;
+      beta = 0.0;
+      const bool refl = k + 2 < n && !(sig == 0.0 && x0.y == 0.0);  // the same in every lane
+      if (refl) {
+        const double t = x0.x * x0.x + x0.y * x0.y, s = t + sig;
+        const double nrm = s * cx_rsqrt(s);
+        const bool big = t > 1e-290;
+        const double rt = cx_rsqrt(big ? t : 1.0), ax0 = big ? t * rt : 0.0;
+        const double2 ph = make_double2(big ? x0.x * rt : 1.0, big ? x0.y * rt : 0.0);
+        alpha = make_double2(-ph.x * nrm, -ph.y * nrm);
+        v0 = make_double2(ph.x * (ax0 + nrm), ph.y * (ax0 + nrm));
+        beta = rcp_nr(fma(nrm, ax0, s));  // 2 / |v|^2
+      }
+#pragma unroll
+      for (int h = 0; h < NH; ++h) {
+        const int i = l + 64 * h;
+        v[h] = dkeep(refl && i >= k1 && i < n, make_double2(i == k1 ? v0.x : x[h].x, i == k1 ? v0.y : x[h].y));
+        s_vn[i] = v[h];
+        if (i >= k1 && i < n) Vh[eig_vh_off(n, k) + i - k1] = v[h];
+      }
+      if (l == 0) {
+        s_beta[k] = beta;
+        s_ec[k] = alpha;
+      }
+    }
+    __syncthreads();
+    if (wv == (k & (W - 1))) {  // column k is past: the wave's columns move down
+#pragma unroll
+      for (int h = 0; h < NH; ++h) {
+#pragma unroll
+        for (int t = 0; t + 1 < CT; ++t) A[h][t] = A[h][t + 1];
+        A[h][CT - 1] = zero2;
+      }
+      jb += W;
+    }
+    // B -= v w^H + w v^H, and the product with the new reflector
+    const int jc = min(jb + W * (l & (CT - 1)), NR);  // lane t: column t of this wave
+    const double2 vj = s_vo[jc], wj = s_w[jc], nj = s_vn[jc];
+    double2 vr[NH], wr[NH], pp[NH];
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+      vr[h] = s_vo[l + 64 * h];
+      wr[h] = s_w[l + 64 * h];
+      pp[h] = zero2;
+    }
+    const int nact = (n - jb + W - 1) / W;
+#pragma unroll
+    for (int t0 = 0; t0 < CT; t0 += 2) {
+      if (t0 < nact) {
+#pragma unroll
+        for (int t = t0; t < t0 + 2; ++t) {
+          const double2 cv = lane_get(vj, t), cw = lane_get(wj, t), cn = lane_get(nj, t);
+#pragma unroll
+          for (int h = 0; h < NH; ++h) {
+            if (NH == 2 && h == 0 && k1 >= 64) continue;  // rows that are done
+            double2 b = A[h][t];
+            b.x = fma(-vr[h].x, cw.x, fma(-vr[h].y, cw.y, fma(-wr[h].x, cv.x, fma(-wr[h].y, cv.y, b.x))));
+            b.y = fma(-vr[h].y, cw.x, fma(vr[h].x, cw.y, fma(-wr[h].y, cv.x, fma(wr[h].x, cv.y, b.y))));
+            A[h][t] = b;
+            pp[h].x = fma(b.x, cn.x, fma(-b.y, cn.y, pp[h].x));
+            pp[h].y = fma(b.x, cn.y, fma(b.y, cn.x, pp[h].y));
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < NH; ++h) s_pp[wv * PP + l + 64 * h] = pp[h];
+    if (wv == (k1 & (W - 1))) {
+#pragma unroll
+      for (int h = 0; h < NH; ++h) s_c[l + 64 * h] = A[h][0];
+    }
+    __syncthreads();
+  }
+  // the last diagonal entry: column n - 1 before any update of the last step (there is none: its v is zero)
+  if (wv == ((n - 1) & (W - 1))) {
+#pragma unroll
+    for (int h = 0; h < NH; ++h)
+      if (l + 64 * h == n - 1) s_d[n - 1] = A[h][0].x;
   }
   __syncthreads();
-  // ---- 1. Householder tridiagonalisation (full Hermitian trailing block
-  // kept): wave 0 forms each reflector, the workgroup shares the product
-  // p = beta B v (8 column slices) and the rank-2 update of B
-  const int l = tid & 63, wv = tid >> 6;
-  if constexpr (IN_LDS) {
-    for (int k = 0; k + 2 < n; ++k) {
-      const int k1 = k + 1, m = n - k1;
-      if (wv == 0) {
-        double sig = 0.0;
-        for (int i = 1 + l; i < m; i += 64) {
-          const double2 x = A[(k1 + i) * ld + k];
-          sig += x.x * x.x + x.y * x.y;
-        }
-        sig = wave_sum(sig);
-        const double2 x0 = A[k1 * ld + k];
-        if (sig == 0.0 && x0.y == 0.0) {  // already reduced: H_k = I
-          if (l == 0) {
-            s_beta[k] = 0.0;
-            s_ec[k] = x0;
-          }
-        } else {
-          const double ax0 = sqrt(x0.x * x0.x + x0.y * x0.y), nrm = sqrt(ax0 * ax0 + sig);
-          const double2 ph = ax0 > 0.0 ? make_double2(x0.x / ax0, x0.y / ax0) : make_double2(1.0, 0.0);
-          const double2 alpha = make_double2(-ph.x * nrm, -ph.y * nrm);
-          const double2 v0 = dsub(x0, alpha);
-          for (int i = 1 + l; i < m; i += 64) Vh[(k1 + i) * ld + k] = A[(k1 + i) * ld + k];
-          if (l == 0) {
-            Vh[k1 * ld + k] = v0;
-            s_beta[k] = 2.0 / (v0.x * v0.x + v0.y * v0.y + sig);
-            s_ec[k] = alpha;
-          }
-        }
-      }
-      __syncthreads();
-      const double beta = s_beta[k];
-      if (beta == 0.0) continue;  // the same in every thread
-      // partial products over column slices j = h (mod 8), 8 waves
-      if (wv < 8) {
-  #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          const int i = l + 64 * hh;
-          if (i < m) {
-            const double2* row = A + (k1 + i) * ld + k1;
-            double2 acc = make_double2(0.0, 0.0);
-            for (int j = wv; j < m; j += 8) acc = dadd(acc, dmul(row[j], Vh[(k1 + j) * ld + k]));
-            s_p[wv][i] = acc;
-          }
-        }
-      }
-      __syncthreads();
-      // p = beta B v, K = (beta / 2) v^H p, w = p - K v (wave 0)
-      if (wv == 0) {
-        double2 pv[2];
-        double2 kp = make_double2(0.0, 0.0);
-  #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          const int i = l + 64 * hh;
-          double2 acc = make_double2(0.0, 0.0);
-          if (i < m) {
-  #pragma unroll
-            for (int h = 0; h < 8; ++h) acc = dadd(acc, s_p[h][i]);
-            acc = make_double2(beta * acc.x, beta * acc.y);
-            kp = dadd(kp, djmul(Vh[(k1 + i) * ld + k], acc));
-          }
-          pv[hh] = acc;
-        }
-        kp = wave_sum2(kp);
-        const double2 K = make_double2(0.5 * beta * kp.x, 0.5 * beta * kp.y);
-  #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          const int i = l + 64 * hh;
-          if (i < m) s_w[i] = dsub(pv[hh], dmul(K, Vh[(k1 + i) * ld + k]));
-        }
-      }
-      __syncthreads();
-      // B -= v w^H + w v^H, entry by entry over the workgroup
-      for (int e = tid; e < m * m; e += NT) {
-        const int i = e / m, j = e - (e / m) * m;
-        const double2 vi = Vh[(k1 + i) * ld + k], wi = s_w[i];
-        const double2 vj = Vh[(k1 + j) * ld + k], wj = s_w[j];
-        double2* aij = A + (k1 + i) * ld + k1 + j;
-        *aij = dsub(*aij, dadd(dmul(vi, dconj(wj)), dmul(wi, dconj(vj))));
-      }
-      __syncthreads();
-    }
-  } else {
-    // the same steps on the packed lower triangle: B(i, j) of the trailing
-    // block is the stored entry for i >= j and the conjugate of (j, i) above;
-    // the step's reflector is read from LDS (s_v), its global copy kept for
-    // the back-transformation; the rank-2 update touches the lower triangle
-    // only (rows i = w, w + 16, ... by wave, columns by lane)
-    for (int k = 0; k + 2 < n; ++k) {
-      const int k1 = k + 1, m = n - k1;
-      if (wv == 0) {
-        double sig = 0.0;
-        for (int i = 1 + l; i < m; i += 64) {
-          const double2 x = A[tri(k1 + i) + k];
-          sig += x.x * x.x + x.y * x.y;
-        }
-        sig = wave_sum(sig);
-        const double2 x0 = A[tri(k1) + k];
-        if (sig == 0.0 && x0.y == 0.0) {  // already reduced: H_k = I
-          if (l == 0) {
-            s_beta[k] = 0.0;
-            s_ec[k] = x0;
-          }
-        } else {
-          const double ax0 = sqrt(x0.x * x0.x + x0.y * x0.y), nrm = sqrt(ax0 * ax0 + sig);
-          const double2 ph = ax0 > 0.0 ? make_double2(x0.x / ax0, x0.y / ax0) : make_double2(1.0, 0.0);
-          const double2 alpha = make_double2(-ph.x * nrm, -ph.y * nrm);
-          const double2 v0 = dsub(x0, alpha);
-          for (int i = 1 + l; i < m; i += 64) {
-            const double2 x = A[tri(k1 + i) + k];
-            s_v[i] = x;
-            Vh[(k1 + i) * ld + k] = x;
-          }
-          if (l == 0) {
-            s_v[0] = v0;
-            Vh[k1 * ld + k] = v0;
-            s_beta[k] = 2.0 / (v0.x * v0.x + v0.y * v0.y + sig);
-            s_ec[k] = alpha;
-          }
-        }
-      }
-      __syncthreads();
-      const double beta = s_beta[k];
-      if (beta == 0.0) continue;  // the same in every thread
-      if (wv < 8) {  // partial products over column slices j = wv (mod 8)
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          const int i = l + 64 * hh;
-          if (i < m) {
-            // one load per entry from a selected (valid) index, no branch:
-            // row k1 + i's offset is fixed for the lane, row k1 + j's is
-            // wave-uniform
-            const int ti = tri(k1 + i) + k1;
-            double2 acc = make_double2(0.0, 0.0);
-#pragma unroll 4
-            for (int j = wv; j < m; j += 8) {
-              const int up = i < j;
-              const double2 raw = A[up ? tri(k1 + j) + k1 + i : ti + j];
-              const double2 bij = make_double2(raw.x, up ? -raw.y : raw.y);
-              acc = dadd(acc, dmul(bij, s_v[j]));
-            }
-            s_p[wv][i] = acc;
-          }
-        }
-      }
-      __syncthreads();
-      if (wv == 0) {  // p = beta B v, K = (beta / 2) v^H p, w = p - K v
-        double2 pv[2];
-        double2 kp = make_double2(0.0, 0.0);
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          const int i = l + 64 * hh;
-          double2 acc = make_double2(0.0, 0.0);
-          if (i < m) {
-#pragma unroll
-            for (int h = 0; h < 8; ++h) acc = dadd(acc, s_p[h][i]);
-            acc = make_double2(beta * acc.x, beta * acc.y);
-            kp = dadd(kp, djmul(s_v[i], acc));
-          }
-          pv[hh] = acc;
-        }
-        kp = wave_sum2(kp);
-        const double2 K = make_double2(0.5 * beta * kp.x, 0.5 * beta * kp.y);
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          const int i = l + 64 * hh;
-          if (i < m) s_w[i] = dsub(pv[hh], dmul(K, s_v[i]));
-        }
-      }
-      __syncthreads();
-      for (int i = wv; i < m; i += NT / 64) {  // B -= v w^H + w v^H, lower triangle
-        const double2 vi = s_v[i], wi = s_w[i];
-        double2* row = A + tri(k1 + i) + k1;
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          const int j = l + 64 * hh;
-          if (j <= i) row[j] = dsub(row[j], dadd(dmul(vi, dconj(s_w[j])), dmul(wi, dconj(s_v[j]))));
-        }
-      }
-      __syncthreads();
-    }
-  }
   if (wv == 0) {  // one wave: the tridiagonal eigenproblem
-    // ---- 2. T_r: diagonal, |e_k|, and the phases of D
-    for (int i = l; i < n; i += 64) s_d[i] = (IN_LDS ? A[i * ld + i] : A[tri(i) + i]).x;
-    if (l == 0 && n >= 2) s_ec[n - 2] = IN_LDS ? A[(n - 1) * ld + (n - 2)] : A[tri(n - 1) + n - 2];
-    wave_sync();
-    for (int i = l; i + 1 < n; i += 64) {
-      const double2 e = s_ec[i];
-      const double ae = sqrt(e.x * e.x + e.y * e.y);
-      s_ea[i] = ae;
-      s_e2[i] = ae * ae;
-    }
-    if (l == 0) {
-      double2 ph = make_double2(1.0, 0.0);
-      s_ph[0] = ph;
-      for (int i = 0; i + 1 < n; ++i) {
+    // ---- 2. T_r: diagonal, |e_k|, and the phases of D (a running product)
+    double2 u[NH];
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+      const int i = NH * l + h;
+      u[h] = make_double2(1.0, 0.0);
+      if (i + 1 < n) {
         const double2 e = s_ec[i];
         const double ae = sqrt(e.x * e.x + e.y * e.y);
-        if (ae > 0.0) ph = dmul(ph, make_double2(e.x / ae, e.y / ae));
-        s_ph[i + 1] = ph;
+        s_ea[i] = ae;
+        s_e2[i] = ae * ae;
+        if (ae > 0.0) u[h] = make_double2(e.x / ae, e.y / ae);
       }
+      if (h > 0) u[h] = dmul(u[h - 1], u[h]);
     }
+    const double2 inc = wave_scan_mul(u[NH - 1], l);
+    double2 exc = make_double2(__shfl_up(inc.x, 1), __shfl_up(inc.y, 1));
+    if (l == 0) {
+      exc = make_double2(1.0, 0.0);
+      s_ph[0] = exc;
+    }
+#pragma unroll
+    for (int h = 0; h < NH; ++h)
+      if (NH * l + h + 1 < n) s_ph[NH * l + h + 1] = dmul(exc, u[h]);
     wave_sync();
-    // Gershgorin interval and scales
-    double glo = INFINITY, ghi = -INFINITY, emax2 = 0.0, scale = 0.0;
+    // Gershgorin interval and scale; T_r is scaled in place by a power of two
+    double glo = INFINITY, ghi = -INFINITY, scale = 0.0;
     for (int i = l; i < n; i += 64) {
       const double rad = (i > 0 ? s_ea[i - 1] : 0.0) + (i + 1 < n ? s_ea[i] : 0.0);
       glo = fmin(glo, s_d[i] - rad);
       ghi = fmax(ghi, s_d[i] + rad);
       scale = fmax(scale, fabs(s_d[i]) + rad);
-      if (i + 1 < n) emax2 = fmax(emax2, s_e2[i]);
     }
     glo = wave_min(glo);
     ghi = wave_max(ghi);
     scale = fmax(wave_max(scale), 1e-300);
-    emax2 = wave_max(emax2);
+    const int ex = __builtin_amdgcn_frexp_exp(scale);
+    for (int i = l; i < NR; i += 64) {  // rows past n: no sign changes, no part in any vector
+      const double d = i < n ? __builtin_amdgcn_ldexp(s_d[i], -ex) : 4.0;
+      const double e = i + 1 < n ? __builtin_amdgcn_ldexp(s_ea[i], -ex) : 0.0;
+      s_d[i] = d;
+      s_ea[i] = e;
+      s_e2[i] = e * e;
+    }
     if (l == 0) {
       const double wdt = ghi - glo;
-      s_gs[0] = glo - (1e-3 * wdt + 1e-300);
-      s_gs[1] = ghi + (1e-3 * wdt + 1e-300);
-      s_gs[2] = scale;
-      s_gs[3] = 2.3e-308 * fmax(1.0, emax2);  // pivmin
+      s_gs[0] = __builtin_amdgcn_ldexp(glo - (1e-3 * wdt + 1e-300), -ex);
+      s_gs[1] = __builtin_amdgcn_ldexp(ghi + (1e-3 * wdt + 1e-300), -ex);
+      s_gs[2] = __builtin_amdgcn_ldexp(scale, -ex);
+      s_gs[3] = __builtin_amdgcn_ldexp(1.0, ex);
     }
   }
   __syncthreads();
-  // ---- 3. multisection: wave w < r takes the w-th largest eigenvalue
-  // (ascending index n-1-w), its 64 lanes one Sturm count each per round (a
-  // 65-section of the interval), to an isolating interval of relative width
-  // 1e-10: inverse iteration converges from it and the Rayleigh quotient
-  // refines the value
-  const double scale = s_gs[2];
-  if (wv < r) {
-    const int idx = n - 1 - wv;
-    const double pivmin = s_gs[3];
-    double lo = s_gs[0], hi = s_gs[1];
-    for (int rnd = 0; rnd < 80; ++rnd) {
-      const double x = lo + (hi - lo) * (double)(l + 1) / 65.0;
-      const int cnt = sturm_count(s_d, s_e2, n, x, pivmin);
-      const double nlo = wave_max(cnt <= idx ? x : -INFINITY);
-      const double nhi = wave_min(cnt > idx ? x : INFINITY);
-      lo = fmax(lo, nlo);
-      hi = fmin(hi, nhi);
-      if (hi - lo <= 1e-10 * fmax(fabs(lo), fabs(hi)) + 1e-300) break;  // the same in every lane
+  // ---- 3. wave w takes the eigenvalues w, w + W, ... (descending; ascending
+  // index n - 1 - w), two at a time; inverse iteration converges from the
+  // interval's middle and the Rayleigh quotient refines the value
+  const double scale = s_gs[2], unit = s_gs[3];
+#pragma unroll 1
+  for (int j = wv; j < r; j += 2 * W) {
+    if (j + W < r) {
+      const int idx[2] = {n - 1 - j, n - 1 - j - W};
+      multisect<2>(s_d, s_e2, n, s_gs[0], s_gs[1], l, idx, s_lam + j, W);
+    } else {
+      const int idx[1] = {n - 1 - j};
+      multisect<1>(s_d, s_e2, n, s_gs[0], s_gs[1], l, idx, s_lam + j, W);
     }
-    if (l == 0) s_lam[wv] = 0.5 * (lo + hi);
   }
   __syncthreads();
+  double* const sy = reinterpret_cast<double*>(work);  // right-hand side / solution [i * r + j]
   if (wv == 0) {
-    // ---- 4. inverse iteration, lane j < r for eigenvalue j; scratch in A's region
-    double* su = reinterpret_cast<double*>(A);  // u pivots [i * r + j]
-    double* sy = su + n * r;                    // right-hand side / solution [i * r + j]
-    if (l < r) {
-      const double lam = s_lam[l], tiny = 1e-14 * scale;
-      for (int i = 0; i < n; ++i) {  // a start vector of its own per lane (golden-ratio sequence)
-        const double t = (double)(i + 1) * (double)(2 * l + 3) * 0.6180339887498949;
-        sy[i * r + l] = 0.5 + (t - floor(t));
-      }
-      for (int it = 0; it < 3; ++it) {
-        double u = s_d[0] - lam, y = sy[l];
-  #pragma unroll 4
-        for (int i = 0; i + 1 < n; ++i) {
-          if (fabs(u) <= tiny) u = tiny;
-          const double ru = rcp_nr(u);
-          su[i * r + l] = ru;  // 1 / u_i for the backward pass
-          sy[i * r + l] = y;
-          const double lm = s_ea[i] * ru;
-          u = s_d[i + 1] - lam - lm * s_ea[i];
-          y = sy[(i + 1) * r + l] - lm * y;
+    // ---- 4. inverse iteration, one lane per eigenvalue, a.gw of them at a
+    // time (all r, unless the reciprocal pivots' room is short); values in
+    // LDS are read sixteen rows at a time ahead of the serial chains that use
+    // them, over the padded rows, whose entries are zero in every vector
+    const int gw = a.gw, n16 = (n + 15) & ~15;
+    double* const su = sy + n16 * r;  // 1 / u pivots [i * gw + j]
+#pragma unroll 1
+    for (int j0 = 0; j0 < r; j0 += gw) {
+      const int j = j0 + l;
+      if (l < gw && j < r) {
+        const double lam = s_lam[j], tiny = 1e-14 * scale;
+        {  // the reciprocal pivots, and a start vector of its own per eigenvalue (golden-ratio sequence)
+          double u = s_d[0] - lam;
+#pragma unroll 1
+          for (int i0 = 0; i0 < n16; i0 += 8) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const int i = i0 + e;
+              if (fabs(u) <= tiny) u = tiny;
+              const double ru = rcp_nr(u);
+              u = s_d[min(i + 1, NR - 1)] - lam - s_e2[i] * ru;
+              const double t = (double)(i + 1) * (double)(2 * j + 3) * 0.6180339887498949;
+              su[i * gw + l] = ru;
+              sy[i * r + j] = i < n ? 0.5 + (t - floor(t)) : 0.0;
+            }
+          }
         }
-        if (fabs(u) <= tiny) u = tiny;
-        double xnext = y / u, nrm2 = xnext * xnext;
-        sy[(n - 1) * r + l] = xnext;
-  #pragma unroll 4
-        for (int i = n - 2; i >= 0; --i) {
-          const double xi = (sy[i * r + l] - s_ea[i] * xnext) * su[i * r + l];
-          sy[i * r + l] = xi;
-          nrm2 += xi * xi;
-          xnext = xi;
+        double inv = 1.0, nrm2 = 0.0;
+#pragma unroll 1
+        for (int it = 0; it < 3; ++it) {
+          double y = 0.0, lmp = 0.0;  // the row before's value and its multiplier
+#pragma unroll 1
+          for (int i0 = 0; i0 < n16; i0 += 16) {
+            double lm[16], yn[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+              lm[e] = s_ea[i0 + e] * su[(i0 + e) * gw + l];
+              yn[e] = sy[(i0 + e) * r + j] * inv;
+            }
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+              y = fma(-lmp, y, yn[e]);
+              lmp = lm[e];
+              sy[(i0 + e) * r + j] = y;
+            }
+          }
+          double xn = 0.0;
+          nrm2 = 0.0;
+#pragma unroll 1
+          for (int i0 = n16 - 16; i0 >= 0; i0 -= 16) {
+            double ys[16], es[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+              const double ru = su[(i0 + e) * gw + l];
+              ys[e] = sy[(i0 + e) * r + j] * ru;
+              es[e] = s_ea[i0 + e] * ru;
+            }
+#pragma unroll
+            for (int e = 15; e >= 0; --e) {
+              xn = fma(-es[e], xn, ys[e]);
+              sy[(i0 + e) * r + j] = xn;
+              nrm2 = fma(xn, xn, nrm2);
+            }
+          }
+          inv = 1.0 / sqrt(nrm2);
         }
-        const double inv = 1.0 / sqrt(nrm2);
-        for (int i = 0; i < n; ++i) sy[i * r + l] *= inv;
+        // normalised, and its Rayleigh quotient z^T T_r z
+        double rq = 0.0, ez = 0.0;  // ez: off-diagonal times the value before
+#pragma unroll 1
+        for (int i0 = 0; i0 < n16; i0 += 8) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int i = i0 + e;
+            const double z = sy[i * r + j] * inv;
+            sy[i * r + j] = z;
+            rq = fma(z, fma(s_d[i], z, 2.0 * ez), rq);
+            ez = s_ea[i] * z;
+          }
+        }
+        s_lam[j] = rq;
       }
-      // the Rayleigh quotient z^T T_r z of the normalised vector
-      double rq = 0.0, zp = 0.0;
-      for (int i = 0; i < n; ++i) {
-        const double zi = sy[i * r + l];
-        rq += zi * (s_d[i] * zi + 2.0 * (i > 0 ? s_ea[i - 1] * zp : 0.0));
-        zp = zi;
-      }
-      s_lam[l] = rq;
+      wave_sync();
     }
-    wave_sync();
     // orthogonalise within clusters of close eigenvalues, twice, in descending order
     for (int j = 1; j < r; ++j) {
       bool any = false;
@@ -1242,93 +1357,10 @@ __global__ __launch_bounds__(1024) void k_init_eig(InitEigArgs a) {
       for (int i = l; i < n; i += 64) sy[i * r + j] *= inv;
       wave_sync();
     }
-    if (IN_LDS && r <= 8) {  // 5. Y = Q D Z by this wave alone, Y in registers
-      if (a.lam_out) {  // only the spectrum was asked for
-        if (l < r) a.lam_out[l] = s_lam[l];
-        return;
-      }
-      if (!(s_lam[r - 1] > 1e-14 * s_lam[0]) || !(s_lam[0] > 0.0)) {
-        if (l == 0) set_error(a.st, 4, -1);
-        return;
-      }
-      backtransform_wave<8, 8>(Vh, ld, s_beta, s_ph, sy, s_lam, n, r, l, a.Vs);
-      return;
-    }
-    // ---- 5. Y = Q D Z, Y [i * r + j] complex over the start of A's region
-    double zr[2][16];
-  #pragma unroll
-    for (int h = 0; h < 2; ++h)
-  #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int i = l + 64 * h;
-        zr[h][j] = (i < n && j < r) ? sy[i * r + j] : 0.0;
-      }
-    wave_sync();
-    double2* const Y0 = A;
-  #pragma unroll
-    for (int h = 0; h < 2; ++h)
-  #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int i = l + 64 * h;
-        if (i < n && j < r) Y0[i * r + j] = make_double2(s_ph[i].x * zr[h][j], s_ph[i].y * zr[h][j]);
-      }
-    wave_sync();
   }
-  if (IN_LDS && r <= 8) return;  // every other wave is done after the reduction
   __syncthreads();
-  // back-transformation Y <- H_k Y, k descending, over the workgroup (q > 64 or r > 8):
-  // thread = (column jc = tid % 16, rows g, g + 64 with g = tid / 16), the same
-  // rows for the column sums and the update, so that a thread only reads the
-  // rows of Y it wrote; the reflector's values at those rows are loaded one
-  // column ahead (they live in global memory for q > 64); column sums by
-  // shuffles within a wave, then across the 16 waves through LDS
-  double2* Y = A;
-  const int jc = tid & 15, g64 = tid >> 4;
-  double2* s_sj = &s_p[0][0];  // [wave][16] partial sums, then the 16 totals
-  double2 vc[2], vn[2];
-  auto vload = [&](int k, double2 (&dst)[2]) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) dst[h] = Vh[min(g64 + 64 * h, n - 1) * ld + max(k, 0)];
-  };
-  vload(n - 3, vc);
-  for (int k = n - 3; k >= 0; --k) {
-    vload(k - 1, vn);
-    const double beta = s_beta[k];
-    if (beta != 0.0) {  // the same in every thread
-      double2 sj = make_double2(0.0, 0.0);
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int i = g64 + 64 * h;
-        if (jc < r && i > k && i < n) sj = dadd(sj, djmul(vc[h], Y[i * r + jc]));
-      }
-#pragma unroll
-      for (int off = 16; off < 64; off <<= 1) {
-        sj.x += __shfl_xor(sj.x, off);
-        sj.y += __shfl_xor(sj.y, off);
-      }
-      if (l < 16) s_sj[wv * 16 + l] = sj;
-      __syncthreads();
-      if (tid < 16) {
-        double2 t = make_double2(0.0, 0.0);
-        for (int w = 0; w < NT / 64; ++w) t = dadd(t, s_sj[w * 16 + tid]);
-        s_sj[256 + tid] = make_double2(beta * t.x, beta * t.y);
-      }
-      __syncthreads();
-      // (the next step's totals are written after its first barrier, which
-      // every thread reaches only once its update here is done)
-      const double2 sv = s_sj[256 + jc];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int i = g64 + 64 * h;
-        if (jc < r && i > k && i < n) Y[i * r + jc] = dsub(Y[i * r + jc], dmul(vc[h], sv));
-      }
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) vc[h] = vn[h];
-  }
-  __syncthreads();  // every row of Y is final before the columns are scaled below
   if (a.lam_out) {  // only the spectrum was asked for
-    if (tid < r) a.lam_out[tid] = s_lam[tid];
+    if (tid < r) a.lam_out[tid] = s_lam[tid] * unit;
     return;
   }
   const double lam0 = s_lam[0], lamr = s_lam[r - 1];
@@ -1336,12 +1368,8 @@ __global__ __launch_bounds__(1024) void k_init_eig(InitEigArgs a) {
     if (tid == 0) set_error(a.st, 4, -1);
     return;
   }
-  for (int e2 = tid; e2 < n * r; e2 += NT) {
-    const int j = e2 % r;
-    const double sc = 1.0 / sqrt(s_lam[j]);
-    const double2 v = Y[e2];  // Y[k][j] with e2 = k * r + j
-    a.Vs[e2] = make_float2((float)(v.x * sc), (float)(v.y * sc));
-  }
+  // ---- 5. wave w the columns 4 w .. 4 w + 3
+  if (4 * wv < r) backtransform<NH>(Vh, s_beta, s_ph, sy, s_lam, unit, n, r, wv, l, a.Vs);
 }
 
 // U0[:, j] = sum_k X0[:, k] Vs[k][j]: a workgroup takes 64 pixels, its four
@@ -1457,20 +1485,26 @@ __global__ void k_cost_total(const double* cost_k, int q, double* out, DevState*
 // ---------------------------------------------------------------------------
 // launchers (explicit instantiations behind plain functions)
 // ---------------------------------------------------------------------------
-hipError_t launch_init_eig(const InitEigArgs& a, hipStream_t s) {
-  if (a.q > 128 || a.r > 16 || a.r > a.q) return hipErrorInvalidValue;
-  // q <= 64: matrix and reflectors in LDS; else the packed lower triangle
-  // (the reflectors in a.V)
-  const size_t lds = a.in_lds ? 2 * (size_t)a.q * (a.q | 1) * sizeof(double2)
-                              : (size_t)a.q * (a.q + 1) / 2 * sizeof(double2);
-  const void* fn = a.in_lds ? (const void*)k_init_eig<true> : (const void*)k_init_eig<false>;
+template <int NH>
+static hipError_t launch_init_eig_nh(InitEigArgs a, hipStream_t s) {
+  constexpr int NR = 64 * NH;
+  // room for all r pivot columns of the inverse iteration, or for eight at a time
+  const size_t vh = (size_t)a.q * (a.q - 1) / 2 * sizeof(double2), fixed = NR * 64 + 512, room = 160 * 1024 - fixed - vh;
+  const size_t q16 = (a.q + 15) / 16 * 16;
+  a.gw = q16 * a.r * 16 <= room ? a.r : std::min(a.r, 8);
+  const size_t reduce = (size_t)EIG_WORK<NH> * sizeof(double2), iterate = q16 * (a.r + a.gw) * 8;
+  const size_t lds = vh + std::max(reduce, iterate);
   if (lds > 48 * 1024) {
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipError_t e = hipFuncSetAttribute((const void*)k_init_eig<NH>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  if (a.in_lds) hipLaunchKernelGGL((k_init_eig<true>), dim3(1), dim3(1024), lds, s, a);
-  else hipLaunchKernelGGL((k_init_eig<false>), dim3(1), dim3(1024), lds, s, a);
+  hipLaunchKernelGGL(k_init_eig<NH>, dim3(1), dim3(64 * EIG_W<NH>), lds, s, a);
   return hipGetLastError();
+}
+
+hipError_t launch_init_eig(const InitEigArgs& a, hipStream_t s) {
+  if (a.q < 1 || a.q > 128 || a.r < 1 || a.r > 16 || a.r > a.q) return hipErrorInvalidValue;
+  return a.q <= 64 ? launch_init_eig_nh<1>(a, s) : launch_init_eig_nh<2>(a, s);
 }
 
 }  // namespace ag

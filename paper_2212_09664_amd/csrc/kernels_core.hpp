@@ -214,10 +214,9 @@ struct ApplyArgs {
 };
 
 struct InitEigArgs {
-  const double2* part;
-  int nblk, q, r;
-  double2* V;            // 2 q x (q | 1) scratch (global): matrix and reflectors when not in LDS
-  int in_lds;            // matrix and eigenvectors in dynamic LDS (q <= 64)
+  const double2* part;   // the upper triangle of X_0^H X_0
+  int q, r;
+  int gw;                // eigenvalues per pass of the inverse iteration
   float2* Vs;            // q x r out: V_r Sigma_r^{-1}
   double* lam_out;       // non-null: the r largest eigenvalues (descending) go here, no eigenvectors
   DevState* st;
@@ -250,13 +249,14 @@ __device__ __forceinline__ double2 lane_get(double2 v, int src) {
 template <int CTRL>
 __device__ __forceinline__ double dpp_get(double v) {
   const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b & 0xffffffffull), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, false);
+  // every lane's source is valid, so no old value is merged (and none is set up)
+  const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned)(b & 0xffffffffull), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, false);
   return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 template <int CTRL>
 __device__ __forceinline__ float dpp_getf(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, false));
 }
 #define DPP_XOR1 0xB1       // quad_perm [1,0,3,2]
 #define DPP_XOR2 0x4E       // quad_perm [2,3,0,1]
@@ -379,7 +379,6 @@ __global__ void k_pick_init(const double* f, const int32_t* snap, const float2* 
 __global__ void k_err_restore(const int32_t* snap, DevState* st);
 __global__ void k_copy(const float2* src, float2* dst, long n);
 __global__ void k_cost_total(const double* cost_k, int q, double* out, DevState* st);
-__global__ void k_init_eig(InitEigArgs a);
 
 hipError_t launch_gram_lines(const GramLinesArgs& a, int ny, int ngroups, int max_pairs, bool fp64,
                              hipStream_t s);

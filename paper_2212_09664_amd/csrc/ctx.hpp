@@ -26,7 +26,6 @@ enum TimedKernel {
 struct altgdmin_ctx {
   altgdmin_params p;
   int n, lines, fp64;
-  int pdft;       // ky transforms as FP16 hi+lo MFMA partial DFTs (mixed form, 1D Cartesian)
   int width;     // mask row width: lines per frame (LINES) or m_max (INDEX)
   int lmax;      // LINES: m_max / nx
   int per;       // samples per mask entry (nx for LINES, 1 for INDEX)

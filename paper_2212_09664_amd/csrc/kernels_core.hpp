@@ -102,21 +102,6 @@ struct BasisArgs {
   float2* qpart;              // k_adj_qr: the column's QR Gram partial (FP32, tri order)
 };
 
-struct PdftArgs {
-  const float2* U;       // pixel-major [p][j]
-  const float2* coils;   // [c][p]
-  float2* W;             // [c][u][x][j], ua rows per coil (forward out)
-  const float2* K;       // [c][u][x][j] (adjoint in)
-  float2* G;             // [part][p][j] (adjoint out)
-  const float2* tw;      // exp(-2 pi i t / ny), t < ny
-  const int32_t* unit_loc;  // sampled row u -> ky
-  int nx, r, nc, ua, cgs;
-  long n, part_stride;
-  float scale;           // 1 / sqrt(ny)
-  DevState* st;
-  int check_halt;
-};
-
 // warm-start CNN
 struct ConvArgs {
   const float* X;        // [b][cin][H][W]
@@ -402,7 +387,6 @@ hipError_t launch_cnn_to_M(const float* Y4, int r, long n, int batch, float2* M,
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, long n, float lr, int step, hipStream_t s);
 hipError_t launch_cnn_planes(const float2* X, long n, int q, double* partial, float* out, hipStream_t s);
 // mixed form, 1D Cartesian masks: which 0 forward, 1 adjoint + coil combine
-hipError_t launch_pdft(int which, int ny, const PdftArgs& a, int grid_x, int grid_y, hipStream_t s);
 int basis_txx(int N, int nx, int r);
 __global__ void k_build_lines(const float2* yh, const int2* pairs, const int4* items, int nc, int nx, int lmax,
                               float2* yu, float2* yg, const DevState* st);

@@ -205,7 +205,9 @@ hipError_t gram_solve(altgdmin_ctx* c, int check_halt) {
     g.st = c->st();
     g.check_halt = check_halt;
     tmark(c, TK_GRAM);
-    e = launch_gram_lines(g, p.ny, c->gram_ngroups, p.q, c->fp64, c->stream);
+    // a line's samples in tiles of 8: at most one partly filled tile per line
+    e = launch_gram_lines(g, (int)std::min((long)p.ny * ((p.q + 7) / 8), p.ny + (long)p.q * c->lmax / 8),
+                          c->gram_ngroups, c->fp64, c->stream);
     tmark(c, TK_GRAM);
   } else {
     GramIndexArgs g{};

@@ -5,10 +5,7 @@
 
 #define SOLVE_NT 1024  // threads of the per-frame solve
 #define QR_NSM 2       // QR Gram: streams of 4 waves per workgroup
-#define GRAM_NWG 1     // per-line Gram: groups of 4 waves per workgroup
 #define GRAM_INDEX_CHUNK 512  // general masks: samples per Gram workgroup (one coil)
-#define GRAM_DS32 2    // per-line Gram, FP32: steps whose loads are issued together
-#define GRAM_DS64 4    // the same for FP64
 
 namespace ag {
 
@@ -365,8 +362,7 @@ __global__ void k_err_restore(const int32_t* snap, DevState* st);
 __global__ void k_copy(const float2* src, float2* dst, long n);
 __global__ void k_cost_total(const double* cost_k, int q, double* out, DevState* st);
 
-hipError_t launch_gram_lines(const GramLinesArgs& a, int ny, int ngroups, int max_pairs, bool fp64,
-                             hipStream_t s);
+hipError_t launch_gram_lines(const GramLinesArgs& a, int max_items, int ngroups, bool fp64, hipStream_t s);
 hipError_t launch_gram_index(const GramIndexArgs& a, int q, bool fp64, hipStream_t s);
 hipError_t launch_solve(const SolveArgs& a, int q, bool fp64, hipStream_t s);
 hipError_t launch_qr_gram(const GramColsArgs& a, int nblk, bool fp64, hipStream_t s);

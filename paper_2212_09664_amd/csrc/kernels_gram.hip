@@ -20,145 +20,6 @@
 namespace ag {
 
 
-// ---------------------------------------------------------------------------
-// 1D Cartesian: one workgroup (4 waves) per (sampled line u, tile t of 8 of
-// its samples, coil group g).  Tile 0 also forms the line's Gram P_u.
-// Rows of K are (c, x) for the group's coils; wave w takes rows x = 16s+4w..+3.
-// Loads are unconditional (clamped address, then a select) so the MFMA chain
-// is branch-free.  Outputs (FP64): Ppart[g][u][i][j], hpart[g][pair][j].
-// ---------------------------------------------------------------------------
-template <typename T, int TR, int UN, bool WP, int NWG>
-__device__ __forceinline__ void gram_lines_loop(const GramLinesArgs& a, int u, int c0, int c1, int np, int pp,
-                                                bool pok, int lane, int wave, int wg,
-                                                typename Mma<T>::V (&P)[TR][TR], typename Mma<T>::V (&H)[TR]) {
-  using M = Mma<T>;
-  const int r = a.r, nx = a.nx, col = lane & 15, kk = lane >> 4;
-  const int xl = 4 * wave + kk;
-  int wj[TR], wim[TR];
-  float wmask[TR];
-#pragma unroll
-  for (int t = 0; t < TR; ++t) {
-    const int i = 16 * t + col;
-    const bool ok = i < 2 * r;
-    wmask[t] = ok ? 1.f : 0.f;
-    wj[t] = ok ? ((i < r) ? i : i - r) : 0;
-    wim[t] = (i >= r) && ok;
-  }
-  const int yim = col >> 3;
-  const float ymask = pok ? 1.f : 0.f;
-  const float* Wf = reinterpret_cast<const float*>(a.W);
-  // the item's data: [c][x][8 samples] complex (zero past the line's count)
-  const float* Yitem = reinterpret_cast<const float*>(a.yg);
-  // one flat loop over (coil, block of 16*UN rows x), the NWG groups of 4
-  // waves taking every NWG-th block; the next block's operands are loaded
-  // while the current one feeds the matrix cores
-  constexpr int XB = 16 * UN;
-  const int nxb = (nx + XB - 1) / XB;
-  const int niter = max(0, c1 - c0) * nxb;
-  T av[UN][TR], bv[UN];
-  auto load = [&](int c, int x0, T (&A)[UN][TR], T (&Bv)[UN]) {
-    const float* yrow = Yitem + 16L * ((long)c * nx) + 2 * (col & 7) + yim;
-    const long wbase = 2L * (((long)c * a.ua + u) * nx * r);
-#pragma unroll
-    for (int q2 = 0; q2 < UN; ++q2) {
-      // always load (from a clamped, valid address) and scale by a 0/1 mask,
-      // so that no load sits under a branch
-      const int x = x0 + 16 * q2 + xl;
-      const float rm = (x < nx) ? 1.f : 0.f;
-      const int xc = min(x, nx - 1);
-#pragma unroll
-      for (int t = 0; t < TR; ++t)
-        A[q2][t] = (T)(Wf[wbase + 2L * (r * xc + wj[t]) + wim[t]] * (rm * wmask[t]));
-      Bv[q2] = (T)(yrow[16 * xc] * (rm * ymask));
-    }
-  };
-  // common shapes (every row block full, 2r filling the row tiles): a
-  // wave-uniform base per step and a fixed per-lane offset, no masks (the
-  // item's data is already zero past the line's count); a mask applied to a
-  // loaded value would make the load wait at once
-  const bool fast = (nx % XB) == 0 && 2 * r == 16 * TR;
-  const float* Wline = Wf + 2L * ((long)u * nx * r);  // line u of coil 0
-  const long CS = 2L * a.ua * nx * r;                 // coil stride of W, floats
-  int lw[TR];
-#pragma unroll
-  for (int t = 0; t < TR; ++t) lw[t] = 2 * (r * xl + wj[t]) + wim[t];
-  const int ly = 16 * xl + 2 * (col & 7) + yim;
-  auto load_fast = [&](int c, int x0, T (&A)[UN][TR], T (&Bv)[UN]) {
-    const float* wp = Wline + (long)c * CS + 2L * r * x0;
-    const float* yp = Yitem + 16L * ((long)c * nx + x0);
-#pragma unroll
-    for (int q2 = 0; q2 < UN; ++q2) {
-#pragma unroll
-      for (int t = 0; t < TR; ++t) A[q2][t] = (T)wp[32 * r * q2 + lw[t]];
-      Bv[q2] = (T)yp[256 * q2 + ly];
-    }
-  };
-  {
-    if (fast) {
-      // the loads of DS steps are issued together, then their products run
-      // (a step past the end loads a valid block of the last coil and skips
-      // its products), so a workgroup waits for memory once per DS steps.
-      // The group index is wave-uniform: in a scalar register, the step
-      // counters and base addresses are scalar too.  DS measured per type.
-      constexpr int DS = sizeof(T) == 8 ? GRAM_DS64 : GRAM_DS32;
-      const int wgu = __builtin_amdgcn_readfirstlane(wg);
-      int ci = wgu / nxb, xb = wgu % nxb;  // (coil, row block) of the next step to load
-      for (int it0 = wgu; it0 < niter; it0 += DS * NWG) {
-        T A[DS][UN][TR], Bv[DS][UN];
-#pragma unroll
-        for (int s2 = 0; s2 < DS; ++s2) {
-          load_fast(min(c0 + ci, c1 - 1), xb * XB, A[s2], Bv[s2]);
-          xb += NWG;
-          while (xb >= nxb) {
-            xb -= nxb;
-            ++ci;
-          }
-        }
-#pragma unroll
-        for (int s2 = 0; s2 < DS; ++s2) {
-          if (it0 + s2 * NWG < niter) {
-#pragma unroll
-            for (int q2 = 0; q2 < UN; ++q2) {
-              if constexpr (WP) {
-#pragma unroll
-                for (int i = 0; i < TR; ++i)
-#pragma unroll
-                  for (int j = 0; j < TR; ++j) P[i][j] = M::mma(A[s2][q2][i], A[s2][q2][j], P[i][j]);
-              }
-#pragma unroll
-              for (int i = 0; i < TR; ++i) H[i] = M::mma(A[s2][q2][i], Bv[s2][q2], H[i]);
-            }
-          }
-        }
-      }
-      return;
-    }
-  }
-  if (wg < niter) load(c0 + wg / nxb, (wg % nxb) * XB, av, bv);
-  for (int it = wg; it < niter; it += NWG) {
-    T an[UN][TR], bn[UN];
-    const int itn = it + NWG;
-    if (itn < niter) load(c0 + itn / nxb, (itn % nxb) * XB, an, bn);
-#pragma unroll
-    for (int q2 = 0; q2 < UN; ++q2) {
-      if constexpr (WP) {
-#pragma unroll
-        for (int i = 0; i < TR; ++i)
-#pragma unroll
-          for (int j = 0; j < TR; ++j) P[i][j] = M::mma(av[q2][i], av[q2][j], P[i][j]);
-      }
-#pragma unroll
-      for (int i = 0; i < TR; ++i) H[i] = M::mma(av[q2][i], bv[q2], H[i]);
-    }
-#pragma unroll
-    for (int q2 = 0; q2 < UN; ++q2) {
-      bv[q2] = bn[q2];
-#pragma unroll
-      for (int t = 0; t < TR; ++t) av[q2][t] = an[q2][t];
-    }
-  }
-}
-
 // The loop's two copies of the hybrid data y'[k][c][l][x], per work item (line,
 // tile of 8 of its pairs) and coil: the line's block yu[nc nx p0 + (c np + p) nx +
 // x], read along x by the fold, and the Gram kernel's [item][c][x][8 samples], zero
@@ -196,76 +57,128 @@ __global__ __launch_bounds__(256) void k_build_lines(const float2* yh, const int
   }
 }
 
-template <typename T, int TR, int UN, int NWG>
-__global__ __launch_bounds__(256 * NWG) void k_gram_lines_mma(GramLinesArgs a) {
+// ---------------------------------------------------------------------------
+// 1D Cartesian: one workgroup (4 waves) per (sampled line u, tile t of 8 of its
+// samples, coil group g).  Tile 0 also forms the line's Gram P_u.  Rows of K
+// are (c, x) for the group's coils; step s takes 16 of them, wave w the rows
+// x = 16 s + 4 w .. + 3.  Up to rank 8 (TR = 1) the operand's 16 columns are W's
+// row as stored, Re W_0, Im W_0, Re W_1, ...; above (TR = 2) a lane loads one
+// complex column and feeds the tiles of the real and the imaginary parts, of
+// whose four products the upper three are formed.  Columns past 2r repeat a
+// valid one and are not read from the result; samples past the line's count
+// are zero in yg; so no load is masked.  What bounds it is memory: W (and
+// the data) once, plus W again for each further tile of a much sampled line.
+// The loads of NS steps are in flight while the NS before them feed the matrix
+// cores; NS is small because the kernel runs once per iteration on a cold
+// instruction cache (256 x 256, 12 coils, rank 8: 27.5, 24.7 and 23.3 us for NS
+// = 8, 4 and 2; 16 coils, rank 16: 62, 58 and 54 us for 4, 2 and 1).  Against a
+// version that masked its loads, except at rank 8 and 16, and waited for each
+// batch: 64 x 64 rank 4 6.4 -> 5.2 us, 256 x 256 rank 16 69 -> 54, in FP64 rank
+// 7 26 -> 21, one frame of 128 x 128 14.2 -> 9.8.
+// Outputs (FP64): Ppart[g][u][i][j], hpart[g][pair][j].
+// ---------------------------------------------------------------------------
+template <typename T, int TR, int NS>
+__global__ __launch_bounds__(256) void k_gram_lines_mma(GramLinesArgs a) {
   using M = Mma<T>;
-  __shared__ T red[(TR * TR + TR) * 256];
+  constexpr int NP = TR * (TR + 1) / 2, NT = NP + TR;  // tiles of P and, after them, of h
+  __shared__ T red[NT * 256], scr[4 * NT * 256];
   const int g = blockIdx.y;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wl = wave & 3, wg = wave >> 2;
-  // the first item is requested together with the state (the list holds
-  // gridDim.x entries at least; one past the count is not used)
-  const int4 first = a.items[blockIdx.x];
-  if (halted(a.st, a.check_halt)) return;
-  const int nwork = a.st->n_gwork;
-  for (int w = blockIdx.x; w < nwork; w += gridDim.x) {
-  if (w > blockIdx.x) __syncthreads();  // the previous item's LDS reductions are complete
-  const int4 item = (w == blockIdx.x) ? first : a.items[w];
-  const int u = item.x, t = item.y;
-  const int r = a.r, col = lane & 15;
-  const int p0 = item.z, np = item.w;
-  const int c0 = g * a.cg, c1 = min(a.nc, c0 + a.cg);
-  // this lane's sample (B column) in tile t
-  const int pl = 8 * t + (col & 7);
-  const bool pok = pl < np;
-  const int pp = pok ? pl : 0;
-  GramLinesArgs al = a;
-  al.yg = a.yg + (long)w * a.nc * a.nx * 8;  // this item's [c][x][8] block
-  typename M::V P[TR][TR], H[TR];
+  const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, kk = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // the item is requested together with the state (the list holds gridDim.x entries)
+  const int4 item = a.items[blockIdx.x];
+  if (halted(a.st, a.check_halt) || (int)blockIdx.x >= a.st->n_gwork) return;
+  const int u = item.x, t = item.y, p0 = item.z, np = item.w;
+  const int r = a.r, nx = a.nx, c0 = g * a.cg, c1 = min(a.nc, c0 + a.cg);
+  const int spc = max(1, nx >> 4), sh = 31 - __builtin_clz(spc);  // steps per coil (nx is a power of two)
+  const int nst = (c1 - c0) * spc;
+  const long CS = 2L * a.ua * nx * r;                             // coil stride of W, floats
+  const int xl = 4 * wave + kk;
+  const float* const Wl = reinterpret_cast<const float*>(a.W) + 2L * u * nx * r + c0 * CS;
+  const int lw = 2 * r * xl + (TR == 1 ? min(col, 2 * r - 1) : 2 * min(col, r - 1));
+  const float* const Yl = reinterpret_cast<const float*>(a.yg) + 16L * ((long)blockIdx.x * a.nc + c0) * nx;
+  const int ly = 16 * xl + 2 * (col & 7) + (col >> 3);
+  typename M::V acc[NT];
 #pragma unroll
-  for (int i = 0; i < TR; ++i) {
-    H[i] = M::zero();
-#pragma unroll
-    for (int j = 0; j < TR; ++j) P[i][j] = M::zero();
-  }
-  if (t == 0)
-    gram_lines_loop<T, TR, UN, true, NWG>(al, u, c0, c1, np, pp, pok, lane, wl, wg, P, H);
-  else
-    gram_lines_loop<T, TR, UN, false, NWG>(al, u, c0, c1, np, pp, pok, lane, wl, wg, P, H);
-  // reduce across the 4 waves and form the complex outputs
-  T* Pt = red;                    // TR*TR tiles
-  T* Ht = red + TR * TR * 256;    // TR tiles of the h column block
-  auto C = [&](const T* base, int ntile_cols, int i, int j) -> double {
-    return (double)base[((i / 16) * ntile_cols + (j / 16)) * 256 + (i % 16) * 16 + (j % 16)];
+  for (int i = 0; i < NT; ++i) acc[i] = M::zero();
+  struct Buf {
+    float w[NS][TR], y[NS];
   };
-  constexpr int NTP = TR * TR + TR;
-  __shared__ T scr[4 * NWG * NTP * 256];
-  if (t == 0) {  // the P tiles and the h tiles together (red holds P, then h)
-    typename M::V all[NTP];
+  auto load = [&](int s0, Buf& b) {  // steps past the end load the last one
 #pragma unroll
-    for (int i = 0; i < TR; ++i) {
-      all[TR * TR + i] = H[i];
-#pragma unroll
-      for (int j = 0; j < TR; ++j) all[i * TR + j] = P[i][j];
+    for (int i = 0; i < NS; ++i) {
+      const int st = min(s0 + i, nst - 1), c = st >> sh, x0 = (st & (spc - 1)) << 4;
+      const float* wp = Wl + c * CS + 2 * r * x0;
+      if constexpr (TR == 1) {
+        b.w[i][0] = wp[lw];
+      } else {
+        const float2 v = *reinterpret_cast<const float2*>(wp + lw);
+        b.w[i][0] = v.x;
+        b.w[i][TR - 1] = v.y;
+      }
+      b.y[i] = Yl[16L * ((long)c * nx + x0) + ly];
     }
-    tiles_reduce_par<T, 4 * NWG, NTP>(red, scr, all, wave, lane);
+    __builtin_amdgcn_sched_barrier(0);  // every load of the batch is issued before what follows
+  };
+  auto mul = [&](int s0, const Buf& b, auto with_p) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      if (s0 + i < nst) {
+        if constexpr (decltype(with_p)::value) {
+          int n = 0;
+#pragma unroll
+          for (int i1 = 0; i1 < TR; ++i1)
+#pragma unroll
+            for (int i2 = i1; i2 < TR; ++i2) {
+              acc[n] = M::mma((T)b.w[i][i1], (T)b.w[i][i2], acc[n]);
+              ++n;
+            }
+        }
+#pragma unroll
+        for (int i1 = 0; i1 < TR; ++i1) acc[NP + i1] = M::mma((T)b.w[i][i1], (T)b.y[i], acc[NP + i1]);
+      }
+    }
+  };
+  auto run = [&](auto with_p) {
+    Buf b0, b1;
+    load(0, b0);
+    for (int s0 = 0; s0 < nst; s0 += 2 * NS) {
+      load(s0 + NS, b1);
+      mul(s0, b0, with_p);
+      load(s0 + 2 * NS, b0);
+      mul(s0 + NS, b1, with_p);
+    }
+  };
+  if (4 * wave < nx) {  // (8 columns: two waves have rows)
+    if (t == 0) run(std::true_type{});
+    else run(std::false_type{});
+  }
+  tiles_reduce_par<T, 4, NT>(red, scr, acc, wave, lane);
+  // entry (i, k) of a 16 x 16 tile; re(j), im(j): tile and row (column) of W_j's parts
+  auto re = [&](int j) { return TR == 1 ? 2 * j : j; };
+  auto im = [&](int j) { return TR == 1 ? 2 * j + 1 : 16 + j; };
+  auto C = [&](int i, int k) -> double {
+    if (TR == 2 && i >= 16 && k < 16) {
+      const int m = i;
+      i = k;
+      k = m;
+    }
+    const int tile = TR == 1 ? 0 : (i >> 4) + (k >> 4);
+    return (double)red[tile * 256 + (i & 15) * 16 + (k & 15)];
+  };
+  if (t == 0) {
     double2* Pout = a.P + ((long)g * a.ua + u) * r * r;
-    for (int e = tid; e < r * r; e += 256 * NWG) {
-      const int i = e / r, j = e % r;
-      const double re = C(Pt, TR, i, j) + C(Pt, TR, r + i, r + j);
-      const double im = C(Pt, TR, i, r + j) - C(Pt, TR, r + i, j);
-      Pout[e] = make_double2(re, im);
+    for (int e = tid; e < r * r; e += 256) {
+      const int i = e / r, j = e - i * r;
+      Pout[e] = make_double2(C(re(i), re(j)) + C(im(i), im(j)), C(re(i), im(j)) - C(im(i), re(j)));
     }
-  } else {
-    tiles_reduce_par<T, 4 * NWG, TR>(Ht, scr, H, wave, lane);
   }
   const int npt = min(8, np - 8 * t);
-  for (int e = tid; e < npt * r; e += 256 * NWG) {
-    const int p = e / r, j = e % r;
-    // rows j and r + j of the TR x 1 column of tiles, columns p (Re y) and 8 + p (Im y)
-    const double re = C(Ht, 1, j, p) + C(Ht, 1, r + j, 8 + p);
-    const double im = C(Ht, 1, j, 8 + p) - C(Ht, 1, r + j, p);
-    a.hp[((long)g * a.npairs + p0 + 8 * t + p) * r + j] = make_double2(re, im);
-  }
+  for (int e = tid; e < npt * r; e += 256) {
+    const int p = e / r, j = e - p * r;
+    auto H = [&](int i, int k) -> double { return (double)red[(NP + (i >> 4)) * 256 + (i & 15) * 16 + k]; };
+    a.hp[((long)g * a.npairs + p0 + 8 * t + p) * r + j] =
+        make_double2(H(re(j), p) + H(im(j), 8 + p), H(re(j), 8 + p) - H(im(j), p));
   }
 }
 
@@ -585,27 +498,15 @@ __global__ __launch_bounds__(SOLVE_NT) void k_solve(SolveArgs a) {
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-template <typename T, int TR>
-static void launch_lines_tr(const GramLinesArgs& a, int ny, int ngroups, int ht, hipStream_t s) {
-  // about one work item per workgroup: every sampled line plus a few extra
-  // sample tiles; a grid-stride loop takes any remainder
-  (void)ht;
-  const dim3 g(ny + 64, ngroups);
-  constexpr int NWG = GRAM_NWG;
-  if (a.nx >= 64) hipLaunchKernelGGL((k_gram_lines_mma<T, TR, 4, NWG>), g, dim3(256 * NWG), 0, s, a);
-  else hipLaunchKernelGGL((k_gram_lines_mma<T, TR, 1, NWG>), g, dim3(256 * NWG), 0, s, a);
-}
-
-hipError_t launch_gram_lines(const GramLinesArgs& a, int ny, int ngroups, int max_pairs, bool fp64,
-                             hipStream_t s) {
-  const int ht = std::max(1, (max_pairs + 7) / 8);
-  const int tr = (2 * a.r + 15) / 16;
+// max_items: a bound on the (line, tile) items; workgroups past their number leave at once
+hipError_t launch_gram_lines(const GramLinesArgs& a, int max_items, int ngroups, bool fp64, hipStream_t s) {
+  const dim3 g(max_items, ngroups), b(256);
   if (fp64) {
-    if (tr == 1) launch_lines_tr<double, 1>(a, ny, ngroups, ht, s);
-    else launch_lines_tr<double, 2>(a, ny, ngroups, ht, s);
+    if (a.r <= 8) hipLaunchKernelGGL((k_gram_lines_mma<double, 1, 2>), g, b, 0, s, a);
+    else hipLaunchKernelGGL((k_gram_lines_mma<double, 2, 1>), g, b, 0, s, a);
   } else {
-    if (tr == 1) launch_lines_tr<float, 1>(a, ny, ngroups, ht, s);
-    else launch_lines_tr<float, 2>(a, ny, ngroups, ht, s);
+    if (a.r <= 8) hipLaunchKernelGGL((k_gram_lines_mma<float, 1, 2>), g, b, 0, s, a);
+    else hipLaunchKernelGGL((k_gram_lines_mma<float, 2, 1>), g, b, 0, s, a);
   }
   return hipGetLastError();
 }

@@ -258,13 +258,21 @@ hipError_t gram_solve(altgdmin_ctx* c, int check_halt) {
 }
 
 // the QR Gram's partials summed (FP64) and the kernel that factors and
-// updates, for either mode that updates
+// updates, for either mode that updates.  Every workgroup of that kernel sums
+// partials of up to STEP_SUM_BYTES by itself, a round or two of loads, where a
+// kernel that sums them once costs a launch.  Ten iterations with the launch
+// and without, us: 19 KB (64 x 64, rank 4) 442 / 419, 37 KB (128 x 128, rank 4)
+// 593 / 567, 70 KB (64 x 64, rank 8) 533 / 519, 80 KB (128 x 128, rank 6) 639 /
+// 630; 139 KB (128 x 128, rank 8) 673 / 676, 154 KB (64 x 64, rank 12) 745 / 752.
+constexpr size_t STEP_SUM_BYTES = 96 * 1024;
 hipError_t step_apply(altgdmin_ctx* c, QrSmallArgs qa, const ApplyArgs& aa) {
-  const int m = qa.mode == STEP_MODE_QR ? qa.r : 2 * qa.r;
-  hipError_t e = launch_partials_total(qa.part, qa.part_f32, qa.nblk, m * (m + 1) / 2, c->at<double2>(c->o_qtot),
-                                       c->stream);
-  if (e != hipSuccess) return e;
-  qa.part = c->at<double2>(c->o_qtot);
+  const int m = qa.mode == STEP_MODE_QR ? qa.r : 2 * qa.r, nout = m * (m + 1) / 2;
+  if ((size_t)qa.nblk * nout * (qa.part_f32 ? 8 : 16) > STEP_SUM_BYTES) {
+    hipError_t e = launch_partials_total(qa.part, qa.part_f32, qa.nblk, nout, c->at<double2>(c->o_qtot), c->stream);
+    if (e != hipSuccess) return e;
+    qa.part = c->at<double2>(c->o_qtot);
+    qa.summed = 1;
+  }
   return launch_step_apply(qa, aa, c->stream);
 }
 

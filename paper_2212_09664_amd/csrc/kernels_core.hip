@@ -477,7 +477,7 @@ __device__ __forceinline__ void partials_sum(const double2* part, int f32, int n
 // the partials' sum, against 61 us for a one-workgroup factor and a separate
 // update; rank 8: 11.3 us, 12.2 us with the Gram staged in LDS by the workgroup.
 // ===========================================================================
-template <int RT>
+template <int RT, bool SUM>
 __global__ __launch_bounds__(256) void k_step_apply(QrSmallArgs a, ApplyArgs ap) {
   __shared__ double2 L[16 * CHOL_LD], W0[256], W1[256], W2[256];
   __shared__ float2 Rf[RT * RT];
@@ -514,10 +514,12 @@ __global__ __launch_bounds__(256) void k_step_apply(QrSmallArgs a, ApplyArgs ap)
       for (int i = 0; i < RT; ++i) g0[i] = (i < r) ? ap.G[pc * r + i] : make_float2(0.f, 0.f);
     }
   }
+  __shared__ double2 s_tot[SUM ? 16 * 33 : 1];
+  if constexpr (SUM) partials_sum<256>(a.part, a.part_f32, a.nblk, m * (m + 1) / 2, s_tot, 0, 1);
   // entry (x, y) of the Hermitian Gram, from its upper triangle in tri order
   auto gram = [&](int x, int y) -> double2 {
-    const int lo = min(x, y), hi = max(x, y);
-    const double2 v = a.part[lo * m - lo * (lo - 1) / 2 + (hi - lo)];
+    const int lo = min(x, y), hi = max(x, y), e = lo * m - lo * (lo - 1) / 2 + (hi - lo);
+    const double2 v = SUM ? s_tot[e] : a.part[e];
     return make_double2(v.x, x <= y ? v.y : -v.y);
   };
   // this lane's entries (ri, 4 t + rg) of U^H U, U^H G, G^H U and G^H G
@@ -779,10 +781,16 @@ hipError_t launch_step_apply(const QrSmallArgs& a, const ApplyArgs& ap, hipStrea
   // 256 pixels per workgroup: the update's stores spread over every compute
   // unit; register rows of 4, 8, 12 or 16
   const dim3 g(a.mode == STEP_MODE_ETA ? 1u : (unsigned)((ap.n + 255) / 256));
-  if (a.r <= 4) hipLaunchKernelGGL(k_step_apply<4>, g, dim3(256), 0, s, a, ap);
-  else if (a.r <= 8) hipLaunchKernelGGL(k_step_apply<8>, g, dim3(256), 0, s, a, ap);
-  else if (a.r <= 12) hipLaunchKernelGGL(k_step_apply<12>, g, dim3(256), 0, s, a, ap);
-  else hipLaunchKernelGGL(k_step_apply<16>, g, dim3(256), 0, s, a, ap);
+  switch (2 * ((a.r + 3) / 4) + !a.summed) {
+    case 2: hipLaunchKernelGGL((k_step_apply<4, false>), g, dim3(256), 0, s, a, ap); break;
+    case 3: hipLaunchKernelGGL((k_step_apply<4, true>), g, dim3(256), 0, s, a, ap); break;
+    case 4: hipLaunchKernelGGL((k_step_apply<8, false>), g, dim3(256), 0, s, a, ap); break;
+    case 5: hipLaunchKernelGGL((k_step_apply<8, true>), g, dim3(256), 0, s, a, ap); break;
+    case 6: hipLaunchKernelGGL((k_step_apply<12, false>), g, dim3(256), 0, s, a, ap); break;
+    case 7: hipLaunchKernelGGL((k_step_apply<12, true>), g, dim3(256), 0, s, a, ap); break;
+    case 8: hipLaunchKernelGGL((k_step_apply<16, false>), g, dim3(256), 0, s, a, ap); break;
+    default: hipLaunchKernelGGL((k_step_apply<16, true>), g, dim3(256), 0, s, a, ap); break;
+  }
   if (a.mode == STEP_MODE_STEP && !a.commit_direct)
     hipLaunchKernelGGL(k_step_commit, dim3(1), dim3(64), 0, s, a.st, a.exit_consec);
   return hipGetLastError();

@@ -170,8 +170,8 @@ struct GramColsArgs {
 };
 
 struct QrSmallArgs {
-  const double2* part;   // per QR Gram workgroup: its partial (FP32 pairs when part_f32), summed first; then the sum
-  int part_f32;
+  const double2* part;   // per QR Gram workgroup: its partial (FP32 pairs when part_f32); their FP64 sum when summed
+  int part_f32, summed;
   int nblk, r, mode, n, q;  // mode: STEP_MODE_*
   double eta_c, eta_cap_c, eps_exit;
   int exit_consec;  // the exit rule fires after this many consecutive small steps (>= 1)

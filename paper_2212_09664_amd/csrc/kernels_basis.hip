@@ -110,15 +110,17 @@ __global__ __launch_bounds__(AG_NT) void k_basis_adj(BasisArgs a) {
   constexpr int IT0 = GM::IT0, R0 = GM::R0, ITL = GM::ITL, RL = GM::RL;
   __shared__ float2 s[FftPlan<N>::P > 1 ? N * CT : 1];
   __shared__ float2 s_tw[N];
-  __shared__ int s_ro[N];  // k-space row -> offset of its K row within a coil, -1 for a zero row
+  __shared__ int s_ro[N];  // k-space row -> offset of its K row within a coil
   const int tid = threadIdx.x;
   const int txx = a.txx, r = a.r, ctr = txx * r;
   const int x0 = blockIdx.x * txx;
+  // a row that is not sampled reads the row past the sampled ones, which the fold clears
+  const int zrow = a.row_unit ? min(a.st->n_units, a.ua - 1) : 0;
   for (int e = tid; e < N; e += AG_NT) {  // both loads before either store: one round trip
     const float2 w = a.tw[e];
     const int u = a.row_unit ? a.row_unit[e] : e;
     s_tw[e] = make_float2(w.x, -w.y);
-    s_ro[e] = u >= 0 ? u * a.nx * r : -1;
+    s_ro[e] = (u >= 0 ? u : zrow) * a.nx * r;
   }
   __syncthreads();
   float2 acc[ITL][RL];
@@ -128,17 +130,13 @@ __global__ __launch_bounds__(AG_NT) void k_basis_adj(BasisArgs a) {
     for (int q = 0; q < RL; ++q) acc[it][q] = make_float2(0.f, 0.f);
   const int cb = blockIdx.y * a.cgs, ce = min(a.nc, cb + a.cgs);
   float2 kv[IT0][R0];
-  auto fetch = [&](int c) {
+  auto fetch = [&](int c) {  // columns past the tile's repeat a valid one; they are not stored
     const float2* src = a.K + (long)c * a.ua * a.nx * r + x0 * r;
 #pragma unroll
     for (int it = 0; it < IT0; ++it) {
-      const int g = tid + it * AG_NT, col = g % CT;
-      const bool ok = GM::in_ok(g) && col < ctr;
+      const int g = GM::in_ok(tid + it * AG_NT) ? tid + it * AG_NT : 0, col = min(g % CT, ctr - 1);
 #pragma unroll
-      for (int q = 0; q < R0; ++q) {
-        const int ro = ok ? s_ro[GM::in_row(g, q)] : -1;
-        kv[it][q] = ro >= 0 ? src[ro + col] : make_float2(0.f, 0.f);
-      }
+      for (int q = 0; q < R0; ++q) kv[it][q] = src[s_ro[GM::in_row(g, q)] + col];
     }
   };
   if (cb < ce) fetch(cb);
@@ -204,7 +202,9 @@ __global__ __launch_bounds__(512) void k_adj_qr(BasisArgs a) {
   // row pitch of the embedding: a step's 4 rows in disjoint bank quarters
   constexpr int LDX = (EC % 64 == 0 || EC % 64 == 32) ? EC + 16 : EC;
   constexpr int UE = (N * 4 * TRM + 511) / 512;  // U entries per thread (r <= 4 TRM)
-  constexpr int CMAX = 3072;  // coil values of the column staged in LDS when nc N fits
+  // coil values of the column staged in LDS when nc N fits
+  constexpr int CMAX = N * LDX / 2 > 3072 ? N * LDX / 2 : 3072;
+  constexpr int CE = (12 * N + 511) / 512;  // ... twelve coils' at a time in flight
   // one LDS block: the two transform tiles, then the embedding X (the staged
   // coil values share its space: they are done with before X is formed);
   // after the matrix-core loop both serve as the scratch of the reduction
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(512) void k_adj_qr(BasisArgs a) {
   float2* const s_cw = reinterpret_cast<float2*>(lds_blk + S_BYTES);
   __shared__ float red[NTL * 256];
   __shared__ float2 s_tw[N];
-  __shared__ int s_ro[N];  // k-space row -> offset of its K row within a coil, -1 for a zero row
+  __shared__ int s_ro[N];  // k-space row -> offset of its K row within a coil
   const int tid = threadIdx.x, grp = tid >> 8, lt = tid & 255;
   const int r = a.r, nx = a.nx, ncp = CT / r, nct = ncp * r, txx = a.txx;
   const bool cw_lds = a.nc * N <= CMAX;
@@ -230,18 +230,30 @@ __global__ __launch_bounds__(512) void k_adj_qr(BasisArgs a) {
     const int e = min(tid + 512 * i, N * r - 1), y = e / r, j = e - y * r;
     uv[i] = a.U[((long)y * nx + x) * r + j];
   }
-  for (int e = tid; e < N; e += 512) {
-    const float2 w = a.tw[e];
-    const int u = a.row_unit ? a.row_unit[e] : e;
-    s_tw[e] = make_float2(w.x, -w.y);
-    s_ro[e] = u >= 0 ? u * nx * r : -1;
+  // ... then the column's coil values s_c(y, x), which the combine reads from
+  // LDS, and the tables; the loads are all issued before the first is stored
+  const float2* const cx = a.coils + (long)(x / txx) * N * txx + (x % txx);
+  auto coil_at = [&](int e) { return cx[(long)(e / N) * a.n + (long)(e % N) * txx]; };
+  float2 cw0[CE];
+  if (cw_lds) {
+#pragma unroll
+    for (int i = 0; i < CE; ++i) cw0[i] = coil_at(min(tid + 512 * i, a.nc * N - 1));
   }
-  // the column's coil values s_c(y, x) for every coil: the combine then reads LDS
-  if (cw_lds)
-    for (int e = tid; e < a.nc * N; e += 512) {
-      const int c = e / N, y = e - c * N;
-      s_cw[e] = a.coils[(long)c * a.n + (long)(x / txx) * N * txx + (long)y * txx + (x % txx)];
-    }
+  // a row that is not sampled reads the row past the sampled ones, which the fold clears
+  const int te = min(tid, N - 1), zrow = a.row_unit ? min(a.st->n_units, a.ua - 1) : 0;
+  const float2 tw0 = a.tw[te];
+  const int un0 = a.row_unit ? a.row_unit[te] : te;
+  __builtin_amdgcn_sched_barrier(0);
+  if (tid < N) {
+    s_tw[tid] = make_float2(tw0.x, -tw0.y);
+    s_ro[tid] = (un0 >= 0 ? un0 : zrow) * nx * r;
+  }
+  if (cw_lds) {
+#pragma unroll
+    for (int i = 0; i < CE; ++i)
+      if (tid + 512 * i < a.nc * N) s_cw[tid + 512 * i] = cw0[i];
+    for (int e = tid + 512 * CE; e < a.nc * N; e += 512) s_cw[e] = coil_at(e);
+  }
   __syncthreads();
   const int npass = (a.nc + ncp - 1) / ncp, nround = (npass + 1) / 2;
   float2 acc[ITL][RL];
@@ -250,17 +262,22 @@ __global__ __launch_bounds__(512) void k_adj_qr(BasisArgs a) {
 #pragma unroll
     for (int q = 0; q < RL; ++q) acc[it][q] = make_float2(0.f, 0.f);
   float2 kv[IT0][R0];
-  auto fetch = [&](int pass) {  // a pass past the last coil gives zeros
+  // columns past the tile's and passes past the last coil repeat a valid one; they are not combined
+  const float2* kp[IT0];
+  int kc[IT0], row0[IT0];
+#pragma unroll
+  for (int it = 0; it < IT0; ++it) {
+    const int g = GM::in_ok(lt + it * AG_NT) ? lt + it * AG_NT : 0, col = min(g % CT, nct - 1), cs = col / r;
+    kc[it] = cs;
+    kp[it] = a.K + x * r + col - cs * r;
+    row0[it] = GM::in_row(g, 0);
+  }
+  auto fetch = [&](int pass) {
 #pragma unroll
     for (int it = 0; it < IT0; ++it) {
-      const int g = lt + it * AG_NT, col = g % CT, cs = col / r, j = col - cs * r, c = pass * ncp + cs;
-      const bool ok = GM::in_ok(g) && col < nct && c < a.nc;
-      const float2* src = a.K + (long)(ok ? c : 0) * a.ua * nx * r + x * r + j;
+      const float2* src = kp[it] + (long)min(pass * ncp + kc[it], a.nc - 1) * a.ua * nx * r;
 #pragma unroll
-      for (int q = 0; q < R0; ++q) {
-        const int ro = ok ? s_ro[GM::in_row(g, q)] : -1;
-        kv[it][q] = ro >= 0 ? src[ro] : make_float2(0.f, 0.f);
-      }
+      for (int q = 0; q < R0; ++q) kv[it][q] = src[s_ro[row0[it] + q * (N / R0)]];
     }
   };
   fetch(grp);
@@ -458,7 +475,12 @@ __global__ __launch_bounds__(AG_NT) void k_fold_lines2(FoldArgs a) {
   // used only once the line is known to be sampled
   load_w(0);
   const int nu_ = a.st->n_units;  // requested with the stop test's loads
-  if (halted(a.st, a.check_halt) || u >= nu_) return;
+  if (halted(a.st, a.check_halt)) return;
+  if (u >= nu_) {  // the adjoint reads the first row past the sampled ones for those that are not
+    if (u == nu_)
+      for (int e = tid; e < nx * r; e += AG_NT) a.K[((long)c * a.ua + u) * nx * r + e] = make_float2(0.f, 0.f);
+    return;
+  }
   const int p0 = lrec.y, np = lrec.z;
   const float2* Yc = a.yu + (long)a.nc * nx * p0 + (long)c * np * nx;  // this line and coil, [p][x]
   float2 ya[8], yb[8];
@@ -563,7 +585,12 @@ __global__ __launch_bounds__(AG_NT) void k_fold_lines_mma(FoldArgs a) {
     for (int h = 0; h < RT / 4; ++h) wv[tt][h] = wr[min(4 * h + kq, r - 1)];
   }
   const int nu_ = a.st->n_units;
-  if (halted(a.st, a.check_halt) || u >= nu_) return;
+  if (halted(a.st, a.check_halt)) return;
+  if (u >= nu_) {  // the adjoint reads the first row past the sampled ones for those that are not
+    if (u == nu_)
+      for (int e = tid; e < nx * r; e += AG_NT) a.K[((long)c * a.ua + u) * nx * r + e] = make_float2(0.f, 0.f);
+    return;
+  }
 #pragma unroll
   for (int tt = 0; tt < TW; ++tt)
 #pragma unroll

@@ -34,7 +34,10 @@ namespace ag {
 //   NORMAL_ISTA  w = A_k^H (y_k - A_k s) for image k = s
 // Bound by the transforms' arithmetic and their LDS exchanges.  Mean image,
 // 256 x 256, 12 coils: 900 -> 159 us with its ten iterations (a CG iteration
-// from eight launches, 90 us, to two).
+// from eight launches, 90 us, to two).  ISTA, 48 frames of 128 x 128, 8 coils:
+// 26 us (27.7 with the data requested where it is used, under a branch, and the
+// next coil after its transform; the image values in LDS leave the registers
+// for both).
 // ---------------------------------------------------------------------------
 template <int N, int CT, int NT, int MODE>
 __global__ __launch_bounds__(NT) void k_normal_lines(NormalArgs a) {
@@ -42,6 +45,7 @@ __global__ __launch_bounds__(NT) void k_normal_lines(NormalArgs a) {
   constexpr int IT0 = GM::IT0, R0 = GM::R0, ITL = GM::ITL, RL = GM::RL;
   constexpr bool MEAN = MODE == NORMAL_MEAN;
   __shared__ float2 s[GM::LDS];
+  __shared__ float2 s_p[IT0 * R0 * NT];  // each thread's image values, used once a coil
   __shared__ float2 s_tw[N];
   __shared__ float s_wt[MEAN ? N : 1];
   __shared__ int s_li[MEAN ? 1 : N];
@@ -112,7 +116,7 @@ __global__ __launch_bounds__(NT) void k_normal_lines(NormalArgs a) {
 #pragma unroll
     for (int q = 0; q < R0; ++q) {
       acc[it][q] = make_float2(0.f, 0.f);
-      if (!ok[it]) pv[it][q] = make_float2(0.f, 0.f);
+      s_p[(it * R0 + q) * NT + tid] = ok[it] ? pv[it][q] : make_float2(0.f, 0.f);
     }
   double dot = 0.0;
   for (int c = cb; c < ce; ++c) {
@@ -120,7 +124,19 @@ __global__ __launch_bounds__(NT) void k_normal_lines(NormalArgs a) {
 #pragma unroll
     for (int it = 0; it < IT0; ++it)
 #pragma unroll
-      for (int q = 0; q < R0; ++q) v0[it][q] = cmul(cv[it][q], pv[it][q]);
+      for (int q = 0; q < R0; ++q) v0[it][q] = cmul(cv[it][q], s_p[(it * R0 + q) * NT + tid]);
+    // the frame's data at the transform's outputs, in flight during it (the
+    // rows that are not sampled request the frame's first)
+    float2 yv[MEAN ? 1 : ITL][MEAN ? 1 : RL];
+    if constexpr (!MEAN) {
+      const float2* yc = a.y + ((long)img * a.nc + c) * a.m_max;
+#pragma unroll
+      for (int it = 0; it < ITL; ++it) {
+        const int g = tid + it * NT, x = min(x0 + GM::out_col(g), a.nx - 1);
+#pragma unroll
+        for (int q = 0; q < RL; ++q) yv[it][q] = yc[max(GM::out_ok(g) ? s_li[GM::out_row(g, q)] : 0, 0) * a.nx + x];
+      }
+    }
     fft_regs<N, CT, NT, false>(v0, vo, s, s_tw);
 #pragma unroll
     for (int it = 0; it < ITL; ++it) {
@@ -134,22 +150,22 @@ __global__ __launch_bounds__(NT) void k_normal_lines(NormalArgs a) {
           vo[it][q] = cscale(v, w);
           dot += (double)w * ((double)v.x * v.x + (double)v.y * v.y);
         } else {
-          const int l = in ? s_li[GM::out_row(g, q)] : -1;
-          float2 r = make_float2(0.f, 0.f);
-          if (l >= 0) {
-            const float2 y = a.y[((long)img * a.nc + c) * a.m_max + (long)l * a.nx + x];
-            r = cscale(csub(y, cscale(v, a.scale)), a.scale);
-          }
-          vo[it][q] = r;
+          const float w = in && s_li[GM::out_row(g, q)] >= 0 ? a.scale : 0.f;
+          const float2 r = csub(yv[it][q], cscale(v, a.scale));
+          vo[it][q] = w != 0.f ? cscale(r, w) : make_float2(0.f, 0.f);
         }
       }
     }
+    float2 cn[IT0][R0];
+    load(a.coils + (long)min(c + 1, ce - 1) * a.n, cn);  // the next coil's, in flight during the transform
     fft_regs<N, CT, NT, true, true, true>(vo, v0, s, s_tw);
 #pragma unroll
     for (int it = 0; it < IT0; ++it)
 #pragma unroll
-      for (int q = 0; q < R0; ++q) acc[it][q] = cjfma(acc[it][q], cv[it][q], v0[it][q]);
-    if (c + 1 < ce) load(a.coils + (long)(c + 1) * a.n, cv);
+      for (int q = 0; q < R0; ++q) {
+        acc[it][q] = cjfma(acc[it][q], cv[it][q], v0[it][q]);
+        cv[it][q] = cn[it][q];
+      }
   }
   float2* const out = a.w + (long)grp * a.part_stride + (long)img * a.n;
 #pragma unroll

@@ -26,8 +26,12 @@ namespace {
 
 
 // sum over lines of ceil(pairs / 8) <= (pairs + 7 lines) / 8, pairs <= q * width
-// workgroups of the spectral init's X0^H X0 on the matrix cores: 128 rows each, at most 512
-int init_nblk(const altgdmin_ctx* c) { return (int)std::max(1L, std::min(512L, ((long)c->n + 127) / 128)); }
+// workgroups of the spectral init's X0^H X0 on the matrix cores: 128 rows each, at most 512, or 64 rows where
+// that leaves compute units idle
+int init_nblk(const altgdmin_ctx* c) {
+  const long n = c->n;
+  return (int)std::max({1L, std::min(512L, (n + 127) / 128), std::min(256L, (n + 63) / 64)});
+}
 
 long gram_items_bound(const altgdmin_ctx* c) {
   return ((long)c->p.q * c->width + 7L * c->n_loc) / 8 + 1;

@@ -98,8 +98,8 @@ __global__ void k_cg_end(CgArgs a, const DevState* st);
 __global__ void k_line_sum(const float2* yu, const int32_t* loc_ptr, int nc, int nx, float2* T, const DevState* st);
 __global__ void k_loc_sum(const float2* y, const int2* pairs, const int32_t* loc_ptr, long n, int nc, int m_max,
                           float2* T, const DevState* st);
-__global__ void k_expand(const float2* U, const float2* B, const float2* zbar, const float2* E, long n, int q, int r,
-                         float2* Z, const DevState* st);
+hipError_t launch_expand(const float2* U, const float2* B, const float2* zbar, const float2* E, long n, int q, int r,
+                         float2* Z, const DevState* st, hipStream_t s);
 
 // ISTA's temporal step (kernels_mri.hip); partial sums: one pair per 64 pixels
 struct IstaArgs {

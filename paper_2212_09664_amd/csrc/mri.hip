@@ -98,7 +98,6 @@ size_t aux_layout(const altgdmin_ctx* c, char* base, Aux* a) {
 
 bool aux_ok(const void* d_aux) { return d_aux && (reinterpret_cast<uintptr_t>(d_aux) & 255) == 0; }
 
-unsigned grid_for(long n) { return (unsigned)std::max(1L, std::min(1024L, (n + 255) / 256)); }
 
 #define AGCHK(x)                     \
   do {                               \
@@ -506,11 +505,9 @@ altgdmin_status altgdmin_expand(altgdmin_ctx* c, const void* d_U, const void* d_
                                 const void* d_E, void* d_Z) {
   if (!c || !d_Z || (!d_U) != (!d_B)) return ALTGDMIN_EINVAL;
   if (!c->bound) return ALTGDMIN_ESTATE;
-  const long nq = (long)c->n * c->p.q;
-  hipLaunchKernelGGL(k_expand, dim3(grid_for(nq)), dim3(256), 0, c->stream, static_cast<const float2*>(d_U),
-                     static_cast<const float2*>(d_B), static_cast<const float2*>(d_zbar),
-                     static_cast<const float2*>(d_E), (long)c->n, c->p.q, c->p.r, static_cast<float2*>(d_Z), c->st());
-  return map_hip(hipGetLastError());
+  return map_hip(launch_expand(static_cast<const float2*>(d_U), static_cast<const float2*>(d_B),
+                               static_cast<const float2*>(d_zbar), static_cast<const float2*>(d_E), (long)c->n, c->p.q,
+                               c->p.r, static_cast<float2*>(d_Z), c->st(), c->stream));
 }
 
 altgdmin_status altgdmin_rank_energy(altgdmin_ctx* c, int32_t r_cap, double* h_sigma2, void* d_aux) {

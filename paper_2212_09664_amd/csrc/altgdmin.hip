@@ -24,8 +24,6 @@ size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 namespace {
 
-
-// sum over lines of ceil(pairs / 8) <= (pairs + 7 lines) / 8, pairs <= q * width
 // workgroups of the spectral init's X0^H X0 on the matrix cores: 128 rows each, at most 512, or 64 rows where
 // that leaves compute units idle
 int init_nblk(const altgdmin_ctx* c) {
@@ -33,6 +31,7 @@ int init_nblk(const altgdmin_ctx* c) {
   return (int)std::max({1L, std::min(512L, (n + 127) / 128), std::min(256L, (n + 63) / 64)});
 }
 
+// the Gram kernel's work items: sum over lines of ceil(pairs / 8) <= (pairs + 7 lines) / 8, pairs <= q * width
 long gram_items_bound(const altgdmin_ctx* c) {
   return ((long)c->p.q * c->width + 7L * c->n_loc) / 8 + 1;
 }
@@ -209,9 +208,7 @@ hipError_t gram_solve(altgdmin_ctx* c, int check_halt) {
     g.st = c->st();
     g.check_halt = check_halt;
     tmark(c, TK_GRAM);
-    // a line's samples in tiles of 8: at most one partly filled tile per line
-    e = launch_gram_lines(g, (int)std::min((long)p.ny * ((p.q + 7) / 8), p.ny + (long)p.q * c->lmax / 8),
-                          c->gram_ngroups, c->fp64, c->stream);
+    e = launch_gram_lines(g, (int)gram_items_bound(c), c->gram_ngroups, c->fp64, c->stream);
     tmark(c, TK_GRAM);
   } else {
     GramIndexArgs g{};

@@ -95,12 +95,14 @@ void carve(altgdmin_ctx* c) {
   c->o_qtot = take(sizeof(double2) * m_iter * (m_iter + 1) / 2);  // their sum (the fused step)
   c->o_stsrc = take(sizeof(double2) * STATS_SRC);  // deferred statistics of the step
   c->o_Vs = take(sizeof(float2) * (size_t)q * r);
-  // temp: X0 plus the truncated hybrid data (LINES) or a chunk of coil images (INDEX)
+  // temp: X0 plus the truncated hybrid data (LINES) or a chunk of coil images
+  // (INDEX); or the FP64 coil images of the mean's right-hand side
   size_t tb = sizeof(float2) * (size_t)n * q;
   if (c->lines)
     tb += ysz;
   else
     tb += sizeof(float2) * (size_t)c->kc * nc * n;
+  tb = std::max(tb, sizeof(double2) * (size_t)nc * n);
   c->T_bytes = tb;
   c->o_T = take(tb);
   c->o_end = off;

@@ -47,6 +47,10 @@ __device__ __forceinline__ double2 djmul(double2 a, double2 b) {  // conj(a) * b
   return make_double2(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x);
 }
 __device__ __forceinline__ double2 dconj(double2 a) { return make_double2(a.x, -a.y); }
+// the names the transforms use in either precision
+__device__ __forceinline__ double2 cadd(double2 a, double2 b) { return dadd(a, b); }
+__device__ __forceinline__ double2 csub(double2 a, double2 b) { return dsub(a, b); }
+__device__ __forceinline__ double2 cmul(double2 a, double2 b) { return dmul(a, b); }
 __device__ __forceinline__ double2 f2d(float2 a) { return make_double2((double)a.x, (double)a.y); }
 __device__ __forceinline__ float2 d2f(double2 a) { return make_float2((float)a.x, (float)a.y); }
 
@@ -90,25 +94,25 @@ __device__ __forceinline__ bool halted(const DevState* st, int check_halt) {
 #define STEP_CONVERGED 4
 
 // ---------------------------------------------------------------------------
-// in-register DFTs of radix 2, 4, 8, 16
+// in-register DFTs of radix 2, 4, 8, 16 (C: float2 or double2)
 // Output k of the radix-R DFT ends up in register out_pos<R>(k).
 // ---------------------------------------------------------------------------
-template <bool INV>
-__device__ __forceinline__ float2 mul_mi(float2 v) {  // * (-i) forward, * (+i) inverse
-  return INV ? make_float2(-v.y, v.x) : make_float2(v.y, -v.x);
+template <bool INV, typename C>
+__device__ __forceinline__ C mul_mi(C v) {  // * (-i) forward, * (+i) inverse
+  return INV ? C{-v.y, v.x} : C{v.y, -v.x};
 }
 
-template <bool INV>
-__device__ __forceinline__ void dft2(float2& a, float2& b) {
-  float2 t = a;
+template <bool INV, typename C>
+__device__ __forceinline__ void dft2(C& a, C& b) {
+  C t = a;
   a = cadd(t, b);
   b = csub(t, b);
 }
 
-template <bool INV>
-__device__ __forceinline__ void dft4(float2& a0, float2& a1, float2& a2, float2& a3) {
-  float2 s02 = cadd(a0, a2), d02 = csub(a0, a2), s13 = cadd(a1, a3), d13 = csub(a1, a3);
-  float2 t = mul_mi<INV>(d13);
+template <bool INV, typename C>
+__device__ __forceinline__ void dft4(C& a0, C& a1, C& a2, C& a3) {
+  C s02 = cadd(a0, a2), d02 = csub(a0, a2), s13 = cadd(a1, a3), d13 = csub(a1, a3);
+  C t = mul_mi<INV>(d13);
   a0 = cadd(s02, s13);
   a2 = csub(s02, s13);
   a1 = cadd(d02, t);
@@ -116,10 +120,11 @@ __device__ __forceinline__ void dft4(float2& a0, float2& a1, float2& a2, float2&
 }
 
 // v * exp(-+ 2 pi i k / 16), k a compile-time constant after unrolling
-template <bool INV>
-__device__ __forceinline__ float2 tw16(float2 v, int k) {
-  const float C1 = 0.92387953251128674f, C2 = 0.70710678118654752f, C3 = 0.38268343236508977f;
-  float c, s;
+template <bool INV, typename C>
+__device__ __forceinline__ C tw16(C v, int k) {
+  using F = decltype(v.x + v.x);
+  const F C1 = (F)0.92387953251128674, C2 = (F)0.70710678118654752, C3 = (F)0.38268343236508977;
+  F c, s;
   switch (k & 15) {
     case 0: return v;
     case 1: c = C1; s = C3; break;
@@ -129,13 +134,12 @@ __device__ __forceinline__ float2 tw16(float2 v, int k) {
     case 5: c = -C3; s = C1; break;
     case 6: c = -C2; s = C2; break;
     case 7: c = -C1; s = C3; break;
-    case 8: return make_float2(-v.x, -v.y);
+    case 8: return C{-v.x, -v.y};
     case 9: c = -C1; s = -C3; break;
-    default: c = 1.f; s = 0.f; break;
+    default: c = (F)1; s = (F)0; break;
   }
   // forward: (c - i s); inverse: (c + i s)
-  float2 w = INV ? make_float2(c, s) : make_float2(c, -s);
-  return cmul(v, w);
+  return cmul(v, INV ? C{c, s} : C{c, -s});
 }
 
 template <int R>
@@ -143,8 +147,8 @@ __device__ __forceinline__ constexpr int out_pos(int k) {
   return R == 16 ? 4 * (k % 4) + k / 4 : (R == 8 ? 4 * (k % 2) + k / 2 : k);
 }
 
-template <int R, bool INV>
-__device__ __forceinline__ void dft_reg(float2* v) {
+template <int R, bool INV, typename C>
+__device__ __forceinline__ void dft_reg(C* v) {
   if constexpr (R == 2) {
     dft2<INV>(v[0], v[1]);
   } else if constexpr (R == 4) {
@@ -171,34 +175,30 @@ __device__ __forceinline__ void dft_reg(float2* v) {
 }
 
 // ---------------------------------------------------------------------------
-// Stockham autosort FFT of TX columns of length N held in LDS as s[e*TX+col]
-// (column index fastest), by NT threads (thread index modulo NT: a
-// workgroup of several groups of NT threads transforms one tile per group,
-// every group reaching the barriers together).  Each pass of radix R reads R points at stride
-// N/R, applies the twiddles exp(-+2 pi i (j mod Ns) r / (Ns R)), does an
-// in-register radix-R DFT and writes them at stride Ns.  tw[t] holds
-// exp(-2 pi i t / N) in float (computed in double).  Unnormalised.
+// Stockham autosort FFT of TX columns of length N (a power of two in [8, 512])
+// held in LDS as s[e*TX+col] (column index fastest), by a workgroup of NT
+// threads.  Each pass of radix R reads R points at stride N/R, applies the
+// twiddles exp(-+2 pi i (j mod Ns) r / (Ns R)), does an in-register radix-R DFT
+// and writes them at stride Ns.  tw[t] holds exp(-2 pi i t / N).
+// Unnormalised.  The double-precision transforms of the mean's right-hand
+// side run once a call through this form; the others are register-fed.
 // ---------------------------------------------------------------------------
-template <int N, int R, int TX, int NT, bool INV, bool CONJ_TW = INV>
-__device__ __forceinline__ void stockham_pass(float2* s, const float2* __restrict__ tw, int Ns) {
-  constexpr int G = TX * (N / R);
-  constexpr int IT = (G + NT - 1) / NT;
-  float2 v[IT][R];
-  const int tid = threadIdx.x % NT;  // a workgroup of several NT-thread groups runs one transform per group
+template <int N, int R, int TX, int NT, bool INV, typename C>
+__device__ __forceinline__ void stockham_pass(C* s, const C* tw, int Ns) {
+  constexpr int G = TX * (N / R), IT = (G + NT - 1) / NT;
+  C v[IT][R];
+  const int tid = threadIdx.x;
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
     const int g = tid + it * NT;
-    if ((G % NT == 0) || g < G) {
-      const int col = g % TX, j = g / TX;
+    if (g < G) {
+      const int col = g % TX, j = g / TX, step = (j % Ns) * (N / (Ns * R));
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[it][r] = s[(j + r * (N / R)) * TX + col];
-      if (Ns > 1) {
-        const int step = (j % Ns) * (N / (Ns * R));
-#pragma unroll
-        for (int r = 1; r < R; ++r) {
-          float2 w = tw[step * r];
-          if (CONJ_TW) w.y = -w.y;
-          v[it][r] = cmul(v[it][r], w);
+      for (int r = 0; r < R; ++r) {
+        v[it][r] = s[(j + r * (N / R)) * TX + col];
+        if (Ns > 1 && r > 0) {
+          const C w = tw[step * r];
+          v[it][r] = cmul(v[it][r], INV ? C{w.x, -w.y} : w);
         }
       }
       dft_reg<R, INV>(v[it]);
@@ -208,45 +208,27 @@ __device__ __forceinline__ void stockham_pass(float2* s, const float2* __restric
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
     const int g = tid + it * NT;
-    if ((G % NT == 0) || g < G) {
-      const int col = g % TX, j = g / TX;
-      const int idxD = (j / Ns) * Ns * R + (j % Ns);
+    if (g < G) {
+      const int col = g % TX, j = g / TX, d = (j / Ns) * Ns * R + (j % Ns);
 #pragma unroll
-      for (int r = 0; r < R; ++r) s[(idxD + r * Ns) * TX + col] = v[it][out_pos<R>(r)];
+      for (int r = 0; r < R; ++r) s[(d + r * Ns) * TX + col] = v[it][out_pos<R>(r)];
     }
   }
   __syncthreads();
 }
 
-// The whole transform; N a power of two in [8, 512].
-template <int N, int TX, int NT, bool INV>
-__device__ __forceinline__ void fft_lds(float2* s, const float2* __restrict__ tw) {
-  if constexpr (N == 8) {
-    stockham_pass<8, 8, TX, NT, INV>(s, tw, 1);
-  } else if constexpr (N == 16) {
-    stockham_pass<16, 16, TX, NT, INV>(s, tw, 1);
-  } else if constexpr (N == 32) {
-    stockham_pass<32, 8, TX, NT, INV>(s, tw, 1);
-    stockham_pass<32, 4, TX, NT, INV>(s, tw, 8);
-  } else if constexpr (N == 64) {
-    stockham_pass<64, 8, TX, NT, INV>(s, tw, 1);
-    stockham_pass<64, 8, TX, NT, INV>(s, tw, 8);
-  } else if constexpr (N == 128) {
-    stockham_pass<128, 16, TX, NT, INV>(s, tw, 1);
-    stockham_pass<128, 8, TX, NT, INV>(s, tw, 16);
-  } else if constexpr (N == 256) {
-    stockham_pass<256, 16, TX, NT, INV>(s, tw, 1);
-    stockham_pass<256, 16, TX, NT, INV>(s, tw, 16);
-  } else if constexpr (N == 512) {
-    stockham_pass<512, 8, TX, NT, INV>(s, tw, 1);
-    stockham_pass<512, 8, TX, NT, INV>(s, tw, 8);
-    stockham_pass<512, 8, TX, NT, INV>(s, tw, 64);
-  }
+template <int N, int TX, int NT, bool INV, typename C>
+__device__ __forceinline__ void fft_lds(C* s, const C* tw) {
+  constexpr int R0 = N == 16 ? 4 : 8, N1 = N / R0;                  // 8: one pass of radix 8
+  constexpr int R1 = N1 == 1 ? 1 : (N1 % 8 == 0 ? 8 : 4), N2 = N1 / R1;
+  stockham_pass<N, R0, TX, NT, INV>(s, tw, 1);
+  if constexpr (R1 > 1) stockham_pass<N, R1, TX, NT, INV>(s, tw, R0);
+  if constexpr (N2 > 1) stockham_pass<N, N2, TX, NT, INV>(s, tw, R0 * R1);
 }
 
 // ---------------------------------------------------------------------------
-// The same transform with its first pass fed from registers and its last
-// pass left in registers: only the passes in between go through LDS.
+// The transform with its first pass fed from registers and its last pass
+// left in registers: only the passes in between go through LDS.
 //   input  item (it, r) of thread t, g = t + it*NT: row g/TX + r*(N/R0),
 //          column g%TX;
 //   output item (it, r): row out_row(g, r), column g%TX.
@@ -386,10 +368,3 @@ __device__ __forceinline__ void fft_regs(float2 (&v0)[IT0_][R0_], float2 (&vo)[I
     }
   }
 }
-
-// Columns per workgroup for a transform of length N: keeps the LDS tile at
-// N*TX*8 bytes <= 32 KB with TX in [4, 32].
-template <int N>
-struct ColTile {
-  static constexpr int TX = (N >= 512) ? 8 : (N >= 256 ? 16 : (N >= 128 ? 32 : 32));
-};

@@ -89,15 +89,20 @@ __device__ __forceinline__ int xcd_tile(int b, int nt) { return nt % 8 == 0 ? (b
 enum { NORMAL_MEAN = 0, NORMAL_ISTA = 1 };
 hipError_t launch_normal_lines(const NormalArgs& a, int mode, int images, int groups, hipStream_t s);
 hipError_t launch_normal_rows(const NormalArgs& a, hipStream_t s);  // the mean
-__global__ void k_cg_begin(const float2* src, int nsum, long part_stride, float2* s, float2* x, long n, double* nrm,
+__global__ void k_cg_begin(const double2* src, int nsum, long part_stride, float2* s, float2* x, long n, double* nrm,
                            const DevState* st);
 __global__ void k_cg_step(CgStepArgs a);
 __global__ void k_cgls_sum(const float2* src, int nsum, long part_stride, float2* s, long n, double* nrm,
                            const FrameCg* cg, const DevState* st);
 __global__ void k_cg_end(CgArgs a, const DevState* st);
-__global__ void k_line_sum(const float2* yu, const int32_t* loc_ptr, int nc, int nx, float2* T, const DevState* st);
+// the mean's right-hand side in FP64: the frames' sums T[c][ky][x], then the adjoint in
+// place (cgs: coils per group, whose first plane receives the group's part)
+__global__ void k_line_sum(const float2* yu, const int32_t* loc_ptr, int nc, int nx, double2* T, const DevState* st);
 __global__ void k_loc_sum(const float2* y, const int2* pairs, const int32_t* loc_ptr, long n, int nc, int m_max,
-                          float2* T, const DevState* st);
+                          double2* T, const DevState* st);
+hipError_t launch_rhs_rows(double2* T, int nx, int nrows, const DevState* st, hipStream_t s);
+hipError_t launch_rhs_cols(double2* T, const float2* coils, int nx, int ny, int nc, int* cgs, const DevState* st,
+                           hipStream_t s);
 hipError_t launch_expand(const float2* U, const float2* B, const float2* zbar, const float2* E, long n, int q, int r,
                          float2* Z, const DevState* st, hipStream_t s);
 

@@ -21,6 +21,8 @@
 // runs in a fixed order.  The scalars of an iteration live in one of two
 // slots: the operator's launch of iteration t reads slot t - 1 and writes slot
 // t, so that no workgroup reads what another one of its launch writes.
+#include <algorithm>
+
 #include "kernels_mri.hpp"
 
 namespace ag {
@@ -33,7 +35,7 @@ namespace ag {
 //                <p, w> goes to dot
 //   NORMAL_ISTA  w = A_k^H (y_k - A_k s) for image k = s
 // Bound by the transforms' arithmetic and their LDS exchanges.  Mean image,
-// 256 x 256, 12 coils: 900 -> 159 us with its ten iterations (a CG iteration
+// 256 x 256, 12 coils: 900 -> 167 us with its ten iterations (a CG iteration
 // from eight launches, 90 us, to two).  ISTA, 48 frames of 128 x 128, 8 coils:
 // 26 us (27.7 with the data requested where it is used, under a branch, and the
 // next coil after its transform; the image values in LDS leave the registers
@@ -278,28 +280,29 @@ __global__ __launch_bounds__(256) void k_cgls_sum(const float2* src, int nsum, l
 }
 
 // ---------------------------------------------------------------------------
-// x = 0, s = the sum of nsum parts of the right-hand side (in place when
-// there is one), and each workgroup's share of ||s||^2.  Grid (NB, images).
+// x = 0, s = the sum of nsum FP64 parts of the right-hand side (rounded to FP32
+// once, here), and each workgroup's share of ||s||^2.  One image.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_cg_begin(const float2* src, int nsum, long part_stride, float2* s, float2* x,
+__global__ __launch_bounds__(256) void k_cg_begin(const double2* src, int nsum, long part_stride, float2* s, float2* x,
                                                   long n, double* nrm, const DevState* st) {
   __shared__ double sh[4];
-  const int img = blockIdx.y, tid = threadIdx.x;
+  const int tid = threadIdx.x;
   const bool bad = st->err != 0;
   double acc = 0.0;
   for (long i = (long)blockIdx.x * 256 + tid; i < n; i += (long)gridDim.x * 256) {
-    const long e = (long)img * n + i;
-    x[e] = make_float2(0.f, 0.f);
+    x[i] = make_float2(0.f, 0.f);
     if (bad) continue;
-    float2 v = src[e];
-    for (int g = 1; g < nsum; ++g) v = cadd(v, src[g * part_stride + e]);
-    if (s != src) s[e] = v;
+    double2 d = src[i];
+#pragma unroll 4
+    for (int g = 1; g < nsum; ++g) d = dadd(d, src[g * part_stride + i]);
+    const float2 v = d2f(d);
+    s[i] = v;
     acc += (double)v.x * v.x + (double)v.y * v.y;
   }
   acc = wave_sum(acc);
   if ((tid & 63) == 0) sh[tid >> 6] = acc;
   __syncthreads();
-  if (tid == 0) nrm[(long)img * gridDim.x + blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+  if (tid == 0) nrm[blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
 // alpha = gamma / ||A p||^2; x += alpha p; s -= alpha w; the workgroup's share of
@@ -341,32 +344,40 @@ __global__ void k_cg_end(CgArgs a, const DevState* st) {
 }
 
 // ---------------------------------------------------------------------------
-// the mean image's right-hand side: k-space sums over the frames (FP64), per
-// (row or location, coil), zero where no frame samples
+// the mean image's right-hand side A^H y = sum_c conj(s_c) F^H sum_k y_{k,c}: the
+// frames are summed in k-space and one adjoint carries the sum, in FP64 until
+// the image is rounded to FP32 (k_cg_begin).  An FP32 adjoint of every frame
+// averages its roundings out over the frames; an FP32 adjoint of their sum would
+// not, and the image would be 1.3 times as far from the 64-bit one (256 x 256,
+// 12 coils, 40 frames: 9.0e-7 against 6.8e-7, and 7.0e-7 with a frame at a time).
+// That size: sums 15 us, columns 13 us, 6 us more than an FP32 adjoint.
 // ---------------------------------------------------------------------------
-// line masks: the hybrid data's lines, yu as built at setup; grid (ny, nc)
-__global__ __launch_bounds__(256) void k_line_sum(const float2* yu, const int32_t* loc_ptr, int nc, int nx, float2* T,
+// k-space sums over the frames, per (row or location, coil), zero where no frame
+// samples.  Line masks: the hybrid data's lines, yu as built at setup; grid (ny, nc)
+__global__ __launch_bounds__(256) void k_line_sum(const float2* yu, const int32_t* loc_ptr, int nc, int nx, double2* T,
                                                   const DevState* st) {
   if (st->err) return;
   const int ky = blockIdx.x, c = blockIdx.y;
-  const int p0 = loc_ptr[ky], np = loc_ptr[ky + 1] - p0;
-  const float2* src = yu + (long)nc * nx * p0 + (long)c * np * nx;
-  float2* dst = T + ((long)c * gridDim.x + ky) * nx;
+  const int first = loc_ptr[ky], np = loc_ptr[ky + 1] - first;
+  const float2* src = yu + (long)nc * nx * first + (long)c * np * nx;
+  double2* dst = T + ((long)c * gridDim.x + ky) * nx;
   for (int x = threadIdx.x; x < nx; x += 256) {
-    double re = 0.0, im = 0.0;
-#pragma unroll 8
-    for (int p = 0; p < np; ++p) {
-      const float2 v = src[(long)p * nx + x];
-      re += v.x;
-      im += v.y;
+    double2 s = make_double2(0.0, 0.0);
+    for (int p0 = 0; p0 < np; p0 += 8) {  // eight loads in flight, the last batch's too
+      float2 v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = src[(long)min(p0 + i, np - 1) * nx + x];
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (p0 + i < np) s = dadd(s, f2d(v[i]));
     }
-    dst[x] = make_float2((float)re, (float)im);
+    dst[x] = s;
   }
 }
 
 // general masks: the (frame, sample) pairs of each location; grid (locations / 256, nc)
 __global__ __launch_bounds__(256) void k_loc_sum(const float2* y, const int2* pairs, const int32_t* loc_ptr, long n,
-                                                 int nc, int m_max, float2* T, const DevState* st) {
+                                                 int nc, int m_max, double2* T, const DevState* st) {
   if (st->err) return;
   const long loc = (long)blockIdx.x * 256 + threadIdx.x;
   const int c = blockIdx.y;
@@ -374,15 +385,93 @@ __global__ __launch_bounds__(256) void k_loc_sum(const float2* y, const int2* pa
   const int p0 = loc_ptr[loc], p1 = loc_ptr[loc + 1];
   const float2* yc = y + (long)c * m_max;
   const long ks = (long)nc * m_max;
-  double re = 0.0, im = 0.0;
+  double2 s = make_double2(0.0, 0.0);
 #pragma unroll 4
   for (int p = p0; p < p1; ++p) {
     const int2 ke = pairs[p];
-    const float2 v = yc[ke.x * ks + ke.y];
-    re += v.x;
-    im += v.y;
+    s = dadd(s, f2d(yc[ke.x * ks + ke.y]));
   }
-  T[(long)c * n + loc] = make_float2((float)re, (float)im);
+  T[(long)c * n + loc] = s;
+}
+
+// the FP64 adjoint's tile: CT columns (or rows) of N points in 32 KB of LDS
+template <int N>
+constexpr int RHS_CT = N == 512 ? 4 : N == 256 ? 8 : 16;
+
+template <int N>
+__device__ __forceinline__ void rhs_twiddles(double2* tw) {
+  for (int e = threadIdx.x; e < N; e += 256) {
+    double sv, cv;
+    sincospi(2.0 * (double)e / (double)N, &sv, &cv);
+    tw[e] = make_double2(cv, -sv);
+  }
+}
+
+// general masks: F_x^H of T's nrows rows in place, CT rows per workgroup
+template <int N>
+__global__ __launch_bounds__(256) void k_rhs_rows(double2* T, int nrows, const DevState* st) {
+  constexpr int CT = RHS_CT<N>;
+  __shared__ double2 s[N * CT], tw[N];
+  if (st->err) return;
+  const int row0 = blockIdx.x * CT;
+  for (int e = threadIdx.x; e < N * CT; e += 256) {
+    const int row = row0 + e / N;
+    s[(e % N) * CT + e / N] = row < nrows ? T[(long)row * N + e % N] : make_double2(0.0, 0.0);
+  }
+  rhs_twiddles<N>(tw);
+  __syncthreads();
+  fft_lds<N, CT, 256, true>(s, tw);
+  const double sc = 1.0 / sqrt((double)N);
+  for (int e = threadIdx.x; e < N * CT; e += 256) {
+    const int row = row0 + e / N;
+    const double2 v = s[(e % N) * CT + e / N];
+    if (row < nrows) T[(long)row * N + e % N] = make_double2(v.x * sc, v.y * sc);
+  }
+}
+
+// F_y^H of a tile of columns and the combine over a group's coils, in place: the
+// group's first coil plane receives its sum.  Grid (column tiles, coil groups).
+template <int N>
+__global__ __launch_bounds__(256) void k_rhs_cols(double2* T, const float2* coils, long n, int nx, int nc, int cgs,
+                                                  const DevState* st) {
+  constexpr int CT = RHS_CT<N>, EM = (N * CT + 255) / 256;
+  __shared__ double2 s[N * CT], tw[N];
+  if (st->err) return;
+  const int tid = threadIdx.x, x0 = blockIdx.x * CT, cb = blockIdx.y * cgs, ce = min(nc, cb + cgs);
+  // this thread's entries of the tile: offset in an image, -1 past its columns
+  int off[EM];
+  double2 v[EM], acc[EM];
+  float2 cv[EM];
+#pragma unroll
+  for (int i = 0; i < EM; ++i) {
+    const int e = tid + 256 * i, x = x0 + e % CT;
+    off[i] = e < N * CT && x < nx ? (e / CT) * nx + x : -1;
+    acc[i] = make_double2(0.0, 0.0);
+  }
+  auto load = [&](int c) {
+#pragma unroll
+    for (int i = 0; i < EM; ++i) v[i] = T[(long)c * n + max(off[i], 0)];
+  };
+  load(cb);
+  rhs_twiddles<N>(tw);
+  for (int c = cb; c < ce; ++c) {
+#pragma unroll
+    for (int i = 0; i < EM; ++i)
+      if (tid + 256 * i < N * CT) s[tid + 256 * i] = v[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < EM; ++i) cv[i] = coils[(long)c * n + max(off[i], 0)];
+    if (c + 1 < ce) load(c + 1);
+    fft_lds<N, CT, 256, true>(s, tw);
+#pragma unroll
+    for (int i = 0; i < EM; ++i)
+      if (off[i] >= 0) acc[i] = dadd(acc[i], djmul(f2d(cv[i]), s[tid + 256 * i]));
+    // (the next coil's values go where this thread has just read)
+  }
+  const double sc = 1.0 / sqrt((double)N);
+#pragma unroll
+  for (int i = 0; i < EM; ++i)
+    if (off[i] >= 0) T[(long)cb * n + off[i]] = make_double2(acc[i].x * sc, acc[i].y * sc);
 }
 
 // ---------------------------------------------------------------------------
@@ -404,6 +493,23 @@ hipError_t normal_rows_n(const NormalArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((k_normal_rows<N, TR, NT>), dim3((a.nc * a.ny + TR - 1) / TR), dim3(NT), 0, s, a);
   return hipGetLastError();
 }
+
+template <int N>
+hipError_t rhs_rows_n(double2* T, int nrows, const DevState* st, hipStream_t s) {
+  constexpr int CT = RHS_CT<N>;
+  hipLaunchKernelGGL((k_rhs_rows<N>), dim3((nrows + CT - 1) / CT), dim3(256), 0, s, T, nrows, st);
+  return hipGetLastError();
+}
+
+template <int N>
+hipError_t rhs_cols_n(double2* T, const float2* coils, long n, int nx, int nc, int* cgs, const DevState* st,
+                      hipStream_t s) {
+  // coil groups for about two workgroups per compute unit
+  const int tiles = (nx + RHS_CT<N> - 1) / RHS_CT<N>, want = std::max(1, std::min(nc, 512 / tiles));
+  *cgs = (nc + want - 1) / want;
+  hipLaunchKernelGGL((k_rhs_cols<N>), dim3(tiles, (nc + *cgs - 1) / *cgs), dim3(256), 0, s, T, coils, n, nx, nc, *cgs, st);
+  return hipGetLastError();
+}
 }  // namespace
 
 #define NORMAL_DISPATCH(fn, N, ...)          \
@@ -422,5 +528,12 @@ hipError_t launch_normal_lines(const NormalArgs& a, int mode, int images, int gr
   NORMAL_DISPATCH(lines_n, a.ny, a, mode, images, groups, s);
 }
 hipError_t launch_normal_rows(const NormalArgs& a, hipStream_t s) { NORMAL_DISPATCH(normal_rows_n, a.nx, a, s); }
+hipError_t launch_rhs_rows(double2* T, int nx, int nrows, const DevState* st, hipStream_t s) {
+  NORMAL_DISPATCH(rhs_rows_n, nx, T, nrows, st, s);
+}
+hipError_t launch_rhs_cols(double2* T, const float2* coils, int nx, int ny, int nc, int* cgs, const DevState* st,
+                           hipStream_t s) {
+  NORMAL_DISPATCH(rhs_cols_n, ny, T, coils, (long)nx * ny, nx, nc, cgs, st, s);
+}
 
 }  // namespace ag

@@ -135,32 +135,29 @@ hipError_t adj_cols_in_place(altgdmin_ctx* c, float2* T) {
   return launch_cols_adj(c->p.ny, d, false, 1, c->stream);
 }
 
-// The mean image by CG: s_0 = A^H y from the frames' sum per k-space location,
-// then two launches per iteration (four for general masks).  Vectors: s in
-// v0, the directions in v1 and v2, the coil groups' parts of A^H A p in ci.
+// The mean image by CG: s_0 = A^H y from the frames' sum per k-space location (FP64,
+// in the workspace's temporary), then two launches per iteration (four for
+// general masks).  Vectors: s in v0, the directions in v1 and v2, the coil
+// groups' parts of A^H A p in ci.
 hipError_t mean_seq(altgdmin_ctx* c, double tol, int maxit, float2* x, const Aux& a, int* it_slot) {
   const altgdmin_params& p = c->p;
   hipStream_t s = c->stream;
   const long n = c->n;
   DevState* st = c->st();
+  double2* const T = c->at<double2>(c->o_T);  // nc coil images
+  int per = 1;
   if (c->lines) {
     hipLaunchKernelGGL(k_line_sum, dim3(p.ny, p.nc), dim3(256), 0, s, c->at<float2>(c->o_yh),
-                       c->at<int32_t>(c->o_locptr), p.nc, p.nx, a.ci, st);
+                       c->at<int32_t>(c->o_locptr), p.nc, p.nx, T, st);
   } else {
     hipLaunchKernelGGL(k_loc_sum, dim3((unsigned)((n + 255) / 256), p.nc), dim3(256), 0, s, c->y,
-                       c->at<int2>(c->o_pairs), c->at<int32_t>(c->o_locptr), n, p.nc, p.m_max, a.ci, st);
-    RowArgs ra{};
-    ra.src = ra.dst = a.ci;
-    ra.tw = c->at<float2>(c->o_twx);
-    ra.nrows = (long)p.nc * p.ny;
-    ra.scale = (float)(1.0 / sqrt((double)p.nx));
-    ra.st = st;
-    AGCHK(launch_rows(p.nx, ra, true, s));
+                       c->at<int2>(c->o_pairs), c->at<int32_t>(c->o_locptr), n, p.nc, p.m_max, T, st);
+    AGCHK(launch_rhs_rows(T, p.nx, p.nc * p.ny, st, s));
   }
   AGCHK(hipGetLastError());
-  AGCHK(adj_cols_in_place(c, a.ci));
+  AGCHK(launch_rhs_cols(T, c->coils, p.nx, p.ny, p.nc, &per, st, s));
   const int nb = cg_nb(c, 1);
-  hipLaunchKernelGGL(k_cg_begin, dim3(nb), dim3(256), 0, s, a.ci, p.nc, n, a.v0, x, n, a.part, st);
+  hipLaunchKernelGGL(k_cg_begin, dim3(nb), dim3(256), 0, s, T, (p.nc + per - 1) / per, per * n, a.v0, x, n, a.part, st);
   AGCHK(hipGetLastError());
   int cgs = 1;
   const int groups = c->lines ? normal_groups(c, 1, &cgs) : p.nc;

@@ -317,6 +317,9 @@ __device__ __forceinline__ double rcp_nr(double x) {
 // largest than 1e-8 of it are all that is left beside it; the result is the
 // weighted mean tr(M^p A) / tr(M^p) of A = M's eigenvalues.  Each squaring is one
 // short product in LDS, where a cyclic Jacobi takes r rotation rounds a sweep.
+// A matrix whose trace is not finite gives its largest diagonal entry: an
+// overflow stays infinite, and the factor of the step it leads to fails and is
+// reported (zero would pass for a stationary start).
 __device__ __forceinline__ double spectral_norm2(double2* M, double2* S, double2* A, int r) {
   const int tid = threadIdx.x, i = (tid >> 4) & 15, j = tid & 15;
   const bool in = tid < 256 && i < r && j < r;
@@ -328,7 +331,11 @@ __device__ __forceinline__ double spectral_norm2(double2* M, double2* S, double2
   };
   if (in) A[i * 16 + j] = M[i * 16 + j];
   double t = trace(M);
-  if (!(t > 0.0) || !isfinite(t)) return 0.0;  // the same in every thread
+  if (!(t > 0.0) || !isfinite(t)) {  // the same in every thread
+    double m = 0.0;
+    for (int k = 0; k < r; ++k) m = fmax(m, M[k * 16 + k].x);
+    return m;
+  }
   for (int it = 0; it < 30; ++it) {
     double2 v = make_double2(0.0, 0.0);
     if (in) {

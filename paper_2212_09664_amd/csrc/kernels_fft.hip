@@ -246,6 +246,14 @@ __global__ __launch_bounds__(NT * NG) void k_cols_adj(ColAdjArgs a) {
   __shared__ double s_red[NT / 64];
   const int tid = threadIdx.x, ng = tid / NT, lt = tid % NT;
   const int x0 = xcd_tile(blockIdx.x, gridDim.x) * CT, im = blockIdx.y, img = a.img0 + im, grp = blockIdx.z;
+  // a system starts from x = 0, also where an error keeps it from running
+  if (CGLS && a.first && grp == 0) {
+    float2* const xp = a.x + (long)img * a.n;
+    for (int e = tid; e < N * CT; e += NT * NG) {
+      const int x = x0 + e % CT;
+      if (x < a.nx) xp[(e / CT) * a.nx + x] = make_float2(0.f, 0.f);
+    }
+  }
   if (halted(a.st, 0)) return;  // (a mask that failed its checks at bind sets err)
   if (a.ista && a.ista->done) return;
   float al = 0.f;
@@ -259,19 +267,15 @@ __global__ __launch_bounds__(NT * NG) void k_cols_adj(ColAdjArgs a) {
       }
       al = (float)(a.cg[img].gamma / d);
     }
-    if (grp == 0) {  // x over this tile
+    if (!a.first && grp == 0) {  // x over this tile
       float2* const xp = a.x + (long)img * a.n;
-      const float2* const pp = a.first ? nullptr : a.p + (long)img * a.n;
+      const float2* const pp = a.p + (long)img * a.n;
       for (int e = tid; e < N * CT; e += NT * NG) {
         const int x = x0 + e % CT;
         if (x < a.nx) {
           const int o = (e / CT) * a.nx + x;
-          if (a.first) {
-            xp[o] = make_float2(0.f, 0.f);
-          } else {
-            const float2 xv = xp[o], pv = pp[o];
-            xp[o] = make_float2(xv.x + al * pv.x, xv.y + al * pv.y);
-          }
+          const float2 xv = xp[o], pv = pp[o];
+          xp[o] = make_float2(xv.x + al * pv.x, xv.y + al * pv.y);
         }
       }
     }

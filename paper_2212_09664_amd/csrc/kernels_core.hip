@@ -475,7 +475,8 @@ __device__ __forceinline__ void partials_sum(const double2* part, int f32, int n
 // k_stats_finish forms them on request.
 //
 // STEP_MODE_QR: U+ = CholeskyQR of src (the sum is the Gram of src alone, a
-// small ridge is added if it is numerically singular).  STEP_MODE_ETA (one
+// small ridge is added if it is numerically singular; U+ = src where an error
+// is pending or the factor fails all the same).  STEP_MODE_ETA (one
 // workgroup): only the step size is set.
 //
 // The factor's wave takes its entries straight from the sum (a lane's four
@@ -551,7 +552,16 @@ __global__ __launch_bounds__(256) void k_step_apply(QrSmallArgs a, ApplyArgs ap)
     s_eta = step ? eta0 : 0.0;
   }
   __syncthreads();
-  if (!s_ok) return;
+  auto keep_src = [&] {
+    if (step || ap.src == ap.U || p >= n) return;
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+      if (i < r) ap.U[(long)i * n + p] = u0[i];
+  };
+  if (!s_ok) {
+    keep_src();
+    return;
+  }
   if (step && !(s_eta > 0.0)) {  // first iteration: eta = eta_c / ||grad||_2 (with the guard and the cap)
     const int x = tid >> 4, y = tid & 15;
     if (x < r && y < r) W0[tid] = gram(r + x, r + y);
@@ -684,7 +694,11 @@ __global__ __launch_bounds__(256) void k_step_apply(QrSmallArgs a, ApplyArgs ap)
     }
   }
   __syncthreads();
-  if (!s_ok || p >= n) return;
+  if (!s_ok) {
+    keep_src();
+    return;
+  }
+  if (p >= n) return;
   // U+ R = U - eta grad for this pixel (forward substitution, 1 / R_jj on the diagonal)
   const float etaf = (float)eta;
   float2 un[RT];

@@ -311,13 +311,6 @@ hipError_t cholqr(altgdmin_ctx* c, const float2* src, float2* U) {
   return step_apply(c, qa, aa);
 }
 
-// the statistics that the last iteration left pending (the device knows
-// whether one did; a context that never iterated has none)
-hipError_t finish_stats(altgdmin_ctx* c) {
-  if (!c->iterated) return hipSuccess;
-  return launch_stats_finish(c->st(), c->at<double2>(c->o_stsrc), c->at<double>(c->o_cost), c->p.q, c->p.r, c->stream);
-}
-
 // b_k for every frame and the gradient at U (into the workspace's B and G)
 hipError_t gradient_pieces(altgdmin_ctx* c, int check_halt) {
   const altgdmin_params& p = c->p;
@@ -456,7 +449,6 @@ hipError_t qr_step_apply(altgdmin_ctx* c, float2* U, float2* U_prev) {
 }
 
 hipError_t one_iteration(altgdmin_ctx* c, float2* U, float2* U_prev) {
-  c->iterated = 1;
   hipError_t e = gradient_pieces(c, 1);
   if (e != hipSuccess) return e;
   return qr_step_apply(c, U, U_prev);
@@ -938,8 +930,6 @@ altgdmin_status altgdmin_set_eta(altgdmin_ctx* c, double eta) {
 altgdmin_status altgdmin_cost(altgdmin_ctx* c, const void* d_U, double* d_f) {
   if (!c || !d_U || !d_f) return ALTGDMIN_EINVAL;
   if (!c->bound || !c->y) return ALTGDMIN_ESTATE;
-  // the last iteration's statistics read cost_k, which the solve below overwrites
-  HIPCHK(finish_stats(c));
   HIPCHK(to_pixmajor(c, static_cast<const float2*>(d_U)));
   HIPCHK(fwd_transform(c, 0));
   HIPCHK(gram_solve(c, 0));
@@ -952,7 +942,6 @@ altgdmin_status altgdmin_gradient(altgdmin_ctx* c, const void* d_U, void* d_B, v
   if (!c || !d_U) return ALTGDMIN_EINVAL;
   if (!c->bound || !c->y) return ALTGDMIN_ESTATE;
   const altgdmin_params& p = c->p;
-  HIPCHK(finish_stats(c));
   HIPCHK(to_pixmajor(c, static_cast<const float2*>(d_U)));
   const BOut scope(c, d_B);  // the solve writes B to the caller's buffer too
   if (!d_G) {  // the LS step alone
@@ -985,7 +974,8 @@ altgdmin_status altgdmin_get_stats(altgdmin_ctx* c, altgdmin_stats* out) {
   if (!c || !out) return ALTGDMIN_EINVAL;
   if (!c->bound) return ALTGDMIN_ESTATE;
   DevState h;
-  HIPCHK(finish_stats(c));
+  // what the last iteration left pending (the device knows whether one did)
+  HIPCHK(launch_stats_finish(c->st(), c->at<double2>(c->o_stsrc), c->p.q, c->p.r, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
   HIPCHK(hipMemcpy(&h, c->st(), sizeof(DevState), hipMemcpyDeviceToHost));
   out->t = h.t;

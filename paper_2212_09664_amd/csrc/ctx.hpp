@@ -41,9 +41,6 @@ struct altgdmin_ctx {
   // set for the duration of one call: the caller's B buffer, which every
   // solve writes too
   float2* b_out = nullptr;
-  // an iteration was ever enqueued (never cleared: a captured one may be
-  // replayed without this code running)
-  int iterated = 0;
   int grad_parts;          // partial gradient arrays the adjoint writes
   int txx;                 // image columns per workgroup in the basis transforms
   size_t bytes;

@@ -471,8 +471,9 @@ __device__ __forceinline__ void partials_sum(const double2* part, int f32, int n
 // workgroup, and a workgroup that reads the new eta instead of the unset one
 // gets the value it would have computed (the same rule on the same sum,
 // bitwise); the stationary start halts every workgroup alike.  SD, the cost
-// and ||grad|| are then only reported: their r x r inputs are stored and
-// k_stats_finish forms them on request.
+// and ||grad|| are then only reported: their inputs (r x r matrices and the
+// frames' costs, which a later solve overwrites) are stored and k_stats_finish
+// forms them on request.
 //
 // STEP_MODE_QR: U+ = CholeskyQR of src (the sum is the Gram of src alone, a
 // small ridge is added if it is numerically singular; U+ = src where an error
@@ -698,6 +699,8 @@ __global__ __launch_bounds__(256) void k_step_apply(QrSmallArgs a, ApplyArgs ap)
     keep_src();
     return;
   }
+  if (blockIdx.x == 0 && step && a.commit_direct && tid >= 128 && tid - 128 < a.q)
+    reinterpret_cast<double*>(a.stats_src + 769)[tid - 128] = a.cost_k[tid - 128];
   if (p >= n) return;
   // U+ R = U - eta grad for this pixel (forward substitution, 1 / R_jj on the diagonal)
   const float etaf = (float)eta;
@@ -750,10 +753,9 @@ __global__ void k_step_commit(DevState* st, int exit_consec) {
 }
 
 // the statistics the fused step left pending (exit rule off): SD, f and
-// ||grad||_F of the last applied step, from its r x r inputs and the
-// per-frame costs (no solve has run since), with the fused step's own code
-__global__ __launch_bounds__(64) void k_stats_finish(DevState* st, const double2* src, const double* cost_k, int q,
-                                                     int r) {
+// ||grad||_F of the last applied step, from its stored inputs, with the fused
+// step's own code
+__global__ __launch_bounds__(64) void k_stats_finish(DevState* st, const double2* src, int q, int r) {
   __shared__ double2 UU[256], UG[256], Gh[16 * CHOL_LD], Tm[256];
   const int l = threadIdx.x;
   if (!st->stats_pending) return;
@@ -765,6 +767,7 @@ __global__ __launch_bounds__(64) void k_stats_finish(DevState* st, const double2
   const double2 et = src[768];
   wave_sync();
   const double fro = wave_sum(sd_row_sum(UU, UG, Gh, Tm, et.x, r, l));
+  const double* const cost_k = reinterpret_cast<const double*>(src + 769);
   double fv = 0.0;
   for (int k = l; k < q; k += 64) fv += cost_k[k];
   fv = wave_sum(fv);
@@ -776,8 +779,8 @@ __global__ __launch_bounds__(64) void k_stats_finish(DevState* st, const double2
   }
 }
 
-hipError_t launch_stats_finish(DevState* st, const double2* src, const double* cost_k, int q, int r, hipStream_t s) {
-  hipLaunchKernelGGL(k_stats_finish, dim3(1), dim3(64), 0, s, st, src, cost_k, q, r);
+hipError_t launch_stats_finish(DevState* st, const double2* src, int q, int r, hipStream_t s) {
+  hipLaunchKernelGGL(k_stats_finish, dim3(1), dim3(64), 0, s, st, src, q, r);
   return hipGetLastError();
 }
 

@@ -181,10 +181,11 @@ struct QrSmallArgs {
   DevState* st;
   int check_halt;
   int commit_direct;     // workgroup 0 commits t and eta itself (the exit rule is off)
-  double2* stats_src;    // with commit_direct: the r x r inputs of the deferred statistics (STATS_SRC entries)
+  double2* stats_src;    // with commit_direct: the inputs of the deferred statistics (STATS_SRC entries)
 };
 enum { STEP_MODE_STEP = 0, STEP_MODE_QR = 1, STEP_MODE_ETA = 2 };  // a step; CholeskyQR of U; the step size alone
-constexpr int STATS_SRC = 3 * 256 + 1;
+// U^H U, U^H G and L (16 x 16 each), (eta, ||grad||^2), then the costs of up to 128 frames
+constexpr int STATS_SRC = 3 * 256 + 1 + 64;
 
 struct ApplyArgs {
   const float2* src;     // n x r column-major basis to update (may be U)
@@ -391,7 +392,7 @@ __global__ void k_to_pixmajor(const float2* src, int r, long n, float2* dst);
 hipError_t launch_init_eig(const InitEigArgs& a, hipStream_t s);
 hipError_t launch_partials_total(const double2* part, int f32, int nblk, int nout, double2* total, hipStream_t s);
 hipError_t launch_step_apply(const QrSmallArgs& a, const ApplyArgs& ap, hipStream_t s);
-hipError_t launch_stats_finish(DevState* st, const double2* src, const double* cost_k, int q, int r, hipStream_t s);
+hipError_t launch_stats_finish(DevState* st, const double2* src, int q, int r, hipStream_t s);
 hipError_t launch_sum_partials(const double2* part, int nblk, int nout, double2* out, hipStream_t s);
 
 }  // namespace ag

@@ -96,6 +96,8 @@ size_t aux_layout(const altgdmin_ctx* c, char* base, Aux* a) {
   return off;
 }
 
+bool overlap(const float2* a, size_t an, const float2* b, size_t bn) { return a && b && a < b + bn && b < a + an; }
+
 bool aux_ok(const void* d_aux) { return d_aux && (reinterpret_cast<uintptr_t>(d_aux) & 255) == 0; }
 
 
@@ -467,8 +469,21 @@ altgdmin_status altgdmin_mean_noalloc(altgdmin_ctx* c, double tol, int32_t maxit
 altgdmin_status altgdmin_residual(altgdmin_ctx* c, const void* d_zbar, const void* d_X, void* d_yres, void* d_aux) {
   if (!c || !d_yres || !aux_ok(d_aux)) return ALTGDMIN_EINVAL;
   if (!c->bound || !c->y) return ALTGDMIN_ESTATE;
-  return map_hip(ag_host::forward_op(c, static_cast<const float2*>(d_X), static_cast<float2*>(d_yres),
-                                     static_cast<const float2*>(d_zbar), c->y));
+  const altgdmin_params& p = c->p;
+  const float2* X = static_cast<const float2*>(d_X);
+  const float2* zbar = static_cast<const float2*>(d_zbar);
+  float2* Y = static_cast<float2*>(d_yres);
+  const size_t yn = (size_t)p.q * p.nc * p.m_max;
+  if (overlap(Y, yn, X, (size_t)c->n * p.q) || overlap(Y, yn, zbar, c->n)) {
+    // the images share memory with the output, which the passes write before
+    // every image is read: z = X + zbar goes through the auxiliary workspace
+    Aux a;
+    aux_layout(c, static_cast<char*>(d_aux), &a);
+    HIPCHK(launch_expand(nullptr, nullptr, zbar, X, (long)c->n, p.q, p.r, a.v0, c->st(), c->stream));
+    X = a.v0;
+    zbar = nullptr;
+  }
+  return map_hip(ag_host::forward_op(c, X, Y, zbar, c->y));
 }
 
 altgdmin_status altgdmin_mec_cgls(altgdmin_ctx* c, const void* d_yres, int32_t iters, double tol, void* d_E,

@@ -12,7 +12,7 @@ namespace ag {
 // stays at 32 KB or less (512: three passes).
 template <int N> struct OpTile;
 template <> struct OpTile<8>   { static constexpr int CT = 64, NT = 64;  };
-template <> struct OpTile<16>  { static constexpr int CT = 64, NT = 64;  };
+template <> struct OpTile<16>  { static constexpr int CT = 16, NT = 64;  };
 template <> struct OpTile<32>  { static constexpr int CT = 32, NT = 128; };
 template <> struct OpTile<64>  { static constexpr int CT = 16, NT = 128; };
 template <> struct OpTile<128> { static constexpr int CT = 16, NT = 128; };

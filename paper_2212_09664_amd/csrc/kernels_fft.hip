@@ -80,6 +80,24 @@ __global__ __launch_bounds__(NT) void k_rows(RowArgs a) {
   }
 }
 
+// an image's sampled rows (distinct): their number and this thread's first are
+// requested when the list is made, before anything waits
+struct RowList {
+  const int32_t* rows;
+  int mk = 0, r0 = 0;
+  __device__ RowList(const int32_t* list, long stride, const int32_t* m_k, int img, int tid)
+      : rows(list ? list + img * stride : nullptr) {
+    if (!rows) return;
+    mk = m_k[img];
+    r0 = rows[min(tid, (int)stride - 1)];
+  }
+  // li[k-space row] = the line that holds it
+  template <int N, int NT>
+  __device__ void invert(int* li, int n_rows, int tid) const {
+    for (int l = tid; l < n_rows; l += NT) li[min(max(l == tid ? r0 : rows[l], 0), N - 1)] = l;
+  }
+};
+
 // ---------------------------------------------------------------------------
 // image columns -> k-space rows: F_y (s_c o image) for the coils of a group,
 // restricted to the image's sampled rows (or all rows).  Grid: column tiles,
@@ -98,9 +116,8 @@ __global__ __launch_bounds__(NT) void k_cols_fwd(ColFwdArgs a) {
   __shared__ double s_red[NT / 64];
   const int tid = threadIdx.x;
   const int x0 = xcd_tile(blockIdx.x, gridDim.x) * CT, im = blockIdx.y, img = a.img0 + im, grp = blockIdx.z;
-  if (halted(a.st, 0)) return;  // (a mask that failed its checks at bind sets err)
-  if (a.ista && a.ista->done) return;
   const int cb = grp * a.cgs, ce = min(a.nc, cb + a.cgs);
+  const RowList rl(a.rows, a.rows_img_stride, a.m_k, img, tid);
   // the tile's image values and the first coil's, from valid addresses
   // (columns past a narrow image and idle threads are zeroed below)
   int off[IT0];
@@ -128,6 +145,9 @@ __global__ __launch_bounds__(NT) void k_cols_fwd(ColFwdArgs a) {
       for (int q = 0; q < R0; ++q) pv[it][q] = make_float2(0.f, 0.f);
   }
   load(a.coils + (long)min(cb, a.nc - 1) * a.n, cv);
+  // the state is read once the first loads are in flight (their addresses are valid either way)
+  if (halted(a.st, 0)) return;  // (a mask that failed its checks at bind sets err)
+  if (a.ista && a.ista->done) return;
   if (a.add) {
     float2 zv[IT0][R0];
     load(a.add, zv);
@@ -164,10 +184,9 @@ __global__ __launch_bounds__(NT) void k_cols_fwd(ColFwdArgs a) {
   }
   __syncthreads();
   int n_rows = N;
-  if (a.rows) {  // the image's sampled rows (distinct)
-    n_rows = a.m_k[img] / a.nx;
-    const int32_t* rows = a.rows + (long)img * a.rows_img_stride;
-    for (int l = tid; l < n_rows; l += NT) s_li[min(max(rows[l], 0), N - 1)] = l;
+  if (a.rows) {
+    n_rows = rl.mk / a.nx;
+    rl.invert<N, NT>(s_li, n_rows, tid);
     __syncthreads();
   }
 #pragma unroll
@@ -189,12 +208,14 @@ __global__ __launch_bounds__(NT) void k_cols_fwd(ColFwdArgs a) {
     for (int it = 0; it < ITL; ++it) {
       const int g = tid + it * NT, x = x0 + GM::out_col(g);
       if (GM::out_ok(g) && x < a.nx) {
+        int u[RL];  // looked up together: a lookup before each store would wait on its own
+#pragma unroll
+        for (int q = 0; q < RL; ++q) u[q] = s_li[GM::out_row(g, q)];
 #pragma unroll
         for (int q = 0; q < RL; ++q) {
-          const int u = s_li[GM::out_row(g, q)];
-          if (u >= 0) {
+          if (u[q] >= 0) {
             const float2 v = cscale(vo[it][q], a.scale);
-            dst[(long)u * a.nx + x] = v;
+            dst[(long)u[q] * a.nx + x] = v;
             if constexpr (CG) dot += (double)v.x * v.x + (double)v.y * v.y;
           }
         }
@@ -231,7 +252,11 @@ __global__ __launch_bounds__(NT) void k_cols_fwd(ColFwdArgs a) {
 // transform.  512 x 512, 16 coils, 24 frames: 218 us and the forward columns
 // 208 us (578 and 301 us with every radix pass through LDS), bound by the
 // radix arithmetic.  Each workgroup runs NG groups of NT threads on alternate coils,
-// whose sums meet in LDS: the waves that one tile of columns can keep busy.
+// whose sums meet in LDS: the waves that one tile of columns can keep busy.  A
+// coil in turn costs a round trip to memory, 2.5 us, so the short columns (one or
+// two waves a tile) take up to eight coils at once.  32 frames of 16 x 16, 8
+// coils: 7.5 us for the adjoint with its row pass; 26.6 us with one group and 16
+// rows in a thread's registers, 12.4 us with every pass through LDS.
 // CGLS: see ColAdjArgs (alpha from the shares of ||A p||^2, every wave the same).
 // ---------------------------------------------------------------------------
 template <int N, int CT, int NT, int NG, bool CGLS>
@@ -254,6 +279,7 @@ __global__ __launch_bounds__(NT * NG) void k_cols_adj(ColAdjArgs a) {
       if (x < a.nx) xp[(e / CT) * a.nx + x] = make_float2(0.f, 0.f);
     }
   }
+  const RowList rl(a.rows, a.rows_img_stride, a.m_k, img, tid);
   if (halted(a.st, 0)) return;  // (a mask that failed its checks at bind sets err)
   if (a.ista && a.ista->done) return;
   float al = 0.f;
@@ -286,9 +312,7 @@ __global__ __launch_bounds__(NT * NG) void k_cols_adj(ColAdjArgs a) {
   }
   __syncthreads();
   if (a.rows) {
-    const int n_rows = a.m_k[img] / a.nx;
-    const int32_t* rows = a.rows + (long)img * a.rows_img_stride;
-    for (int l = tid; l < n_rows; l += NT * NG) s_li[min(max(rows[l], 0), N - 1)] = l;  // distinct
+    rl.invert<N, NT * NG>(s_li, rl.mk / a.nx, tid);
     __syncthreads();
   }
   float2 acc[ITL][RL];
@@ -328,17 +352,23 @@ __global__ __launch_bounds__(NT * NG) void k_cols_adj(ColAdjArgs a) {
       }
     }
   };
-  if (cb + ng < ce) fetch(cb + ng);
+  // (with a whole column in its registers a thread has none for the next coil's)
+  constexpr bool AHEAD = FftPlan<N>::P > 1;
+  if (AHEAD && cb + ng < ce) fetch(cb + ng);
   // every group of threads runs the same number of rounds (the transforms'
   // barriers are the workgroup's); one past the last coil adds nothing
   for (int c0 = cb; c0 < ce; c0 += NG) {
     const int c = c0 + ng;
     float2 v0[IT0][R0], vo[ITL][RL];
+    if (!AHEAD) {
+      if (c >= ce) break;  // (one pass: no barriers to reach)
+      fetch(c);
+    }
 #pragma unroll
     for (int it = 0; it < IT0; ++it)
 #pragma unroll
       for (int q = 0; q < R0; ++q) v0[it][q] = c < ce ? kv[it][q] : make_float2(0.f, 0.f);
-    if (c + NG < ce) fetch(c + NG);
+    if (AHEAD && c + NG < ce) fetch(c + NG);
     fft_regs<N, CT, NT, true, true>(v0, vo, s[ng], s_tw);
     // the coil values at the output rows come from the cache (every image
     // reads the same maps); loading them one coil ahead cost more in
@@ -357,7 +387,7 @@ __global__ __launch_bounds__(NT * NG) void k_cols_adj(ColAdjArgs a) {
     }
   }
   if constexpr (NG > 1) {  // groups 1.. leave their sums in their (now free) LDS tiles
-    if (ng > 0) {
+    if (ng > 0 && ng < ce - cb) {
 #pragma unroll
       for (int it = 0; it < ITL; ++it)
 #pragma unroll
@@ -365,8 +395,8 @@ __global__ __launch_bounds__(NT * NG) void k_cols_adj(ColAdjArgs a) {
     }
     __syncthreads();
     if (ng == 0) {
-#pragma unroll
-      for (int g2 = 1; g2 < NG; ++g2)
+#pragma unroll 1  // (one group's sums in registers at a time)
+      for (int g2 = 1; g2 < min(NG, ce - cb); ++g2)
 #pragma unroll
         for (int it = 0; it < ITL; ++it)
 #pragma unroll
@@ -577,7 +607,7 @@ hipError_t fwd_n(const ColFwdArgs& a, bool cg, int images, hipStream_t st) {
 template <int N>
 hipError_t adj_n(const ColAdjArgs& a, bool cgls, int images, hipStream_t st) {
   constexpr int CT = OpTile<N>::CT, NT = OpTile<N>::NT;
-  constexpr int NG = N >= 64 ? 2 : 1;
+  constexpr int NG = N >= 64 ? 2 : N == 32 ? 4 : 8;
   const dim3 grid((a.nx + CT - 1) / CT, images, (a.nc + a.cgs - 1) / a.cgs);
   if (a.cgs == 1) {  // one coil per workgroup: one group of threads
     if (cgls) hipLaunchKernelGGL((k_cols_adj<N, CT, NT, 1, true>), grid, dim3(NT), 0, st, a);

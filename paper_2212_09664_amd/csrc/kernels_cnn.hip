@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void k_cnn_pack(CnnLayers a) {
 }
 
 // ---------------------------------------------------------------------------
-// convolution as implicit GEMM: grid (tiles of TW x TH = 256 pixels, batch),
+// convolution as implicit GEMM: grid (tiles of TW x TH = 256 or 64 pixels, batch),
 // 256 threads; a wave computes TH / 4 tile rows, 16 pixels of a row per
 // matrix-core product, for all output channels (<= 32).  Per chunk of 32
 // input channels the tile's inputs (with the halo) are staged once as BF16
@@ -563,6 +563,16 @@ hipError_t launch_cnn_pack(const CnnLayers& a, hipStream_t s) {
 }
 
 hipError_t launch_conv(const ConvArgs& a, int batch, hipStream_t s) {
+  // tiles of 64 pixels up to four of them a compute unit: a quarter of the
+  // work a workgroup and four times the workgroups, where the larger tiles
+  // leave the chip idle.  A forward pass in either, us: one sequence of 64 x 64
+  // 29 / 55, 128 x 128 35 / 70, 256 x 256 (1,024 tiles) 63 / 78; two of 256 x 256
+  // 106 / 92, 16 of 64 x 64 (1,024) 51 / 63, eight of 128 x 128 (2,048) 105 / 98.
+  const long small = (long)((a.H + 3) / 4) * ((a.W + 15) / 16);
+  if (small * batch <= 1024) {
+    hipLaunchKernelGGL((k_conv<16, 4>), dim3((unsigned)small, batch), dim3(256), 0, s, a);
+    return hipGetLastError();
+  }
   // the tile whose padded image is the smallest; among equals the widest,
   // which writes whole cache lines (128 x 128, 16 sequences, 96 channels in:
   // 64 x 4 54 us, 32 x 8 64 us, 16 x 16 66 us; 32 channels in: 28, 31 and 29 us)

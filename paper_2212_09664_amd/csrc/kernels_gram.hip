@@ -80,6 +80,13 @@ __global__ __launch_bounds__(256) void k_build_lines(const float2* yh, const int
 template <typename T, int TR, int NS>
 __global__ __launch_bounds__(256) void k_gram_lines_mma(GramLinesArgs a) {
   using M = Mma<T>;
+  // With one step a batch up to rank 8 in FP32, ROCm 7.2's compiler pairs the
+  // LDS stores of the P tile's fourth and the h tile's first accumulator as a
+  // ds_write2_b32 at base + 32 bytes with offset0 4 (48 bytes) where 40 is meant
+  // (192 bytes): the offset of 48 dwords taken for 48 bytes.  The Gram is wrong.
+  // The instantiations in use store at the offsets written here (in their
+  // assembly, and tests over every form).
+  static_assert(TR > 1 || NS > 1, "miscompiled: the P tile's fourth accumulator is stored at the wrong offset");
   constexpr int NP = TR * (TR + 1) / 2, NT = NP + TR;  // tiles of P and, after them, of h
   __shared__ T red[NT * 256], scr[4 * NT * 256];
   const int g = blockIdx.y;

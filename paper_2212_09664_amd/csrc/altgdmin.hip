@@ -52,15 +52,13 @@ void carve(altgdmin_ctx* c) {
   c->o_bitmap = take(sizeof(uint32_t) * (size_t)c->n_loc * c->nw);
   c->o_locptr = take(sizeof(int32_t) * (size_t)(c->n_loc + 1));
   c->o_loc2unit = take(sizeof(int32_t) * (size_t)c->n_loc);
-  c->o_unitloc = take(sizeof(int32_t) * (size_t)c->n_loc);
-  c->o_unitspan = take(sizeof(int2) * (size_t)c->n_loc);
   c->o_bcp = take(sizeof(float2) * (size_t)q * c->width * r);
   c->o_Uc = take(sizeof(float2) * (size_t)n * r);
   c->o_fcmp = take(sizeof(double) * 4);  // the two costs compared, then the error snapshot
-  // Gram work list: at most ceil(q/8) items per line, and at least one entry per
-  // workgroup of the Gram launch (ny + 64 of them)
-  c->o_gwork = take(sizeof(int4) * ((size_t)c->n_loc * ((q + 7) / 8) + (c->lines ? p.ny + 64 : 0)));
-  c->o_lineord = take(sizeof(int4) * (size_t)c->n_loc);  // the fold's line order, most pairs first
+  // line masks: the Gram's work list (an entry per workgroup of its launch) and
+  // the fold's line order, most pairs first
+  c->o_gwork = take(c->lines ? sizeof(int4) * (size_t)gram_items_bound(c) : 0);
+  c->o_lineord = take(c->lines ? sizeof(int4) * (size_t)c->n_loc : 0);
   c->o_planes = take(sizeof(double) * 256);
   c->o_coilb = take(sizeof(float2) * (size_t)n * nc);
   c->o_yg = take(c->lines ? sizeof(float2) * 8 * (size_t)gram_items_bound(c) * nc * p.nx : 0);
@@ -103,9 +101,7 @@ void carve(altgdmin_ctx* c) {
   else
     tb += sizeof(float2) * (size_t)c->kc * nc * n;
   tb = std::max(tb, sizeof(double2) * (size_t)nc * n);
-  c->T_bytes = tb;
   c->o_T = take(tb);
-  c->o_end = off;
   c->bytes = off;
 }
 
@@ -157,8 +153,6 @@ BasisArgs basis_args(altgdmin_ctx* c, int check_halt) {
   b.cgs = c->adj_cgs;
   b.part_stride = (long)c->n * p.r;
   if (c->lines) {
-    b.rows = c->at<int32_t>(c->o_unitloc);
-    b.n_rows_ptr = &c->st()->n_units;
     b.row_unit = c->at<int32_t>(c->o_loc2unit);
   }
   b.tw = c->at<float2>(c->o_twy);
@@ -193,12 +187,8 @@ hipError_t gram_solve(altgdmin_ctx* c, int check_halt) {
   if (c->lines) {
     GramLinesArgs g{};
     g.W = c->at<float2>(c->o_W);
-    g.yu = c->at<float2>(c->o_yh);
     g.yg = c->at<float2>(c->o_yg);
     g.items = c->at<int4>(c->o_gwork);
-    g.pairs = c->at<int2>(c->o_pairs);
-    g.loc_ptr = c->at<int32_t>(c->o_locptr);
-    g.unit_loc = c->at<int32_t>(c->o_unitloc);
     g.nc = p.nc;
     g.r = p.r;
     g.nx = p.nx;
@@ -235,7 +225,6 @@ hipError_t gram_solve(altgdmin_ctx* c, int check_halt) {
   SolveArgs s{};
   s.P = c->at<double2>(c->o_P);
   s.hp = c->at<double2>(c->o_hp);
-  s.mask = c->mask;
   s.m_k = c->m_k;
   s.pair_of = c->at<int32_t>(c->o_pairof);
   s.unit_of = c->at<int32_t>(c->o_unitof);
@@ -755,8 +744,6 @@ altgdmin_status altgdmin_set_problem(altgdmin_ctx* c, const void* d_coils, const
   b.bitmap = c->at<uint32_t>(c->o_bitmap);
   b.loc_ptr = c->at<int32_t>(c->o_locptr);
   b.loc2unit = c->at<int32_t>(c->o_loc2unit);
-  b.unit_loc = c->at<int32_t>(c->o_unitloc);
-  b.unit_span = c->at<int2>(c->o_unitspan);
   b.pairs = c->at<int2>(c->o_pairs);
   b.pair_of = c->at<int32_t>(c->o_pairof);
   b.unit_of = c->at<int32_t>(c->o_unitof);

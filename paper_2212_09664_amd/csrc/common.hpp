@@ -19,12 +19,7 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
 __device__ __forceinline__ float2 cjmul(float2 a, float2 b) {
   return make_float2(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x);
 }
-// a * conj(b)
-__device__ __forceinline__ float2 cmulj(float2 a, float2 b) {
-  return make_float2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
-}
 __device__ __forceinline__ float2 cscale(float2 a, float s) { return make_float2(a.x * s, a.y * s); }
-__device__ __forceinline__ float cabs2(float2 a) { return a.x * a.x + a.y * a.y; }
 // acc + a * b and acc + a * conj(b) as two fused multiply-adds per part
 // (cadd(acc, cmul(a, b)) costs six instructions: the sum is rounded apart)
 __device__ __forceinline__ float2 cfma(float2 acc, float2 a, float2 b) {

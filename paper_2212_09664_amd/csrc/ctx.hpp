@@ -53,10 +53,9 @@ struct altgdmin_ctx {
   hipStream_t stream = nullptr;
   int bound = 0, initialized = 0;
   // workspace carve
-  size_t o_st, o_twx, o_twy, o_bitmap, o_locptr, o_loc2unit, o_unitloc, o_pairs, o_pairof, o_yh, o_ysq,
-      o_cost, o_W, o_K, o_P, o_hp, o_B, o_G, o_qpart, o_qtot, o_Vs, o_T, o_Ui, o_unitof, o_imap, o_unitspan, o_bcp, o_Uc,
-      o_fcmp, o_planes, o_gwork, o_lineord, o_coilb, o_yg, o_ysqp, o_stsrc, o_end;
-  size_t T_bytes;
+  size_t o_st, o_twx, o_twy, o_bitmap, o_locptr, o_loc2unit, o_pairs, o_pairof, o_yh, o_ysq,
+      o_cost, o_W, o_K, o_P, o_hp, o_B, o_G, o_qpart, o_qtot, o_Vs, o_T, o_Ui, o_unitof, o_imap, o_bcp, o_Uc,
+      o_fcmp, o_planes, o_gwork, o_lineord, o_coilb, o_yg, o_ysqp, o_stsrc;
   // timing
   int timed = TK_NONE;
   std::vector<hipEvent_t> ev;

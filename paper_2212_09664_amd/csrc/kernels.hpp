@@ -40,7 +40,7 @@ struct CgArgs {
 // ISTA (MEC-2)
 struct IstaState {
   double omega, last_change;
-  int32_t iters, done, stop_next, pad;
+  int32_t iters, done;
 };
 
 struct RowArgs {

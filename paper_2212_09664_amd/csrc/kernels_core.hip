@@ -1,8 +1,5 @@
-// altGDmin kernels other than the transforms: the inverse sampling map,
-// per-frame Gram / right-hand side (the LS step of Algorithm 2), the batched
-// r x r Cholesky solves, the gradient fold, the Gram of the QR step, the
-// small dense r x r / q x q work (Cholesky, triangular inverse, Jacobi
-// eigensolver) and the spectral-initialisation helpers.
+// The index tables of a bound problem, the QR step fused with the update, and
+// the spectral initialisation's q x q eigenproblem with the helpers around it.
 #include "kernels_core.hpp"
 
 namespace ag {
@@ -169,8 +166,6 @@ __global__ __launch_bounds__(1024) void k_bind_lines(BindArgs a) {
     s_ptr[tid] = pc;
     s_unit[tid] = c > 0 ? pu : -1;
     if (c > 0) {
-      a.unit_loc[pu] = tid;
-      a.unit_span[pu] = make_int2(pc, c);  // the unit's samples: pairs [pc, pc + c)
       s_np[pu] = c;
       s_p0[pu] = pc;
     }
@@ -214,8 +209,6 @@ __global__ __launch_bounds__(1024) void k_bind_index(BindArgs a) {
   const int nw = a.nw, n_loc = a.n_loc;
   int32_t* const loc_ptr = a.loc_ptr;
   int32_t* const loc2unit = a.loc2unit;
-  int32_t* const unit_loc = a.unit_loc;
-  int2* const unit_span = a.unit_span;
   constexpr int LPT = 1;  // locations per thread and tile (4: slower, the loads less coalesced)
   __shared__ int s_wc[16], s_wu[16];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -262,8 +255,6 @@ __global__ __launch_bounds__(1024) void k_bind_index(BindArgs a) {
         loc_ptr[l] = pc;
         if (c > 0) {
           loc2unit[l] = pu;
-          unit_loc[pu] = l;
-          unit_span[pu] = make_int2(pc, c);  // the unit's samples: pairs [pc, pc + c)
           ++pu;
         } else {
           loc2unit[l] = -1;
@@ -366,13 +357,6 @@ __device__ __forceinline__ float2 rfac_entry(const double2* L, int r, int e) {
   return make_float2(0.f, 0.f);
 }
 
-// ===========================================================================
-// spectral initialisation: eigen-decomposition of X_0^H X_0 (q x q) and the
-// scaled top-r eigenvectors V_r Sigma_r^{-1}, so that X_0 V_r Sigma_r^{-1}
-// are the top-r left singular vectors of X_0.
-// ===========================================================================
-// IN_LDS: matrix and eigenvectors in dynamic LDS (q <= 64; the accesses are
-// then LDS instructions), else in the workspace
 // ||U^H U+||_F^2 = ||(U^H U - eta U^H G) R^{-1}||_F^2, lanes l < r taking
 // row l by forward substitution with R = L^H (L in Gh, row pitch CHOL_LD;
 // x is a row scratch of stride 16); the caller sums over the wave.  The
@@ -819,9 +803,6 @@ hipError_t launch_step_apply(const QrSmallArgs& a, const ApplyArgs& ap, hipStrea
     hipLaunchKernelGGL(k_step_commit, dim3(1), dim3(64), 0, s, a.st, a.exit_consec);
   return hipGetLastError();
 }
-
-// one-wave reductions
-__device__ __forceinline__ double2 wave_sum2(double2 v) { return make_double2(wave_sum(v.x), wave_sum(v.y)); }
 
 // Number of eigenvalues below each of E points of the real symmetric
 // tridiagonal (d, e), scaled so that |d|, |e| <= 1 and padded to a multiple of

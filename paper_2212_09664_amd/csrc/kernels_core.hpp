@@ -20,8 +20,7 @@ struct BindArgs {
   double trunc_c;
   float2 *twx, *twy, *coilb;
   uint32_t* bitmap;      // [location][nw]: a bit per frame
-  int32_t *loc_ptr, *loc2unit, *unit_loc;
-  int2* unit_span;
+  int32_t *loc_ptr, *loc2unit;
   int2* pairs;           // (frame, entry) by location
   int32_t *pair_of, *unit_of;  // [frame][width]
   int32_t* imap;         // general masks, else null: [frame][location] -> entry, -1
@@ -32,12 +31,8 @@ struct BindArgs {
 
 struct GramLinesArgs {
   const float2* W;       // [c][u][x][j], ua rows per coil
-  const float2* yu;      // per-line data [c][p][x]
   const float2* yg;      // per work item: [c][x][8 samples]
   const int4* items;     // work items (line, sample tile of 8, first pair, pair count)
-  const int2* pairs;
-  const int32_t* loc_ptr;
-  const int32_t* unit_loc;
   int nc, r, nx, ua;
   int cg;                // coils per workgroup (coil group)
   long npairs;           // allocated pairs per group in hp
@@ -63,7 +58,6 @@ struct GramIndexArgs {
 struct SolveArgs {
   const double2* P;      // LINES: per-line Grams; INDEX: chunk partials
   const double2* hp;
-  const int32_t* mask;
   const int32_t* m_k;
   const int32_t* pair_of;
   const int32_t* unit_of;    // LINES: sampled-line index of (frame k, line l)
@@ -88,8 +82,6 @@ struct BasisArgs {
   long n;
   int nx, r, nc, ua, txx, cgs;
   long part_stride;
-  const int32_t* rows;        // sampled rows (ky) of W / K, or null: all rows
-  const int32_t* n_rows_ptr;
   const int32_t* row_unit;    // k-space row -> row of W / K (-1: not kept), or null: identity
   const float2* tw;           // twiddles along y
   const float2* tw_x;         // twiddles along x
@@ -228,7 +220,7 @@ __device__ __forceinline__ float2 lane_get(float2 v, int src) { return make_floa
 __device__ __forceinline__ double2 lane_get(double2 v, int src) {
   return make_double2(lane_get(v.x, src), lane_get(v.y, src));
 }
-// v from another lane by a DPP move (CTRL: quad_perm / row_ror / row_half_mirror)
+// v from another lane by a DPP move (CTRL: quad_perm / row_ror)
 template <int CTRL>
 __device__ __forceinline__ double dpp_get(double v) {
   const unsigned long long b = (unsigned long long)__double_as_longlong(v);
@@ -245,7 +237,6 @@ __device__ __forceinline__ float dpp_getf(float v) {
 #define DPP_XOR2 0x4E       // quad_perm [2,3,0,1]
 #define DPP_ROR4 0x124      // row_ror:4
 #define DPP_ROR8 0x128      // row_ror:8
-#define DPP_HALF_MIRROR 0x141
 // maximum over the 64 lanes (every lane active)
 __device__ __forceinline__ double wave_max(double v) {
   v = fmax(v, dpp_get<DPP_XOR1>(v));
@@ -383,7 +374,6 @@ hipError_t launch_loss(const LossArgs& a, hipStream_t s);
 hipError_t launch_cnn_to_M(const float* Y4, int r, long n, int batch, float2* M, hipStream_t s);
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, long n, float lr, int step, hipStream_t s);
 hipError_t launch_cnn_planes(const float2* X, long n, int q, double* partial, float* out, hipStream_t s);
-// mixed form, 1D Cartesian masks: which 0 forward, 1 adjoint + coil combine
 int basis_txx(int N, int nx, int r);
 __global__ void k_build_lines(const float2* yh, const int2* pairs, const int4* items, int nc, int nx, int lmax,
                               float2* yu, float2* yg, const DevState* st);

@@ -556,7 +556,7 @@ template <typename T, int TRM, int NSM>
 __global__ __launch_bounds__(256 * NSM) void k_qr_gram_mma(GramColsArgs a) {
   using M = Mma<T>;
   constexpr int NT = TRM * (TRM + 1) / 2;
-  constexpr int RC = TRM <= 4 ? 64 : 32;  // rows per chunk staged in LDS (fewer for wide Grams: registers)
+  constexpr int RC = 64;  // rows per chunk staged in LDS
   // row pitch of the staged real embedding: the 4 rows one MFMA step reads
   // land in disjoint quarters of the 64 LDS banks
   constexpr int LDX = (16 * TRM) % 64 == 0 || (16 * TRM) % 64 == 32 ? 16 * TRM + 16 : 16 * TRM;
@@ -699,17 +699,14 @@ __global__ __launch_bounds__(256 * NSM) void k_qr_gram_mma(GramColsArgs a) {
 // (three or four row tiles keep their accumulators with one stream of 256 threads)
 hipError_t launch_qr_gram(const GramColsArgs& a, int nblk, bool fp64, hipStream_t s) {
   const int trm = (2 * (a.m1 + a.m2) + 15) / 16;
+  if (trm > 4) return hipErrorInvalidValue;
   const dim3 g(nblk);
   if (fp64) {
     switch (trm) {
       case 1: hipLaunchKernelGGL((k_qr_gram_mma<double, 1, QR_NSM>), g, dim3(256 * QR_NSM), 0, s, a); break;
       case 2: hipLaunchKernelGGL((k_qr_gram_mma<double, 2, QR_NSM>), g, dim3(256 * QR_NSM), 0, s, a); break;
       case 3: hipLaunchKernelGGL((k_qr_gram_mma<double, 3, 1>), g, dim3(256), 0, s, a); break;
-      case 4: hipLaunchKernelGGL((k_qr_gram_mma<double, 4, 1>), g, dim3(256), 0, s, a); break;
-      // wider Grams (the spectral init's q columns, up to 48)
-      case 5: hipLaunchKernelGGL((k_qr_gram_mma<double, 5, 1>), g, dim3(256), 0, s, a); break;
-      case 6: hipLaunchKernelGGL((k_qr_gram_mma<double, 6, 1>), g, dim3(256), 0, s, a); break;
-      default: return hipErrorInvalidValue;
+      default: hipLaunchKernelGGL((k_qr_gram_mma<double, 4, 1>), g, dim3(256), 0, s, a); break;
     }
   } else {
     switch (trm) {

@@ -1019,7 +1019,7 @@ __global__ __launch_bounds__(64 * EIG_W<NH>) void k_init_eig(InitEigArgs a) {
   __shared__ double s_d[NR], s_ea[NR], s_e2[NR], s_beta[NR];
   __shared__ double2 s_ec[NR], s_ph[NR];
   __shared__ double s_lam[16];
-  __shared__ double s_gs[4];  // Gershgorin interval (lo, hi) and scale of the scaled T_r, its unit
+  __shared__ double s_gs[4];  // Gershgorin interval (lo, hi) and scale of the scaled T_r, its unit in the matrix's terms
   const int tid = threadIdx.x, l = tid & 63, n = a.q, r = a.r;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   double2* const Vh = lds_m;
@@ -1039,13 +1039,28 @@ __global__ __launch_bounds__(64 * EIG_W<NH>) void k_init_eig(InitEigArgs a) {
       const int i = min(l + 64 * h, n - 1), j = min(wv + W * t, n - 1), lo = min(i, j), hi = max(i, j);
       A[h][t] = a.part[lo * n - lo * (lo - 1) / 2 + (hi - lo)];  // entry (lo, hi) of the upper triangle
     }
+  double dg[NH];
+#pragma unroll
+  for (int h = 0; h < NH; ++h) {
+    const int i = min(l + 64 * h, n - 1);
+    dg[h] = a.part[i * n - i * (i - 1) / 2].x;
+  }
+#pragma unroll
+  for (int h = 0; h < NH; ++h) {
+    asm volatile("" : "+v"(dg[h]));  // loaded, all at once, before anything is selected
+#pragma unroll
+    for (int t = 0; t < CT; ++t) asm volatile("" : "+v"(A[h][t].x), "+v"(A[h][t].y));
+  }
+  // scaled by a power of two to a largest entry of 0.5 to 1 (the diagonal's: the
+  // matrix is positive semidefinite)
+  const int ex0 = __builtin_amdgcn_frexp_exp(wave_max(NH == 2 ? fmax(dg[0], dg[NH - 1]) : dg[0]));
 #pragma unroll
   for (int h = 0; h < NH; ++h)
 #pragma unroll
     for (int t = 0; t < CT; ++t) {
       const int i = l + 64 * h, j = wv + W * t;
-      asm volatile("" : "+v"(A[h][t].x), "+v"(A[h][t].y));  // loaded, all at once, before it is selected
-      A[h][t] = dkeep(i < n && j < n, make_double2(A[h][t].x, i == j ? 0.0 : i < j ? A[h][t].y : -A[h][t].y));
+      const double re = __builtin_amdgcn_ldexp(A[h][t].x, -ex0), im = __builtin_amdgcn_ldexp(A[h][t].y, -ex0);
+      A[h][t] = dkeep(i < n && j < n, make_double2(re, i == j ? 0.0 : i < j ? im : -im));
     }
   int jb = wv;  // the column in register 0
   if (wv == 0) {
@@ -1117,9 +1132,12 @@ __global__ __launch_bounds__(64 * EIG_W<NH>) void k_init_eig(InitEigArgs a) {
       double2 alpha = x0;
       v0 = zero2;
       beta = 0.0;
-      const bool refl = k + 2 < n && !(sig == 0.0 && x0.y == 0.0);  // the same in every lane
+      // none either where the column has vanished beside the matrix: rounding
+      // errors of a rank-deficient one shrink by 1e-16 a step, and their squares
+      // would underflow (no reflector: the column's rest, below 1e-60, is dropped)
+      const double t = x0.x * x0.x + x0.y * x0.y, s = t + sig;
+      const bool refl = k + 2 < n && s > 1e-120 && !(sig == 0.0 && x0.y == 0.0);  // the same in every lane
       if (refl) {
-        const double t = x0.x * x0.x + x0.y * x0.y, s = t + sig;
         const double nrm = s * cx_rsqrt(s);
         const bool big = t > 1e-290;
         const double rt = cx_rsqrt(big ? t : 1.0), ax0 = big ? t * rt : 0.0;
@@ -1245,7 +1263,7 @@ __global__ __launch_bounds__(64 * EIG_W<NH>) void k_init_eig(InitEigArgs a) {
       s_gs[0] = __builtin_amdgcn_ldexp(glo - (1e-3 * wdt + 1e-300), -ex);
       s_gs[1] = __builtin_amdgcn_ldexp(ghi + (1e-3 * wdt + 1e-300), -ex);
       s_gs[2] = __builtin_amdgcn_ldexp(scale, -ex);
-      s_gs[3] = __builtin_amdgcn_ldexp(1.0, ex);
+      s_gs[3] = __builtin_amdgcn_ldexp(1.0, ex + ex0);
     }
   }
   __syncthreads();

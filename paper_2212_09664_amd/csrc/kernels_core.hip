@@ -487,6 +487,10 @@ __global__ __launch_bounds__(256) void k_step_apply(QrSmallArgs a, ApplyArgs ap)
   const int err0 = st->err;
   const int halt0 = __hip_atomic_load(&st->halt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const double eta0 = __hip_atomic_load(&st->eta, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // ... and, for the deferred statistics, a frame's cost per thread of workgroup 0's last two waves
+  const bool keep_cost = blockIdx.x == 0 && step && a.commit_direct && tid >= 128 && tid - 128 < a.q;
+  double cost = 0.0;
+  if (keep_cost) cost = a.cost_k[tid - 128];
   float2 u0[RT], g0[RT];
   if (a.mode != STEP_MODE_ETA) {
 #pragma unroll
@@ -683,8 +687,7 @@ __global__ __launch_bounds__(256) void k_step_apply(QrSmallArgs a, ApplyArgs ap)
     keep_src();
     return;
   }
-  if (blockIdx.x == 0 && step && a.commit_direct && tid >= 128 && tid - 128 < a.q)
-    reinterpret_cast<double*>(a.stats_src + 769)[tid - 128] = a.cost_k[tid - 128];
+  if (keep_cost) reinterpret_cast<double*>(a.stats_src + 769)[tid - 128] = cost;
   if (p >= n) return;
   // U+ R = U - eta grad for this pixel (forward substitution, 1 / R_jj on the diagonal)
   const float etaf = (float)eta;

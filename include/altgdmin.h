@@ -279,9 +279,9 @@ altgdmin_status altgdmin_mean(altgdmin_ctx* ctx, double tol, int32_t maxit, void
  * altgdmin_mean (bitwise: the same kernels in the same order); its scratch
  * (three n-vectors, nc*n coil images, reduction partials and scalars) is a
  * 16 MiB array built into the library, one per GPU, kept until the process
- * ends.  Problems whose scratch exceeds it (8 (3 + nc) n bytes plus about
- * 2 KiB; e.g. 256x256 with up to 28 coils) return ALTGDMIN_ESCRATCH before
- * any launch.  Calls allocate nothing.  Every call on one GPU shares that
+ * ends.  Problems whose scratch exceeds it (8 (3 + nc) n bytes plus at most
+ * 20 KiB; e.g. 256x256 fits with up to 28 coils) return ALTGDMIN_ESCRATCH
+ * before any launch.  Calls allocate nothing.  Every call on one GPU shares that
  * GPU's scratch, so calls that overlap on one GPU (two streams, two threads)
  * race and must be serialised by the caller.  The stream's device must be
  * the current device. */
@@ -291,7 +291,7 @@ altgdmin_status altgdmin_mean_noalloc(altgdmin_ctx* ctx, double tol, int32_t max
 /* Residual measurements (Algorithm 1, steps 2a and 3a):
  * d_yres = y - A(zbar 1^T + X), frame by frame, in the padded layout (padding
  * written as 0).  d_zbar (n) and d_X (n x q) may each be NULL (then taken as
- * zero).  d_yres must not alias y. */
+ * zero).  d_yres must not alias y; it may share memory with d_zbar or d_X. */
 altgdmin_status altgdmin_residual(altgdmin_ctx* ctx, const void* d_zbar, const void* d_X, void* d_yres,
                                   void* d_aux);
 

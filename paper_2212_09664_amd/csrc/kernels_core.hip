@@ -1013,7 +1013,7 @@ __device__ __forceinline__ void backtransform(const double2* Vh, const double* s
 // column t and read with v_readlane.  Wave 0 alone forms w, the next column
 // and its reflector in between: two barriers a step.  (A version with the matrix
 // in LDS and four barriers took 580 us at 100 frames and rank 10, 140 us at 40
-// and rank 8, 53 us at 16 and rank 4; this one 362, 90 and 35 us.)
+// and rank 8, 53 us at 16 and rank 4; this one 363, 95 and 35 us.)
 // ===========================================================================
 template <int NH>
 __global__ __launch_bounds__(64 * EIG_W<NH>) void k_init_eig(InitEigArgs a) {

@@ -249,8 +249,8 @@ __global__ __launch_bounds__(NT) void k_cols_fwd(ColFwdArgs a) {
 // sampled rows enter the first radix pass straight from registers through
 // the inverse row map in LDS, the coil-weighted sum is taken on the last
 // pass's registers, and the next coil's rows are loaded during the current
-// transform.  512 x 512, 16 coils, 24 frames: 218 us and the forward columns
-// 208 us (578 and 301 us with every radix pass through LDS), bound by the
+// transform.  512 x 512, 16 coils, 24 frames: 219 us and the forward columns
+// 185 us (578 and 301 us with every radix pass through LDS), bound by the
 // radix arithmetic.  Each workgroup runs NG groups of NT threads on alternate coils,
 // whose sums meet in LDS: the waves that one tile of columns can keep busy.  A
 // coil in turn costs a round trip to memory, 2.5 us, so the short columns (one or
